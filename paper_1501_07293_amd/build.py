@@ -15,8 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmmag.so")
 # the two largest first, so that the pool compiles them side by side
-SOURCES = ["mm_fast.hip", "mm_fused.hip", "mm_api.hip", "mm_passes.hip", "mm_tensor.hip", "mm_llg.hip",
-           "mm_adjoint.hip", "mm_batch.hip"]
+SOURCES = ["mm_fast.hip", "mm_fused.hip", "mm_rline.hip", "mm_api.hip", "mm_passes.hip", "mm_tensor.hip", "mm_llg.hip",
+           "mm_adjoint.hip", "mm_batch.hip", "mm_batch_rline.hip"]
 ARCH = os.environ.get("MMAG_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -44,7 +44,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", *objs, "-o", tmp]

@@ -119,6 +119,8 @@ struct Plan {
     int prec;
     size_t esz;        // sizeof(T)
     FftPlan fx, fy, fz;
+    LinePlan lx, ly, lz;       // schedules of the runtime-length register passes (ns = 0: none)
+    RShape rs;                 // and their work-group shapes
     int x_lines, y_tw, k_tw;
     int xl, xl_inv;    // complex lines per work-group of the specialised x passes (forward, inverse)
     int64_t S_planes, S_rows;  // spectrum [3][S_planes][hx][S_rows]
@@ -144,7 +146,15 @@ struct Plan {
 // latency-bound.
 constexpr int64_t kFusedStageMaxCells = (int64_t)1 << 20;
 
-mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p)
+// Shapes of the runtime-length passes in a batch: 256 threads a work-group, which every
+// grid fills (the launch holds the tiles of all of them).
+RShape batch_shapes(const Plan& p)
+{
+    return rline_shapes(p.lx, p.ly, p.lz, p.nx, p.ny, p.nz, p.esz, 256, 0);
+}
+
+// two_plane: a batch of runtime-length passes takes the two-plane schedule too
+mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_plane = false)
 {
     if (!g) return fail(MM_EINVAL, "grid is NULL");
     if (g->nx < 1 || g->ny < 1 || g->nz < 1)
@@ -252,15 +262,19 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p)
     }
     if (!make_fft_plan(p->Px, &p->fx) || !make_fft_plan(p->Py, &p->fy) || !make_fft_plan(p->Pz, &p->fz))
         return fail(MM_EINVAL, "padded sizes must be 7-smooth");
+    (void)make_line_plan(p->Px, &p->lx);
+    (void)make_line_plan(p->Py, &p->ly);
+    (void)make_line_plan(p->Pz, &p->lz);
+    p->rs = rline_shapes(p->lx, p->ly, p->lz, p->nx, p->ny, p->nz, p->esz, 512, 256);
     const int cap = kElemsPerThread * nt, ldscap = cap + 64;
     p->x_lines = std::min(cap / p->Px, ldscap / (p->Px + 1));
     p->y_tw = std::max(1, std::min(64, cap / p->Py));
     p->k_tw = std::max(1, std::min(64, cap / (3 * last)));
     // two cells along z with an open z axis (Pz = 4) and a specialised two-plane
     // pass of length Py: no z transform and no Py-long spectrum in HBM
-    p->zd = p->nz == 2 && p->Pz == 4 && !(p->per & 4) && !p->yz && !p->wg1 &&
-            !(o->flags & MM_GENERIC_FFT) && fast_ky2_lines(p->Py) > 0 && p->ny <= p->Py &&
-            !(p->esz == 8 && p->Py > 1024);
+    p->zd = p->nz == 2 && p->Pz == 4 && !(p->per & 4) && !p->yz && !p->wg1 && p->ny <= p->Py &&
+            ((!(o->flags & MM_GENERIC_FFT) && fast_ky2_lines(p->Py) > 0 && !(p->esz == 8 && p->Py > 1024)) ||
+             (two_plane && batch_shapes(*p).ky2 > 0));
     // open, small (latency-bound), with the specialised passes: the fused stage pass
     // (the y / z passes of one-cell-thick and thicker grids run between its launches)
     p->fs_lines = 0;
@@ -296,9 +310,10 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p)
     p->o_S = take(3 * (size_t)p->S_planes * p->hx * p->S_rows * 2 * p->esz);
     p->o_S2 = p->fs ? take(3 * (size_t)p->S_planes * p->hx * p->S_rows * 2 * p->esz) : 0;
     p->o_kern = take((size_t)p->kplanes * p->oct_elems * p->esz);
-    p->o_twx = take((size_t)p->Px * 2 * p->esz);
-    p->o_twy = take((size_t)p->Py * 2 * p->esz);
-    p->o_twz = take((size_t)p->Pz * 2 * p->esz);
+    // twiddles: the plain table of P entries, then the stage table (LinePlan)
+    p->o_twx = take((size_t)p->Px * 4 * p->esz);
+    p->o_twy = take((size_t)p->Py * 4 * p->esz);
+    p->o_twz = take((size_t)p->Pz * 4 * p->esz);
     p->o_twxd = take((size_t)p->Px * 16);
     p->o_twyd = take((size_t)p->Py * 16);
     p->o_twzd = take((size_t)p->Pz * 16);
@@ -467,12 +482,23 @@ PassCtx pass_ctx(const mm_sim* s)
                    s->at<char>(p.o_kern)};
 }
 
+// The stage table of a length behind its plain twiddles.
+const void* stage_tw(const Plan& p, const void* tw, int P)
+{
+    return static_cast<const char*>(tw) + (size_t)P * 2 * p.esz;
+}
+void* stage_tw(const Plan& p, char* tw, int P) { return tw + (size_t)P * 2 * p.esz; }
+
 template <typename T>
 hipError_t pass_x_forward(const PassCtx& c, const T* m, hipStream_t st)
 {
     const Plan& p = c.p;
     XLineArgs xa{m, c.S, c.nplanes, p.ny, p.nx, c.Sy, c.twx, p.xl};
     if (c.fast && launch_xline<T>(xa, p.Px, 0, st)) return hipGetLastError();
+    if (p.rs.lsh_f >= 0) {
+        const RXArgs ra{m, c.S, c.nplanes, p.ny, p.nx, c.Sy, stage_tw(p, c.twx, p.Px), p.rs.lsh_f};
+        return launch_rxline<T>(ra, p.lx, 0, st);
+    }
     RowR2CArgs r{};
     r.in = m;
     r.in_row_stride = p.nx;
@@ -502,6 +528,10 @@ hipError_t pass_y(const PassCtx& c, int inverse, hipStream_t st)
     // nothing, and in FP64 it is slower (116 -> 136 us)
     YLineArgs ya{c.S, c.nplanes * p.hx, c.Sy, nin, nout, c.twy, (inverse && p.esz == 4) ? c.nplanes : 0};
     if (c.fast && launch_yline<T>(ya, p.Py, inverse, st)) return hipGetLastError();
+    if (p.rs.y > 0) {
+        const RYArgs ra{c.S, ya.nlines, c.Sy, nin, nout, stage_tw(p, c.twy, p.Py), ya.kx_major, p.rs.y};
+        return launch_ryline<T>(ra, p.ly, inverse, st);
+    }
     ColArgs cy{};
     cy.buf = c.S;
     cy.nplanes = c.nplanes;
@@ -549,9 +579,19 @@ hipError_t pass_kspace(const PassCtx& c, hipStream_t st)
         k.tw = c.twz;
         k.axis_is_z = 1;
         if (c.fast && launch_kspace_fixed<T>(k, p.Pz, st)) return hipGetLastError();
+        if (p.rs.csh >= 0) {
+            const RKzArgs ra{c.S, kz.comp_stride, kz.ncols, p.nz, p.Py, stage_tw(p, c.twz, p.Pz), c.kern,
+                             p.oct_elems, k_zs, k_xs, p.rs.csh};
+            return launch_rkz<T>(ra, p.lz, st);
+        }
     } else {
         KyArgs ky{c.S, c.plane, c.Sy, p.hx, p.ny, c.twy, c.kern, p.oct_elems, k_xs};
         if (c.fast && launch_kspace_y<T>(ky, p.Py, st)) return hipGetLastError();
+        if (p.rs.ky > 0) {
+            const RKyArgs ra{c.S, c.plane, c.Sy, p.hx, p.ny, stage_tw(p, c.twy, p.Py), c.kern, p.oct_elems, k_xs,
+                             p.rs.ky, div_mul(p.Py)};
+            return launch_rky<T>(ra, p.ly, st);
+        }
         k.comp_stride = c.plane;
         k.ncols = p.hx;
         k.cols_per_row = 1;
@@ -571,6 +611,10 @@ hipError_t pass_x_inverse(const PassCtx& c, T* h, hipStream_t st)
     const Plan& p = c.p;
     XLineArgs xa{c.S, h, c.nplanes, p.ny, p.nx, c.Sy, c.twx, p.xl_inv};
     if (c.fast && launch_xline<T>(xa, p.Px, 1, st)) return hipGetLastError();
+    if (p.rs.lsh_i >= 0) {
+        const RXArgs ra{c.S, h, c.nplanes, p.ny, p.nx, c.Sy, stage_tw(p, c.twx, p.Px), p.rs.lsh_i};
+        return launch_rxline<T>(ra, p.lx, 1, st);
+    }
     RowC2RArgs r{};
     r.in = c.S;
     r.rows_per_plane = p.ny;
@@ -808,6 +852,9 @@ mm_status build_kernel_spectrum(mm_sim* s, hipStream_t st)
     HIP_TRY(launch_twiddles<T>(s->at<char>(p.o_twx), p.Px, st));
     HIP_TRY(launch_twiddles<T>(s->at<char>(p.o_twy), p.Py, st));
     HIP_TRY(launch_twiddles<T>(s->at<char>(p.o_twz), p.Pz, st));
+    HIP_TRY(launch_stage_twiddles<T>(stage_tw(p, s->at<char>(p.o_twx), p.Px), p.lx, st));
+    HIP_TRY(launch_stage_twiddles<T>(stage_tw(p, s->at<char>(p.o_twy), p.Py), p.ly, st));
+    HIP_TRY(launch_stage_twiddles<T>(stage_tw(p, s->at<char>(p.o_twz), p.Pz), p.lz, st));
     HIP_TRY(launch_twiddles<double>(s->at<char>(p.o_twxd), p.Px, st));
     HIP_TRY(launch_twiddles<double>(s->at<char>(p.o_twyd), p.Py, st));
     HIP_TRY(launch_twiddles<double>(s->at<char>(p.o_twzd), p.Pz, st));
@@ -1591,7 +1638,13 @@ struct BatchLayout {
     size_t o_classes = 0;
     int64_t class_ints = 0;
     std::vector<BatchDesc> desc;
-    std::vector<int> prefix[4];   // runtime-radix passes: x forward, y, k-space, x inverse
+    // runtime-length passes: x forward, y, k-space (along z), x inverse, and in the
+    // register form (rline) k-space along y and the two-plane k-space; lds: the dynamic
+    // LDS of a work-group
+    static constexpr int kPasses = 6;
+    std::vector<int> prefix[kPasses];
+    size_t lds[kPasses] = {0, 0, 0, 0, 0, 0};
+    bool rline = false;
     int64_t vec_elems = 0, S_elems = 0, kern_elems = 0, tw_elems = 0, cells = 0;
     size_t scratch = 0;
     size_t o_desc, o_prefix, o_mn, o_ma, o_mb, o_acc, o_hd, o_S, o_kern, o_tw, o_flags, o_scratch, total;
@@ -1617,12 +1670,14 @@ mm_status batch_layout(int32_t n, const mm_grid* grids, const mm_options* opt, B
     // size classes (the specialised passes) are wanted with power-of-two or fast
     // padding; otherwise every grid runs the runtime-radix passes, whose plans
     // must not take the two-plane schedule.  If some grid has no size class, the
-    // layout is built again that way.
+    // layout is built again that way, with the register passes where every grid has
+    // them, else with the LDS-staged ones.
     const bool want_fast = (o.flags & (MM_POW2_PAD | MM_FAST_PAD)) && !(o.flags & MM_GENERIC_FFT);
-    for (int attempt = want_fast ? 0 : 1; attempt < 2; ++attempt) {
+    for (int attempt = want_fast ? 0 : 1; attempt < 3; ++attempt) {
         mm_options oa = o;
-        if (attempt == 1) oa.flags |= MM_GENERIC_FFT;
-        L->plan_generic = attempt == 1;
+        if (attempt >= 1) oa.flags |= MM_GENERIC_FFT;
+        L->plan_generic = attempt >= 1;
+        L->rline = attempt == 1;
         L->pad.assign(n, {0, 0});
         // size classes holding a small share of the cells are padded up into the next
         // class of their axis (at most a few rounds: each round removes a class)
@@ -1631,7 +1686,7 @@ mm_status batch_layout(int32_t n, const mm_grid* grids, const mm_options* opt, B
             if (st != MM_OK) return st;
             if (!L->fast || !merge_small_classes(n, L)) break;
         }
-        if (L->fast || !want_fast) break;
+        if (L->fast || L->rline) break;
     }
     return batch_layout_offsets(n, L);
 }
@@ -1674,7 +1729,10 @@ mm_status batch_layout_plans(int32_t n, const mm_grid* grids, const mm_options* 
     L->class_ints = 0;
     L->plans.assign(n, Plan{});
     L->desc.resize(n);
-    for (int q = 0; q < 4; ++q) L->prefix[q].assign(n + 1, 0);
+    for (int q = 0; q < BatchLayout::kPasses; ++q) {
+        L->prefix[q].assign(n + 1, 0);
+        L->lds[q] = 0;
+    }
     for (int s = 0; s < n; ++s) {
         Plan& p = L->plans[s];
         mm_options og = o;
@@ -1682,7 +1740,7 @@ mm_status batch_layout_plans(int32_t n, const mm_grid* grids, const mm_options* 
             og.px = L->pad[s][0];
             og.py = L->pad[s][1];
         }
-        mm_status st = build_plan(&grids[s], &og, &p);
+        mm_status st = build_plan(&grids[s], &og, &p, L->rline);
         if (st != MM_OK) {
             std::string keep = g_err;
             return fail(st, "grid %d: %s", s, keep.c_str());
@@ -1707,24 +1765,51 @@ mm_status batch_layout_plans(int32_t n, const mm_grid* grids, const mm_options* 
         d.koff = L->kern_elems;
         d.oct = p.oct_elems;
         d.twx = L->tw_elems;
-        d.twy = d.twx + p.Px;
-        d.twz = d.twy + p.Py;
+        d.twy = d.twx + 2 * p.Px;  // plain and stage tables
+        d.twz = d.twy + 2 * p.Py;
         d.fx = p.fx;
         d.fy = p.fy;
         d.fz = p.fz;
+        d.lx = p.lx;
+        d.ly = p.ly;
+        d.lz = p.lz;
+        d.rs = batch_shapes(p);
+        d.pymul = div_mul(p.Py);
         L->vec_elems += 3 * p.N;
         L->S_elems += 3 * (int64_t)p.nz * p.hx * p.S_rows;
         L->kern_elems += (int64_t)p.kplanes * p.oct_elems;
-        L->tw_elems += p.Px + p.Py + p.Pz;
+        L->tw_elems += 2 * (p.Px + p.Py + p.Pz);
         L->cells += p.N;
         L->scratch = std::max(L->scratch, p.total);
-        const int npairs = (3 * p.nz * p.ny + 1) / 2;
-        const int tiles[4] = {
-            (npairs + p.x_lines - 1) / p.x_lines,
-            p.three_d ? (3 * p.nz * p.hx + d.y_lines - 1) / d.y_lines : 0,
-            p.three_d ? (int)((p.hx * (int64_t)p.Py + p.k_tw - 1) / p.k_tw) : (p.hx + p.k_tw - 1) / p.k_tw,
-            (npairs + p.x_lines - 1) / p.x_lines};
-        for (int q = 0; q < 4; ++q) L->prefix[q][s + 1] = L->prefix[q][s] + tiles[q];
+        const RShape& r = d.rs;
+        if (L->rline && (r.lsh_f < 0 || r.lsh_i < 0 || (p.zd ? r.ky2 <= 0 : (p.three_d ? r.y <= 0 || r.csh < 0 : r.ky <= 0))))
+            L->rline = false;
+        int tiles[BatchLayout::kPasses] = {0};
+        auto up = [](int64_t a, int64_t b) { return (int)((a + b - 1) / b); };
+        auto pass = [&](int q, int t, size_t bytes) {
+            tiles[q] = t;
+            L->lds[q] = std::max(L->lds[q], bytes);
+        };
+        if (L->rline) {
+            const size_t e = p.esz;
+            pass(0, 3 * p.nz * up(p.ny, 2 << r.lsh_f), rline_lds_bytes(1 << r.lsh_f, p.Px, e));
+            pass(3, 3 * p.nz * up(p.ny, 2 << r.lsh_i), rxinv_lds_bytes(r.lsh_i, p.Px, e));
+            if (p.zd) {
+                pass(5, up(p.hx, r.ky2), rline_lds_bytes(6 * r.ky2, p.Py, e));
+            } else if (p.three_d) {
+                pass(1, up(3 * (int64_t)p.nz * p.hx, r.y), rline_lds_bytes(r.y, p.Py, e));
+                pass(2, up(p.hx * (int64_t)p.Py, 1 << r.csh), rline_lds_bytes(3 << r.csh, p.Pz, e));
+            } else {
+                pass(4, up(p.hx, r.ky), rline_lds_bytes(3 * r.ky, p.Py, e));
+            }
+        } else {
+            const int npairs = (3 * p.nz * p.ny + 1) / 2;
+            pass(0, up(npairs, p.x_lines), 0);
+            pass(3, up(npairs, p.x_lines), 0);
+            pass(1, p.three_d ? up(3 * (int64_t)p.nz * p.hx, d.y_lines) : 0, 0);
+            pass(2, p.three_d ? up(p.hx * (int64_t)p.Py, p.k_tw) : up(p.hx, p.k_tw), 0);
+        }
+        for (int q = 0; q < BatchLayout::kPasses; ++q) L->prefix[q][s + 1] = L->prefix[q][s] + tiles[q];
     }
     L->prec = o.prec;
     L->esz = o.prec == MM_F32 ? 4 : 8;
@@ -1806,7 +1891,7 @@ mm_status batch_layout_offsets(int32_t n, BatchLayout* L)
     };
     const size_t vec = (size_t)L->vec_elems * L->esz;
     L->o_desc = take(n * sizeof(BatchDesc));
-    L->o_prefix = take(4 * (size_t)(n + 1) * sizeof(int));
+    L->o_prefix = take(BatchLayout::kPasses * (size_t)(n + 1) * sizeof(int));
     L->o_mn = take(vec);
     L->o_ma = take(vec);
     L->o_mb = take(vec);
@@ -1894,6 +1979,20 @@ mm_status batch_demag(mm_batch* b, const T* in, hipStream_t st)
     p.tw = b->at<cpx<T>>(L.o_tw);
     p.out = b->at<T>(L.o_hd);
     p.in = in;
+    if (L.rline) {
+        auto pass = [&](int which, int q, int inverse) {
+            p.prefix = pre + q * (n + 1);
+            return launch_batch_rline<T>(which, p, L.prefix[q][n], inverse, L.lds[q], st);
+        };
+        HIP_TRY(pass(0, 0, 0));
+        HIP_TRY(pass(1, 1, 0));
+        HIP_TRY(pass(2, 2, 0));
+        HIP_TRY(pass(4, 4, 0));
+        HIP_TRY(pass(5, 5, 0));
+        HIP_TRY(pass(1, 1, 1));
+        HIP_TRY(pass(3, 3, 0));
+        return MM_OK;
+    }
     p.prefix = pre + 0 * (n + 1);
     HIP_TRY(launch_batch_pass<T>(0, p, L.prefix[0][n], 0, st));
     p.prefix = pre + 1 * (n + 1);
@@ -2360,6 +2459,10 @@ mm_status mm_workspace_query(const mm_grid* grid, const mm_options* opt, size_t*
     return MM_OK;
 }
 
+// A handle on the plan of opt as given (no autotuning); two_plane as build_plan's.
+static mm_status create_plain(const mm_grid* grid, const mm_material* mat, const mm_options* opt,
+                              void* d_workspace, size_t ws_bytes, void* stream, bool two_plane, mm_sim** out);
+
 mm_status mm_create(const mm_grid* grid, const mm_material* mat, const mm_options* opt,
                     void* d_workspace, size_t ws_bytes, void* stream, mm_sim** out)
 {
@@ -2407,8 +2510,15 @@ mm_status mm_create(const mm_grid* grid, const mm_material* mat, const mm_option
         }
         return r;
     }
+    return create_plain(grid, mat, opt, d_workspace, ws_bytes, stream, false, out);
+}
+
+static mm_status create_plain(const mm_grid* grid, const mm_material* mat, const mm_options* opt,
+                              void* d_workspace, size_t ws_bytes, void* stream, bool two_plane, mm_sim** out)
+{
+    *out = nullptr;
     Plan p;
-    mm_status st = build_plan(grid, opt, &p);
+    mm_status st = build_plan(grid, opt, &p, two_plane);
     if (st != MM_OK) return st;
     if (!check_material(mat))
         return fail(MM_EINVAL, "material needs Ms > 0, A >= 0, alpha >= 0, gamma > 0, all finite");
@@ -2877,8 +2987,8 @@ static mm_status batch_build(int32_t n, const mm_grid* grids, const mm_material*
     e = hipMemcpyAsync(b->at<char>(BL.o_desc), BL.desc.data(), n * sizeof(BatchDesc),
                        hipMemcpyHostToDevice, hs);
     if (e != hipSuccess) return bail(fail(MM_EHIP, "descriptor upload: %s", hipGetErrorString(e)));
-    std::vector<int> pre(4 * (size_t)(n + 1));
-    for (int q = 0; q < 4; ++q)
+    std::vector<int> pre(BatchLayout::kPasses * (size_t)(n + 1));
+    for (int q = 0; q < BatchLayout::kPasses; ++q)
         for (int s = 0; s <= n; ++s) pre[q * (n + 1) + s] = BL.prefix[q][s];
     e = hipMemcpyAsync(b->at<char>(BL.o_prefix), pre.data(), pre.size() * sizeof(int),
                        hipMemcpyHostToDevice, hs);
@@ -2900,7 +3010,7 @@ static mm_status batch_build(int32_t n, const mm_grid* grids, const mm_material*
     mm_options o = opt ? *opt : mm_options{};
     o.threads = 256;
     o.flags &= ~(uint32_t)MM_USE_GRAPH;
-    if (BL.plan_generic) o.flags |= MM_GENERIC_FFT;  // the same plans (no two-plane schedule)
+    if (BL.plan_generic) o.flags |= MM_GENERIC_FFT;  // the same plans
     for (int s = 0; s < n; ++s) {
         const Plan& p = BL.plans[s];
         const BatchDesc& d = BL.desc[s];
@@ -2908,20 +3018,22 @@ static mm_status batch_build(int32_t n, const mm_grid* grids, const mm_material*
         mm_options og = o;  // the grid's padded sizes as the layout planned them
         og.px = BL.pad[s][0];
         og.py = BL.pad[s][1];
-        mm_status r = mm_create(&grids[s], &b->mats[s], &og, b->at<char>(BL.o_scratch), BL.scratch, stream, &t);
+        og.flags &= ~(uint32_t)MM_AUTOTUNE;
+        mm_status r = create_plain(&grids[s], &b->mats[s], &og, b->at<char>(BL.o_scratch), BL.scratch, stream,
+                                   BL.rline, &t);
         if (r != MM_OK) return bail(r);
         const size_t esz = BL.esz;
         hipError_t ce = hipMemcpyAsync(b->at<char>(BL.o_kern) + d.koff * esz, t->at<char>(p.o_kern),
                                        (size_t)p.kplanes * p.oct_elems * esz, hipMemcpyDeviceToDevice, hs);
         const size_t cz = 2 * esz;
         if (ce == hipSuccess)
-            ce = hipMemcpyAsync(b->at<char>(BL.o_tw) + d.twx * cz, t->at<char>(p.o_twx), p.Px * cz,
+            ce = hipMemcpyAsync(b->at<char>(BL.o_tw) + d.twx * cz, t->at<char>(p.o_twx), 2 * p.Px * cz,
                                 hipMemcpyDeviceToDevice, hs);
         if (ce == hipSuccess)
-            ce = hipMemcpyAsync(b->at<char>(BL.o_tw) + d.twy * cz, t->at<char>(p.o_twy), p.Py * cz,
+            ce = hipMemcpyAsync(b->at<char>(BL.o_tw) + d.twy * cz, t->at<char>(p.o_twy), 2 * p.Py * cz,
                                 hipMemcpyDeviceToDevice, hs);
         if (ce == hipSuccess)
-            ce = hipMemcpyAsync(b->at<char>(BL.o_tw) + d.twz * cz, t->at<char>(p.o_twz), p.Pz * cz,
+            ce = hipMemcpyAsync(b->at<char>(BL.o_tw) + d.twz * cz, t->at<char>(p.o_twz), 2 * p.Pz * cz,
                                 hipMemcpyDeviceToDevice, hs);
         mm_destroy(t);  // waits for the stream, so the scratch is free for the next grid
         if (ce != hipSuccess) return bail(fail(MM_EHIP, "spectrum copy: %s", hipGetErrorString(ce)));

@@ -10,21 +10,7 @@
 
 namespace mm {
 
-constexpr int kBatchNT = 256;
 static_assert(kBatchNT == kLlgNT, "the batched LLG pass launches kLlgNT threads per work-group");
-
-__device__ inline int find_sample(const int* prefix, int n, int tile)
-{
-    int lo = 0, hi = n;  // prefix[lo] <= tile < prefix[hi]; empty grids are skipped
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (prefix[mid] <= tile)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
-}
 
 template <typename T>
 __global__ __launch_bounds__(kBatchNT) void kb_xfwd(BatchPass<T> p)

@@ -66,6 +66,20 @@ struct FftPlan {
     int tstride[kMaxStages];  // index step into the length-P twiddle table
 };
 
+// Schedule of one line length for the runtime-length register passes (mm_rline.hpp):
+// TL threads a line, one butterfly per thread and stage.  Stage q has radix R[q], span
+// p[q] (the product of the earlier radices) and m[q] = P / R[q] butterflies; pmul and
+// tmul are the multipliers floor(2^32 / d) + 1 that divide by p[q] and TL; its twiddles
+// exp(-2 pi i r k / (p R)) lie at toff[q] + (r - 1) p + k of the length's stage table
+// (P - R[0] entries in all, stored right behind the plain table of P entries).
+constexpr int kMaxLineStages = 5;
+struct LinePlan {
+    int P, ns, TL;  // ns = 0: no such schedule
+    unsigned tmul;
+    int R[kMaxLineStages], p[kMaxLineStages], m[kMaxLineStages], toff[kMaxLineStages];
+    unsigned pmul[kMaxLineStages];
+};
+
 // Elements each thread keeps in registers per stage (times a radix rounding).
 constexpr int kElemsPerThread = 16;
 

@@ -787,6 +787,43 @@ __device__ inline void body_kspace_y(const KyArgs& a, int tile, cpx<T>* lds)
 // x bins, six lines each (three components of both planes), runs the forward
 // y FFT (stage 1 from global memory), the block product in LDS, and the inverse
 // (last stage to global memory).
+// The two-plane block product of one frequency: line (component c, plane z) at
+// q + (2 c + z) stride, the coefficients kv of the frequency's octant entry, sy = -1 for a
+// mirrored ky.
+template <typename T>
+__device__ inline void two_plane_product(cpx<T>* base, int stride, T sy, const T (&kv)[kTwoPlaneTablePlanes])
+{
+    const T xx0 = kv[0], xx1 = kv[1], xy0 = sy * kv[2], xy1 = sy * kv[3];
+    const T sxz = kv[4], yy0 = kv[5], yy1 = kv[6], syz = sy * kv[7];
+    const T zz0 = kv[8], zz1 = kv[9];
+    cpx<T>* p[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) p[q] = base + q * stride;
+    const cpx<T> ax = *p[0], bx = *p[1], ay = *p[2], by = *p[3], az = *p[4], bz = *p[5];
+    // plane 0 (observer z = 0): K^(0) a + K^(-1) b, with K^(-1)_xz = -i Sxz, K^(-1)_yz = -i Syz
+    // plane 1 (observer z = 1): K^(1) a + K^(0) b, with K^(1)_xz = i Sxz, K^(1)_yz = i Syz
+    // (-i s (u + i v) = s v - i s u; i s (u + i v) = -s v + i s u)
+    const cpx<T> h0x = {xx0 * ax.re + xy0 * ay.re + xx1 * bx.re + xy1 * by.re + sxz * bz.im,
+                        xx0 * ax.im + xy0 * ay.im + xx1 * bx.im + xy1 * by.im - sxz * bz.re};
+    const cpx<T> h0y = {xy0 * ax.re + yy0 * ay.re + xy1 * bx.re + yy1 * by.re + syz * bz.im,
+                        xy0 * ax.im + yy0 * ay.im + xy1 * bx.im + yy1 * by.im - syz * bz.re};
+    const cpx<T> h0z = {zz0 * az.re + zz1 * bz.re + sxz * bx.im + syz * by.im,
+                        zz0 * az.im + zz1 * bz.im - sxz * bx.re - syz * by.re};
+    const cpx<T> h1x = {xx1 * ax.re + xy1 * ay.re + xx0 * bx.re + xy0 * by.re - sxz * az.im,
+                        xx1 * ax.im + xy1 * ay.im + xx0 * bx.im + xy0 * by.im + sxz * az.re};
+    const cpx<T> h1y = {xy1 * ax.re + yy1 * ay.re + xy0 * bx.re + yy0 * by.re - syz * az.im,
+                        xy1 * ax.im + yy1 * ay.im + xy0 * bx.im + yy0 * by.im + syz * az.re};
+    const cpx<T> h1z = {zz1 * az.re + zz0 * bz.re - sxz * ax.im - syz * ay.im,
+                        zz1 * az.im + zz0 * bz.im + sxz * ax.re + syz * ay.re};
+    // stored conjugated: the inverse transform runs as a forward one
+    *p[0] = conj(h0x);
+    *p[1] = conj(h1x);
+    *p[2] = conj(h0y);
+    *p[3] = conj(h1y);
+    *p[4] = conj(h0z);
+    *p[5] = conj(h1z);
+}
+
 template <int P>
 constexpr int ky2_lines() { return (256 / (6 * (P / Sched<P>::R0))) > 0 ? 256 / (6 * (P / Sched<P>::R0)) : 1; }
 
@@ -843,36 +880,7 @@ __device__ inline void body_kspace_y2(const Ky2Args& a, int tile, cpx<T>* lds)
         const int l2 = idx / P, e = idx - l2 * P, kx2 = tile * L + l2;
         if (idx >= L * P || kx2 >= a.hx) continue;
         const T sy = 2 * e > P ? (T)-1 : (T)1;
-        const T xx0 = kv[it][0], xx1 = kv[it][1], xy0 = sy * kv[it][2], xy1 = sy * kv[it][3];
-        const T sxz = kv[it][4], yy0 = kv[it][5], yy1 = kv[it][6], syz = sy * kv[it][7];
-        const T zz0 = kv[it][8], zz1 = kv[it][9];
-        // line (component c, plane z) of bin l2 at LDS line (2 c + z) L + l2
-        cpx<T>* p[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) p[q] = lds + (q * L + l2) * LP + pad16(e);
-        const cpx<T> ax = *p[0], bx = *p[1], ay = *p[2], by = *p[3], az = *p[4], bz = *p[5];
-        // plane 0 (observer z = 0): K^(0) a + K^(-1) b, with K^(-1)_xz = -i Sxz, K^(-1)_yz = -i Syz
-        // plane 1 (observer z = 1): K^(1) a + K^(0) b, with K^(1)_xz = i Sxz, K^(1)_yz = i Syz
-        // (-i s (u + i v) = s v - i s u; i s (u + i v) = -s v + i s u)
-        const cpx<T> h0x = {xx0 * ax.re + xy0 * ay.re + xx1 * bx.re + xy1 * by.re + sxz * bz.im,
-                            xx0 * ax.im + xy0 * ay.im + xx1 * bx.im + xy1 * by.im - sxz * bz.re};
-        const cpx<T> h0y = {xy0 * ax.re + yy0 * ay.re + xy1 * bx.re + yy1 * by.re + syz * bz.im,
-                            xy0 * ax.im + yy0 * ay.im + xy1 * bx.im + yy1 * by.im - syz * bz.re};
-        const cpx<T> h0z = {zz0 * az.re + zz1 * bz.re + sxz * bx.im + syz * by.im,
-                            zz0 * az.im + zz1 * bz.im - sxz * bx.re - syz * by.re};
-        const cpx<T> h1x = {xx1 * ax.re + xy1 * ay.re + xx0 * bx.re + xy0 * by.re - sxz * az.im,
-                            xx1 * ax.im + xy1 * ay.im + xx0 * bx.im + xy0 * by.im + sxz * az.re};
-        const cpx<T> h1y = {xy1 * ax.re + yy1 * ay.re + xy0 * bx.re + yy0 * by.re - syz * az.im,
-                            xy1 * ax.im + yy1 * ay.im + xy0 * bx.im + yy0 * by.im + syz * az.re};
-        const cpx<T> h1z = {zz1 * az.re + zz0 * bz.re - sxz * ax.im - syz * ay.im,
-                            zz1 * az.im + zz0 * bz.im + sxz * ax.re + syz * ay.re};
-        // stored conjugated: the inverse transform runs as a forward one
-        *p[0] = conj(h0x);
-        *p[1] = conj(h1x);
-        *p[2] = conj(h0y);
-        *p[3] = conj(h1y);
-        *p[4] = conj(h0z);
-        *p[5] = conj(h1z);
+        two_plane_product<T>(lds + l2 * LP + pad16(e), L * LP, sy, kv[it]);
     }
     __syncthreads();
 #pragma unroll

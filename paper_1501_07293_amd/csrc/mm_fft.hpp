@@ -188,20 +188,18 @@ __device__ inline void dft_odd(cpx<T>* v)
     cpx<T> y0 = x0;
 #pragma unroll
     for (int n = 0; n < H; ++n) y0 = y0 + a[n];
-    cpx<T> y[R];
-    y[0] = y0;
+    // y_k and y_{R-k} share both sums
 #pragma unroll
-    for (int k = 1; k < R; ++k) {
-        cpx<T> acc = x0;
+    for (int k = 1; k <= H; ++k) {
+        cpx<T> c = x0, d = scale(b[0], (T)OddTab<R>::s(k));
 #pragma unroll
-        for (int n = 1; n <= H; ++n) {
-            const int j = (n * k) % R;
-            acc = acc + scale(a[n - 1], (T)OddTab<R>::c(j)) + scale(b[n - 1], (T)OddTab<R>::s(j));
-        }
-        y[k] = acc;
+        for (int n = 1; n <= H; ++n) c = c + scale(a[n - 1], (T)OddTab<R>::c((n * k) % R));
+#pragma unroll
+        for (int n = 2; n <= H; ++n) d = d + scale(b[n - 1], (T)OddTab<R>::s((n * k) % R));
+        v[k] = c + d;
+        v[R - k] = c - d;
     }
-#pragma unroll
-    for (int k = 0; k < R; ++k) v[k] = y[k];
+    v[0] = y0;
 }
 
 template <typename T>

@@ -115,6 +115,85 @@ struct KyzArgs {
 template <typename T>
 hipError_t launch_kspace_yz(const KyzArgs& a, int nt, hipStream_t s);
 
+// Passes of any 7-smooth length by register radices chosen at run time (mm_rline.hpp,
+// mm_rline.hip).  `tws`: the stage twiddles of the length (LinePlan); dynamic LDS of
+// rline_lds() bytes.
+struct RYArgs {              // contiguous lines, transformed in place
+    void* buf;
+    int nlines;
+    int64_t line_stride;
+    int nin, nout;           // inputs beyond nin are zero; first nout outputs stored
+    const void* tws;
+    int kx_major;            // as YLineArgs
+    int L;                   // lines per work-group
+};
+struct RXArgs {              // x pass, [nplanes][ny][nx] real rows <-> [nplanes][hx][srows] bins
+    const void* in;
+    void* out;
+    int nplanes;
+    int ny, nx;
+    int64_t srows;
+    const void* tws;
+    int lsh;                 // 1 << lsh complex lines (row pairs) per work-group
+};
+struct RKzArgs {             // z k-space pass, columns (kx, ky) = (c / Py, c % Py)
+    void* buf;
+    int64_t comp_stride;
+    int ncols;               // hx * Py; also the z stride
+    int nz, Py;
+    const void* tws;
+    const void* kern;        // octant [6][Pz/2+1][hx][Py/2+1]
+    int64_t k_cs, k_zs, k_xs;
+    int csh;                 // 1 << csh columns per work-group
+};
+struct RKyArgs {             // y k-space pass of a one-cell-thick grid, lines (component, kx)
+    void* buf;
+    int64_t comp_stride, line_stride;
+    int hx, ny;
+    const void* tws;
+    const void* kern;        // octant [4][1][hx][Py/2+1]: xx, xy, yy, zz
+    int64_t k_cs, k_xs;
+    int L;                   // x bins per work-group
+    unsigned dmul;           // divides by Py
+};
+struct RKy2Args {            // y k-space pass of a two-cell-thick grid (see Ky2Args)
+    void* buf;
+    int64_t comp_stride, plane_stride, line_stride;
+    int hx, ny;
+    const void* tws;
+    const void* kern;
+    int64_t k_cs, k_xs;
+    int L;                   // x bins per work-group
+    unsigned dmul;           // divides by Py
+};
+// Work-group shapes of these passes for one grid: lines (or columns) per work-group.
+// Zero where the pass has no such shape (the length's schedule, threads or LDS).
+struct RShape {
+    int lsh_f, lsh_i;        // x forward, x inverse (log2 of the lines), -1: none
+    int y, ky, ky2;          // lines of the y passes, x bins of the y k-space passes
+    int csh;                 // log2 of the columns of the z k-space pass, -1: none
+};
+bool make_line_plan(int P, LinePlan* s);
+// multiplier with which n / d = umulhi(n, mul) for n d < 2^32, d > 1
+constexpr unsigned div_mul(int d) { return d <= 1 ? 0u : (unsigned)(((unsigned long long)1 << 32) / (unsigned)d + 1); }
+// max_threads: of a work-group; min_groups: launches of fewer work-groups take fewer
+// lines each
+RShape rline_shapes(const LinePlan& x, const LinePlan& y, const LinePlan& z, int nx, int ny, int nz, size_t esz,
+                    int max_threads, int min_groups);
+size_t rline_lds_bytes(int lines, int P, size_t esz);
+size_t rxinv_lds_bytes(int lsh, int P, size_t esz);
+// stage twiddles of s (P - R[0] entries), computed in FP64, stored in T
+template <typename T>
+hipError_t launch_stage_twiddles(void* tws, const LinePlan& s, hipStream_t st);
+template <typename T>
+hipError_t launch_rxline(const RXArgs& a, const LinePlan& s, int inverse, hipStream_t st);
+template <typename T>
+hipError_t launch_ryline(const RYArgs& a, const LinePlan& s, int inverse, hipStream_t st);
+template <typename T>
+hipError_t launch_rkz(const RKzArgs& a, const LinePlan& s, hipStream_t st);
+template <typename T>
+hipError_t launch_rky(const RKyArgs& a, const LinePlan& s, hipStream_t st);
+
 // Compile-time specialised passes for power-of-two sizes (mm_fast.hip).  Each
 // launcher returns false (and launches nothing) when no specialisation fits.
 struct YLineArgs {           // contiguous lines, transformed in place
@@ -367,6 +446,9 @@ struct BatchDesc {
     double alpha;     // damping of this grid's material
     double gdt;       // gamma Ms dt / (1 + alpha^2) for the batch's current dt
     FftPlan fx, fy, fz;
+    LinePlan lx, ly, lz;  // the runtime-length register passes' schedules and shapes
+    RShape rs;
+    unsigned pymul;       // divides by Py
 };
 template <typename T>
 struct BatchPass {
@@ -379,6 +461,21 @@ struct BatchPass {
     const T* kern;
     const cpx<T>* tw;
 };
+constexpr int kBatchNT = 256;  // threads per work-group of a batch's passes
+// The grid whose tiles hold `tile`: prefix[lo] <= tile < prefix[lo + 1]; grids without
+// tiles are skipped.
+__device__ inline int find_sample(const int* prefix, int n, int tile)
+{
+    int lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (prefix[mid] <= tile)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return lo;
+}
 template <typename T>
 struct BatchLlg {
     const T* ms;
@@ -424,6 +521,12 @@ int fast_ky_lines(int P);
 // kx bins per work-group of the two-plane y k-space pass (0 if P has none)
 int fast_ky2_lines(int P);
 
+// The runtime-length register passes over all grids, which: 0 x forward, 1 y (inverse
+// flag), 2 z k-space, 3 x inverse, 4 y k-space, 5 two-plane y k-space; lds: the largest
+// dynamic LDS a grid needs.
+template <typename T>
+hipError_t launch_batch_rline(int which, const BatchPass<T>& p, int total_tiles, int inverse, size_t lds,
+                              hipStream_t s);
 // which: 0 x forward, 1 y (inverse flag), 2 k-space, 3 x inverse.
 template <typename T>
 hipError_t launch_batch_pass(int which, const BatchPass<T>& p, int total_tiles, int inverse, hipStream_t s);
