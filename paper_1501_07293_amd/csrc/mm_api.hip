@@ -529,7 +529,8 @@ hipError_t pass_y(const PassCtx& c, int inverse, hipStream_t st)
     YLineArgs ya{c.S, c.nplanes * p.hx, c.Sy, nin, nout, c.twy, (inverse && p.esz == 4) ? c.nplanes : 0};
     if (c.fast && launch_yline<T>(ya, p.Py, inverse, st)) return hipGetLastError();
     if (p.rs.y > 0) {
-        const RYArgs ra{c.S, ya.nlines, c.Sy, nin, nout, stage_tw(p, c.twy, p.Py), ya.kx_major, p.rs.y};
+        RYArgs ra{c.S, ya.nlines, c.Sy, nin, nout, stage_tw(p, c.twy, p.Py), ya.kx_major, p.rs.y};
+        if ((int64_t)c.nplanes * c.plane * 2 * (int64_t)p.esz >= kRLineBytes) ra.kx_major = 0;
         return launch_ryline<T>(ra, p.ly, inverse, st);
     }
     ColArgs cy{};

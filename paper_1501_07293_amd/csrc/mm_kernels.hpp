@@ -118,6 +118,8 @@ hipError_t launch_kspace_yz(const KyzArgs& a, int nt, hipStream_t s);
 // Passes of any 7-smooth length by register radices chosen at run time (mm_rline.hpp,
 // mm_rline.hip).  `tws`: the stage twiddles of the length (LinePlan); dynamic LDS of
 // rline_lds() bytes.
+// bytes a work-group of these passes can address from its base
+constexpr int64_t kRLineBytes = 0x7ffffff0;
 struct RYArgs {              // contiguous lines, transformed in place
     void* buf;
     int nlines;

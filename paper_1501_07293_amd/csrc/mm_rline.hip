@@ -165,6 +165,7 @@ RShape rline_shapes(const LinePlan& x, const LinePlan& y, const LinePlan& z, int
         if (l < 1 && 6 * y.TL <= max_threads) l = 1;
         while (l > 1 && (hx + l - 1) / l < min_groups) --l;
         r.ky2 = 6 * l <= cap ? l : cap / 6;
+        if (6 * (int64_t)hx * ny * 2 * (int64_t)esz >= kBufEnd) r.ky = r.ky2 = 0;
     }
     if (z.ns > 0) {
         const int64_t ncols = (int64_t)(x.P / 2 + 1) * y.P;
@@ -173,7 +174,8 @@ RShape rline_shapes(const LinePlan& x, const LinePlan& y, const LinePlan& z, int
             return (3 * z.TL << q) <= max_threads && rline_lds_bytes(3 << q, z.P, esz) <= kRLdsBudget;
         };
         while (c > 0 && (!fits(c) || ((3 * z.TL << c) > 256 && c > 4))) --c;
-        if (fits(c)) r.csh = c;
+        // the pass addresses the whole spectrum from one descriptor
+        if (fits(c) && 3 * nz * ncols * 2 * (int64_t)esz < kBufEnd) r.csh = c;
     }
     return r;
 }

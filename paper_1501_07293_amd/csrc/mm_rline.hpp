@@ -154,107 +154,165 @@ struct LineRegs {
     X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10)                 \
     X(12) X(14) X(15) X(16)
 
-// Forward FFT of one line by its TL threads (u = this thread's number in the line;
-// act = false: a thread that only joins the barriers).  get(e) delivers input e of the
-// first stage (it is called by every thread, with e below P, and must not branch),
-// put(e, value) takes output e.  SYNC: the inputs come from LDS that the stages
-// overwrite, so every thread's reads end before the first write.
-// tws: the line's stage twiddles (LinePlan::toff).
-//
-// The switches hold nothing but loads and arithmetic on one array v shared by their
-// cases: with a divergent branch or a barrier inside, the compiler keeps every case's
-// values alive side by side (256 registers and hundreds spilled).
-template <typename T, int RM, bool SYNC, class Get, class Put>
-__device__ inline void rline_fft(const LineRegs& s, const cpx<T>* __restrict__ tws, cpx<T>* ln, int u, bool act,
-                                 Get get, Put put)
+// Global memory through buffer descriptors: an offset past the end reads zero and writes
+// nothing, which is what the padding half of a line and the rows and columns beyond a
+// ragged edge need, without a branch (the compiler turns a conditional load into one, and
+// a branch inside a radix case costs the registers of every other case).  The base has to
+// be the same for the whole work-group, offsets stay below 2 GiB (kBufEnd); the launchers
+// see to both.
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+constexpr unsigned kBufEnd = (unsigned)kRLineBytes, kBufNone = 0x80000000u;
+constexpr int kBufRaw = 0x00020000;  // descriptor word 3: raw 32-bit data, no swizzle
+using Buf = __amdgpu_buffer_rsrc_t;
+__device__ inline Buf buf_of(const void* p)
 {
-    const int ns = s.ns;
-    cpx<T> v[RM];
-    {
-        const int m = s.st[0].m, R = s.st[0].R;
-        const bool on = act && u < m;
-        const int i = on ? u : 0;
-        switch (R) {
-#define X(RR)                                                                   \
-    case RR:                                                                    \
-        if constexpr (RR <= RM) {                                               \
-            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = get(i + r * m); \
-            Dft<T, RR>::run(v);                                                 \
-        }                                                                       \
-        break;
-            MM_RADIX_CASES(X)
-#undef X
-        default: break;
-        }
-        if (SYNC) __syncthreads();
-        if (ns == 1) {
-            if (on) {
-#pragma unroll
-                for (int r = 0; r < RM; ++r)
-                    if (r < R) put(r, v[r]);
-            }
-            return;
-        }
-        if (on) {
-            cpx<T>* o = ln + u * R;
-#pragma unroll
-            for (int r = 0; r < RM; ++r)
-                if (r < R) o[r] = v[r];
-        }
-        __syncthreads();
-    }
-    for (int q = 1; q < ns; ++q) {
-        const LineStage c = s.stage(q);
-        const int m = c.m, p = c.p;
-        const bool on = act && u < m;
-        const int i = on ? u : 0;
-        // the last stage has p = m, so its k is i and its outputs sit where its inputs were
-        const bool last = q == ns - 1;
-        const int k = last ? i : i - div_by(i, c.pmul) * p;
-        const cpx<T>* w = tws + c.toff;
-        switch (c.R) {
-#define X(RR)                                                                            \
-    case RR:                                                                             \
-        if constexpr (RR <= RM) {                                                        \
-            cpx<T> tw[RR];                                                               \
-            _Pragma("unroll") for (int r = 1; r < RR; ++r) tw[r] = w[(r - 1) * p + k];   \
-            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = ln[i + r * m];         \
-            _Pragma("unroll") for (int r = 1; r < RR; ++r) v[r] = cmul(v[r], tw[r]);     \
-            Dft<T, RR>::run(v);                                                          \
-        }                                                                                \
-        break;
-            MM_RADIX_CASES(X)
-#undef X
-        default: break;
-        }
-        if (last) {
-            if (on) {
-#pragma unroll
-                for (int r = 0; r < RM; ++r)
-                    if (r < c.R) put(i + r * m, v[r]);
-            }
-            return;
-        }
-        __syncthreads();
-        if (on) {
-            cpx<T>* o = ln + (i - k) * c.R + k;
-#pragma unroll
-            for (int r = 0; r < RM; ++r)
-                if (r < c.R) o[r * p] = v[r];
-        }
-        __syncthreads();
-    }
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)kBufEnd, kBufRaw);
+}
+template <typename V>
+__device__ inline V buf_ld(Buf b, unsigned off)
+{
+    if constexpr (sizeof(V) == 4)
+        return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
+    else if constexpr (sizeof(V) == 8)
+        return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, 0));
+    else
+        return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, 0));
+}
+template <typename V>
+__device__ inline void buf_st(Buf b, unsigned off, V v)
+{
+    if constexpr (sizeof(V) == 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, (int)off, 0, 0);
+    else if constexpr (sizeof(V) == 8)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, v), b, (int)off, 0, 0);
+    else
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v, v), b, (int)off, 0, 0);
 }
 
-// This thread's line (of `per` lines side by side) and its number in it.
+// An entry of a stage table: row (the same for every thread) plus a byte offset below
+// 4 GiB, so that the load takes its base from scalar registers.
+template <typename T>
+__device__ inline cpx<T> ld_tw(const cpx<T>* row, unsigned bytes)
+{
+    return *reinterpret_cast<const cpx<T>*>(reinterpret_cast<const char*>(row) + bytes);
+}
+
+// This thread's line (of `lines` side by side) and its number u in it.  A thread past the
+// last line takes the part of thread 0 of line 0 (real = false), so that it reads and
+// writes valid LDS: what it writes there is what that thread writes.
 struct LaneOf {
     int l, u;
+    bool real;
 };
-__device__ inline LaneOf rline_lane(const LineRegs& s)
+__device__ inline LaneOf rline_lane(const LineRegs& s, int lines)
 {
     const int t = (int)threadIdx.x;
     const int l = s.TL == 1 ? t : div_by(t, s.tmul);
-    return LaneOf{l, t - l * s.TL};
+    const bool real = l < lines;
+    return LaneOf{real ? l : 0, real ? t - l * s.TL : 0, real};
+}
+
+// Forward FFT of one line by its TL threads; u and real as LaneOf.  get(e) delivers input
+// e of the first stage; put(e, value) takes output e.  Both are called by every thread and
+// must not branch.  PUT_LDS: put writes to the line's own LDS entry e; otherwise to global
+// memory, and threads without a butterfly pass an e of kPastEnd or more, which has to
+// store nothing.  SYNC: the inputs come from LDS that the stages overwrite, so every
+// thread's reads end before the first write.  tws: the line's stage twiddles.
+//
+// A stage with fewer butterflies than the line has threads gives the others butterfly 0
+// again.  So a radix case is straight-line code that ends in its own stores: with a
+// divergent branch in it, or with its values handed to code behind the switch, the
+// compiler keeps the values of all cases side by side (up to 256 registers, spilled).
+constexpr int kPastEnd = 0x40000000;
+
+template <typename T, int RM, bool SYNC, bool PUT_LDS, class Get, class Put>
+__device__ inline void rline_fft(const LineRegs& s, const cpx<T>* __restrict__ tws, cpx<T>* ln, int u, bool real,
+                                 Get get, Put put)
+{
+    const int ns = s.ns;
+    {
+        const int m = s.st[0].m;
+        const int i = u < m ? u : 0;
+        const int io = PUT_LDS || (real && u < m) ? i : kPastEnd;
+        switch (s.st[0].R) {
+#define X(RR)                                                                         \
+    case RR:                                                                          \
+        if constexpr (RR <= RM) {                                                     \
+            cpx<T> v[RR];                                                             \
+            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = get(i + r * m);     \
+            Dft<T, RR>::run(v);                                                       \
+            if (SYNC) __syncthreads();                                                \
+            if (ns == 1) {                                                            \
+                _Pragma("unroll") for (int r = 0; r < RR; ++r) put(io + r, v[r]);     \
+            } else {                                                                  \
+                cpx<T>* o = ln + i * RR;                                              \
+                _Pragma("unroll") for (int r = 0; r < RR; ++r) o[r] = v[r];           \
+            }                                                                         \
+        }                                                                             \
+        break;
+            MM_RADIX_CASES(X)
+#undef X
+        default: break;
+        }
+        if (ns == 1) return;
+        __syncthreads();
+    }
+    for (int q = 1; q < ns - 1; ++q) {
+        const LineStage c = s.stage(q);
+        const int m = c.m, p = c.p;
+        const int i = u < m ? u : 0;
+        const int k = i - div_by(i, c.pmul) * p;
+        const cpx<T>* w = tws + c.toff;
+        const unsigned kb = (unsigned)k * (unsigned)sizeof(cpx<T>);
+        switch (c.R) {
+#define X(RR)                                                                                 \
+    case RR:                                                                                  \
+        if constexpr (RR <= RM) {                                                             \
+            cpx<T> v[RR], tw[RR];                                                             \
+            _Pragma("unroll") for (int r = 1; r < RR; ++r) tw[r] = ld_tw(w + (r - 1) * p, kb); \
+            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = ln[i + r * m];              \
+            _Pragma("unroll") for (int r = 1; r < RR; ++r) v[r] = cmul(v[r], tw[r]);          \
+            Dft<T, RR>::run(v);                                                               \
+            __syncthreads();                                                                  \
+            cpx<T>* o = ln + (i - k) * RR + k;                                                \
+            _Pragma("unroll") for (int r = 0; r < RR; ++r) o[r * p] = v[r];                   \
+        }                                                                                     \
+        break;
+            MM_RADIX_CASES(X)
+#undef X
+        default: break;
+        }
+        __syncthreads();
+    }
+    {
+        // last stage: p = m, so k is i and the outputs sit where the inputs were
+        const LineStage c = s.stage(ns - 1);
+        const int m = c.m;
+        const int i = u < m ? u : 0;
+        const int io = PUT_LDS || (real && u < m) ? i : kPastEnd;
+        const cpx<T>* w = tws + c.toff;
+        const unsigned kb = (unsigned)i * (unsigned)sizeof(cpx<T>);
+        // in place in LDS, a thread that repeats butterfly 0 must have read it before
+        // the one that owns it writes
+        switch (c.R) {
+#define X(RR)                                                                                 \
+    case RR:                                                                                  \
+        if constexpr (RR <= RM) {                                                             \
+            cpx<T> v[RR], tw[RR];                                                             \
+            _Pragma("unroll") for (int r = 1; r < RR; ++r) tw[r] = ld_tw(w + (r - 1) * m, kb); \
+            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = ln[i + r * m];              \
+            _Pragma("unroll") for (int r = 1; r < RR; ++r) v[r] = cmul(v[r], tw[r]);          \
+            Dft<T, RR>::run(v);                                                               \
+            if (PUT_LDS) __syncthreads();                                                     \
+            _Pragma("unroll") for (int r = 0; r < RR; ++r) put(io + r * m, v[r]);             \
+        }                                                                                     \
+        break;
+            MM_RADIX_CASES(X)
+#undef X
+        default: break;
+        }
+    }
 }
 
 // ------------------------------------------------------------------ y lines
@@ -262,22 +320,24 @@ template <typename T, int RM, bool INV>
 __device__ inline void body_ryline(const RYArgs& a, const LinePlan& pl, int tile, cpx<T>* lds)
 {
     const LineRegs s(pl);
-    const LaneOf w = rline_lane(s);
+    const LaneOf w = rline_lane(s, a.L);
     const int line = tile * a.L + w.l;
-    const bool ok = w.l < a.L && line < a.nlines;
-    int mline = ok ? line : 0;
-    if (a.kx_major) mline = (mline % a.kx_major) * (a.nlines / a.kx_major) + mline / a.kx_major;
-    cpx<T>* g = (cpx<T>*)a.buf + (int64_t)mline * a.line_stride;
-    const int nin = a.nin, nout = a.nout;
-    rline_fft<T, RM, false>(
-        s, (const cpx<T>*)a.tws, lds + (ok ? w.l : 0) * rline_len(s.P), w.u, ok,
+    const bool ok = line < a.nlines;
+    // the line's place: in memory order the work-group's lines follow one another, bin by
+    // bin (kx_major) they lie anywhere in the buffer
+    constexpr unsigned CS = sizeof(cpx<T>);
+    const Buf g = buf_of((const cpx<T>*)a.buf + (a.kx_major ? 0 : (int64_t)tile * a.L * a.line_stride));
+    int rel = w.l;
+    if (a.kx_major) rel = (line % a.kx_major) * (a.nlines / a.kx_major) + line / a.kx_major;
+    const unsigned at = (unsigned)rel * (unsigned)a.line_stride * CS;
+    const int nin = ok ? a.nin : 0, nout = ok ? a.nout : 0;
+    rline_fft<T, RM, false, false>(
+        s, (const cpx<T>*)a.tws, lds + w.l * rline_len(s.P), w.u, w.real,
         [&](int e) {
-            const cpx<T> x = g[e < nin ? e : 0];
-            return e < nin ? (INV ? conj(x) : x) : cpx<T>{(T)0, (T)0};
+            const cpx<T> x = buf_ld<cpx<T>>(g, e < nin ? at + (unsigned)e * CS : kBufNone);
+            return INV ? conj(x) : x;
         },
-        [&](int e, cpx<T> v) {
-            if (e < nout) g[e] = INV ? conj(v) : v;
-        });
+        [&](int e, cpx<T> v) { buf_st(g, e < nout ? at + (unsigned)e * CS : kBufNone, INV ? conj(v) : v); });
 }
 
 // ------------------------------------------------------------------ x forward
@@ -291,20 +351,20 @@ __device__ inline void body_rxfwd(const RXArgs& a, const LinePlan& pl, int tile,
     const int L = 1 << a.lsh, rows = 2 * L;
     const int tpp = (a.ny + rows - 1) / rows;
     const int plane = tile / tpp, yb = (tile - plane * tpp) * rows;
-    const LaneOf w = rline_lane(s);
+    const LaneOf w = rline_lane(s, L);
     const int y0 = yb + 2 * w.l;
-    const bool act = w.l < L;
-    const bool ok0 = act && y0 < a.ny, ok1 = act && y0 + 1 < a.ny;
-    const T* in = (const T*)a.in + ((int64_t)plane * a.ny + (ok0 ? y0 : 0)) * a.nx;
-    const T* in1 = in + (ok1 ? a.nx : 0);
-    cpx<T>* ln = lds + (act ? w.l : 0) * LP;
+    const bool ok0 = y0 < a.ny, ok1 = y0 + 1 < a.ny;
+    cpx<T>* ln = lds + w.l * LP;
     const int nx = a.nx;
-    rline_fft<T, RM, false>(
-        s, (const cpx<T>*)a.tws, ln, w.u, act,
+    const Buf g = buf_of((const T*)a.in + ((int64_t)plane * a.ny + yb) * nx);
+    const unsigned at0 = (unsigned)(2 * w.l * nx) * (unsigned)sizeof(T);
+    const int n0 = ok0 ? nx : 0, n1 = ok1 ? nx : 0;
+    rline_fft<T, RM, false, true>(
+        s, (const cpx<T>*)a.tws, ln, w.u, w.real,
         [&](int e) {
-            const int i = e < nx ? e : 0;
-            const T re = in[i], im = in1[i];
-            return cpx<T>{e < nx && ok0 ? re : (T)0, e < nx && ok1 ? im : (T)0};
+            const T re = buf_ld<T>(g, e < n0 ? at0 + (unsigned)e * (unsigned)sizeof(T) : kBufNone);
+            const T im = buf_ld<T>(g, e < n1 ? at0 + (unsigned)(nx + e) * (unsigned)sizeof(T) : kBufNone);
+            return cpx<T>{re, im};
         },
         [&](int e, cpx<T> v) { ln[e] = v; });
     __syncthreads();
@@ -342,8 +402,7 @@ __device__ inline void body_rxinv(const RXArgs& a, const LinePlan& pl, int tile,
     const int L = 1 << a.lsh, rows = 2 * L;
     const int tpp = (a.ny + rows - 1) / rows;
     const int plane = tile / tpp, yb = (tile - plane * tpp) * rows;
-    const LaneOf w = rline_lane(s);
-    const bool act = w.l < L;
+    const LaneOf w = rline_lane(s, L);
     const cpx<T>* src = (const cpx<T>*)a.in + (int64_t)plane * hx * a.srows;
     const int NT = blockDim.x, nel = hx << a.lsh;
     const bool paired = (a.srows & 1) == 0 && (reinterpret_cast<uintptr_t>(a.in) % sizeof(cpx2<T>)) == 0;
@@ -373,13 +432,14 @@ __device__ inline void body_rxinv(const RXArgs& a, const LinePlan& pl, int tile,
         }
     }
     __syncthreads();
-    const cpx<T>* ra = lds + (act ? 2 * w.l : 0) * hx;
+    const cpx<T>* ra = lds + 2 * w.l * hx;
     const cpx<T>* rb = ra + hx;
     const int y0 = yb + 2 * w.l, nx = a.nx;
-    const bool ok0 = y0 < a.ny, ok1 = y0 + 1 < a.ny;
-    T* out = (T*)a.out + ((int64_t)plane * a.ny + y0) * nx;
-    rline_fft<T, RM, true>(
-        s, (const cpx<T>*)a.tws, lds + (act ? w.l : 0) * LP, w.u, act,
+    const int n0 = y0 < a.ny ? nx : 0, n1 = y0 + 1 < a.ny ? nx : 0;
+    const Buf o = buf_of((const T*)a.out + ((int64_t)plane * a.ny + yb) * nx);
+    const unsigned at0 = (unsigned)(2 * w.l * nx) * (unsigned)sizeof(T);
+    rline_fft<T, RM, true, false>(
+        s, (const cpx<T>*)a.tws, lds + w.l * LP, w.u, w.real,
         [&](int k) {
             const bool lo = k < hx;
             cpx<T> A = ra[lo ? k : P - k], B = rb[lo ? k : P - k];
@@ -388,10 +448,8 @@ __device__ inline void body_rxinv(const RXArgs& a, const LinePlan& pl, int tile,
             return lo ? cpx<T>{A.re - B.im, -A.im - B.re} : cpx<T>{A.re + B.im, A.im - B.re};
         },
         [&](int e, cpx<T> v) {  // result a + i b = conj(v)
-            if (e < nx) {
-                if (ok0) out[e] = v.re;
-                if (ok1) out[nx + e] = -v.im;
-            }
+            buf_st(o, e < n0 ? at0 + (unsigned)e * (unsigned)sizeof(T) : kBufNone, v.re);
+            buf_st(o, e < n1 ? at0 + (unsigned)(nx + e) * (unsigned)sizeof(T) : kBufNone, -v.im);
         });
 }
 
@@ -421,12 +479,15 @@ __device__ inline void body_rkz(const RKzArgs& a, const LinePlan& pl, int tile, 
     const int P = s.P, LP = rline_len(P), C = 1 << a.csh;
     const int t = (int)threadIdx.x, NT = blockDim.x;
     const int l = t & (C - 1), v = t >> a.csh;  // v = component * TL + u
-    const int comp = s.TL == 1 ? v : div_by(v, s.tmul), u = v - comp * s.TL;
+    int comp = s.TL == 1 ? v : div_by(v, s.tmul), u = v - comp * s.TL;
+    const bool real = comp < 3;  // the others: component 0, thread 0 of their column
+    if (!real) comp = u = 0;
     const int col = tile * C + l;
-    const bool act = comp < 3, ok = act && col < a.ncols;
-    const int64_t zs = a.ncols;
-    cpx<T>* g = (cpx<T>*)a.buf + (ok ? comp * a.comp_stride + col : 0);
-    cpx<T>* ln = lds + ((act ? comp : 0) * C + l) * LP;
+    const bool ok = col < a.ncols;
+    constexpr unsigned CS = sizeof(cpx<T>);
+    const Buf g = buf_of(a.buf);
+    const unsigned zs = (unsigned)a.ncols * CS, at = ((unsigned)comp * (unsigned)a.comp_stride + (unsigned)col) * CS;
+    cpx<T>* ln = lds + (comp * C + l) * LP;
     const T* K = (const T*)a.kern;
     T kv[kRzProduct][6];
 #pragma unroll
@@ -446,14 +507,10 @@ __device__ inline void body_rkz(const RKzArgs& a, const LinePlan& pl, int tile, 
             for (int c = 0; c < 6; ++c) kv[it][c] = Kp[c * a.k_cs];
         }
     }
-    const int nz = a.nz;
-    rline_fft<T, RM, false>(
-        s, (const cpx<T>*)a.tws, ln, u, act,
-        [&](int e) {
-            const bool in = ok && e < nz;
-            const cpx<T> x = g[in ? e * zs : 0];
-            return in ? x : cpx<T>{(T)0, (T)0};
-        },
+    const int nz = ok ? a.nz : 0;
+    rline_fft<T, RM, false, true>(
+        s, (const cpx<T>*)a.tws, ln, u, real,
+        [&](int e) { return buf_ld<cpx<T>>(g, e < nz ? at + (unsigned)e * zs : kBufNone); },
         [&](int e, cpx<T> x) { ln[e] = x; });
     __syncthreads();
 #pragma unroll
@@ -470,11 +527,9 @@ __device__ inline void body_rkz(const RKzArgs& a, const LinePlan& pl, int tile, 
         }
     }
     __syncthreads();
-    rline_fft<T, RM, true>(
-        s, (const cpx<T>*)a.tws, ln, u, act, [&](int e) { return ln[e]; },
-        [&](int e, cpx<T> x) {
-            if (ok && e < nz) g[e * zs] = conj(x);
-        });
+    rline_fft<T, RM, true, false>(
+        s, (const cpx<T>*)a.tws, ln, u, real, [&](int e) { return ln[e]; },
+        [&](int e, cpx<T> x) { buf_st(g, e < nz ? at + (unsigned)e * zs : kBufNone, conj(x)); });
 }
 
 // Along y on one-cell-thick grids: L x bins, three component lines each; spectra xx,
@@ -485,11 +540,13 @@ __device__ inline void body_rky(const RKyArgs& a, const LinePlan& pl, int tile, 
     const LineRegs s(pl);
     const int P = s.P, LP = rline_len(P), L = a.L;
     const int t = (int)threadIdx.x, NT = blockDim.x;
-    const LaneOf w = rline_lane(s);
+    const LaneOf w = rline_lane(s, 3 * L);
     const int comp = w.l / L, l = w.l - comp * L, kx = tile * L + l;
-    const bool act = comp < 3, ok = act && kx < a.hx;
-    cpx<T>* g = (cpx<T>*)a.buf + (ok ? comp * a.comp_stride + (int64_t)kx * a.line_stride : 0);
-    cpx<T>* ln = lds + (act ? w.l : 0) * LP;
+    const bool ok = kx < a.hx;
+    constexpr unsigned CS = sizeof(cpx<T>);
+    const Buf g = buf_of(a.buf);
+    const unsigned at = ((unsigned)comp * (unsigned)a.comp_stride + (unsigned)kx * (unsigned)a.line_stride) * CS;
+    cpx<T>* ln = lds + w.l * LP;
     const T* K = (const T*)a.kern;
     T kv[kRzProduct][4];
 #pragma unroll
@@ -504,14 +561,10 @@ __device__ inline void body_rky(const RKyArgs& a, const LinePlan& pl, int tile, 
             for (int c = 0; c < 4; ++c) kv[it][c] = Kp[c * a.k_cs];
         }
     }
-    const int ny = a.ny;
-    rline_fft<T, RM, false>(
-        s, (const cpx<T>*)a.tws, ln, w.u, act,
-        [&](int e) {
-            const bool in = ok && e < ny;
-            const cpx<T> x = g[in ? e : 0];
-            return in ? x : cpx<T>{(T)0, (T)0};
-        },
+    const int ny = ok ? a.ny : 0;
+    rline_fft<T, RM, false, true>(
+        s, (const cpx<T>*)a.tws, ln, w.u, w.real,
+        [&](int e) { return buf_ld<cpx<T>>(g, e < ny ? at + (unsigned)e * CS : kBufNone); },
         [&](int e, cpx<T> x) { ln[e] = x; });
     __syncthreads();
 #pragma unroll
@@ -530,11 +583,9 @@ __device__ inline void body_rky(const RKyArgs& a, const LinePlan& pl, int tile, 
         }
     }
     __syncthreads();
-    rline_fft<T, RM, true>(
-        s, (const cpx<T>*)a.tws, ln, w.u, act, [&](int e) { return ln[e]; },
-        [&](int e, cpx<T> x) {
-            if (ok && e < ny) g[e] = conj(x);
-        });
+    rline_fft<T, RM, true, false>(
+        s, (const cpx<T>*)a.tws, ln, w.u, w.real, [&](int e) { return ln[e]; },
+        [&](int e, cpx<T> x) { buf_st(g, e < ny ? at + (unsigned)e * CS : kBufNone, conj(x)); });
 }
 
 // Along y on grids two cells thick, the z coupling taken directly (Ky2Args): L x bins,
@@ -548,11 +599,14 @@ __device__ inline void body_rky2(const RKy2Args& a, const LinePlan& pl, int tile
     const LineRegs s(pl);
     const int P = s.P, LP = rline_len(P), L = a.L;
     const int t = (int)threadIdx.x, NT = blockDim.x;
-    const LaneOf w = rline_lane(s);
+    const LaneOf w = rline_lane(s, 6 * L);
     const int cz = w.l / L, l = w.l - cz * L, kx = tile * L + l;
-    const bool act = cz < 6, ok = act && kx < a.hx;
-    cpx<T>* g = (cpx<T>*)a.buf + (ok ? (cz >> 1) * a.comp_stride + (cz & 1) * a.plane_stride + (int64_t)kx * a.line_stride : 0);
-    cpx<T>* ln = lds + (act ? w.l : 0) * LP;
+    const bool ok = kx < a.hx;
+    constexpr unsigned CS = sizeof(cpx<T>);
+    const Buf g = buf_of(a.buf);
+    const unsigned at = ((unsigned)(cz >> 1) * (unsigned)a.comp_stride + (unsigned)(cz & 1) * (unsigned)a.plane_stride +
+                         (unsigned)kx * (unsigned)a.line_stride) * CS;
+    cpx<T>* ln = lds + w.l * LP;
     const T* K = (const T*)a.kern;
     T kv[kRy2Product][kTwoPlaneTablePlanes];
 #pragma unroll
@@ -564,14 +618,10 @@ __device__ inline void body_rky2(const RKy2Args& a, const LinePlan& pl, int tile
 #pragma unroll
         for (int c = 0; c < kTwoPlaneTablePlanes; ++c) kv[it][c] = Kp[c * a.k_cs];
     }
-    const int ny = a.ny;
-    rline_fft<T, RM, false>(
-        s, (const cpx<T>*)a.tws, ln, w.u, act,
-        [&](int e) {
-            const bool in = ok && e < ny;
-            const cpx<T> x = g[in ? e : 0];
-            return in ? x : cpx<T>{(T)0, (T)0};
-        },
+    const int ny = ok ? a.ny : 0;
+    rline_fft<T, RM, false, true>(
+        s, (const cpx<T>*)a.tws, ln, w.u, w.real,
+        [&](int e) { return buf_ld<cpx<T>>(g, e < ny ? at + (unsigned)e * CS : kBufNone); },
         [&](int e, cpx<T> x) { ln[e] = x; });
     __syncthreads();
 #pragma unroll
@@ -581,11 +631,9 @@ __device__ inline void body_rky2(const RKy2Args& a, const LinePlan& pl, int tile
         if (l2 < L && tile * L + l2 < a.hx) two_plane_product<T>(lds + l2 * LP + e, L * LP, 2 * e > P ? (T)-1 : (T)1, kv[it]);
     }
     __syncthreads();
-    rline_fft<T, RM, true>(
-        s, (const cpx<T>*)a.tws, ln, w.u, act, [&](int e) { return ln[e]; },
-        [&](int e, cpx<T> x) {
-            if (ok && e < ny) g[e] = conj(x);
-        });
+    rline_fft<T, RM, true, false>(
+        s, (const cpx<T>*)a.tws, ln, w.u, w.real, [&](int e) { return ln[e]; },
+        [&](int e, cpx<T> x) { buf_st(g, e < ny ? at + (unsigned)e * CS : kBufNone, conj(x)); });
 }
 
 }  // namespace mm
