@@ -1611,13 +1611,16 @@ mm_status backward_impl(mm_sim* s, int64_t nsteps, double dt, int64_t ck, const 
 }
 
 // ---------------------------------------------------------------- batched
-constexpr int kBatchLlgKind = 6;
+constexpr int kBatchLlgKind = 6, kBatchCellsKind = 7, kBatchRKind = 10, kBatchRInvKind = 15;
 struct BatchClassHost {
     int kind;  // 0 x passes, 1 y passes, 2 z k-space, 3 y k-space, 5 two-plane y k-space,
-               // kBatchLlgKind the LLG stage (P = planes per thread)
+               // kBatchLlgKind the LLG stage (P = planes per thread), kBatchCellsKind every
+               // grid's cells, kBatchRKind + pass the runtime-length register passes and
+               // kBatchRInvKind their x inverse (P = the largest radix served)
     int P;
     std::vector<int> members, prefix;
     size_t off;  // element offset of members, then prefix, in the device int array
+    size_t lds = 0;  // dynamic LDS of a work-group (register passes)
 };
 
 bool fast_supported(int kind, int P, size_t esz)
@@ -1639,13 +1642,8 @@ struct BatchLayout {
     size_t o_classes = 0;
     int64_t class_ints = 0;
     std::vector<BatchDesc> desc;
-    // runtime-length passes: x forward, y, k-space (along z), x inverse, and in the
-    // register form (rline) k-space along y and the two-plane k-space; lds: the dynamic
-    // LDS of a work-group
-    static constexpr int kPasses = 6;
-    std::vector<int> prefix[kPasses];
-    size_t lds[kPasses] = {0, 0, 0, 0, 0, 0};
-    bool rline = false;
+    std::vector<int> prefix[4];   // LDS-staged passes: x forward, y, k-space, x inverse
+    bool rline = false;           // the register passes in their place, as classes
     int64_t vec_elems = 0, S_elems = 0, kern_elems = 0, tw_elems = 0, cells = 0;
     size_t scratch = 0;
     size_t o_desc, o_prefix, o_mn, o_ma, o_mb, o_acc, o_hd, o_S, o_kern, o_tw, o_flags, o_scratch, total;
@@ -1721,6 +1719,46 @@ bool merge_small_classes(int32_t n, BatchLayout* L)
     return moved;
 }
 
+// The register passes of every grid as classes: grids in the order of their padded
+// length, so that work-groups that run side by side run the same radices.
+template <class ClassOf, class AddTo>
+void batch_rline_classes(int32_t n, BatchLayout* L, ClassOf class_of, AddTo add_to)
+{
+    std::vector<int> order(n);
+    for (int s = 0; s < n; ++s) order[s] = s;
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    auto rmax = [](const LinePlan& l) {
+        int r = 0;
+        for (int q = 0; q < l.ns; ++q) r = std::max(r, l.R[q]);
+        return r <= 10 ? 10 : 16;
+    };
+    auto pass = [&](int kind, int s, const LinePlan& l, int64_t tiles, size_t lds) {
+        BatchClassHost& c = class_of(kind, rmax(l));
+        add_to(c, s, tiles);
+        c.lds = std::max(c.lds, lds);
+    };
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return L->plans[a].Px < L->plans[b].Px; });
+    for (int s : order) {
+        const Plan& p = L->plans[s];
+        const RShape& r = L->desc[s].rs;
+        pass(kBatchRKind + kRPassX, s, p.lx, 3 * p.nz * up(p.ny, 2 << r.lsh_f), rline_lds_bytes(1 << r.lsh_f, p.Px, p.esz));
+        pass(kBatchRInvKind, s, p.lx, 3 * p.nz * up(p.ny, 2 << r.lsh_i), rxinv_lds_bytes(r.lsh_i, p.Px, p.esz));
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return L->plans[a].Py < L->plans[b].Py; });
+    for (int s : order) {
+        const Plan& p = L->plans[s];
+        const RShape& r = L->desc[s].rs;
+        if (p.zd) {
+            pass(kBatchRKind + kRPassKy2, s, p.ly, up(p.hx, r.ky2), rline_lds_bytes(6 * r.ky2, p.Py, p.esz));
+        } else if (p.three_d) {
+            pass(kBatchRKind + kRPassY, s, p.ly, up(3 * (int64_t)p.nz * p.hx, r.y), rline_lds_bytes(r.y, p.Py, p.esz));
+            pass(kBatchRKind + kRPassKz, s, p.lz, up(p.hx * (int64_t)p.Py, 1 << r.csh), rline_lds_bytes(3 << r.csh, p.Pz, p.esz));
+        } else {
+            pass(kBatchRKind + kRPassKy, s, p.ly, up(p.hx, r.ky), rline_lds_bytes(3 * r.ky, p.Py, p.esz));
+        }
+    }
+}
+
 mm_status batch_layout_plans(int32_t n, const mm_grid* grids, const mm_options* opt, bool classes,
                              BatchLayout* L)
 {
@@ -1730,10 +1768,7 @@ mm_status batch_layout_plans(int32_t n, const mm_grid* grids, const mm_options* 
     L->class_ints = 0;
     L->plans.assign(n, Plan{});
     L->desc.resize(n);
-    for (int q = 0; q < BatchLayout::kPasses; ++q) {
-        L->prefix[q].assign(n + 1, 0);
-        L->lds[q] = 0;
-    }
+    for (int q = 0; q < 4; ++q) L->prefix[q].assign(n + 1, 0);
     for (int s = 0; s < n; ++s) {
         Plan& p = L->plans[s];
         mm_options og = o;
@@ -1785,32 +1820,13 @@ mm_status batch_layout_plans(int32_t n, const mm_grid* grids, const mm_options* 
         const RShape& r = d.rs;
         if (L->rline && (r.lsh_f < 0 || r.lsh_i < 0 || (p.zd ? r.ky2 <= 0 : (p.three_d ? r.y <= 0 || r.csh < 0 : r.ky <= 0))))
             L->rline = false;
-        int tiles[BatchLayout::kPasses] = {0};
-        auto up = [](int64_t a, int64_t b) { return (int)((a + b - 1) / b); };
-        auto pass = [&](int q, int t, size_t bytes) {
-            tiles[q] = t;
-            L->lds[q] = std::max(L->lds[q], bytes);
-        };
-        if (L->rline) {
-            const size_t e = p.esz;
-            pass(0, 3 * p.nz * up(p.ny, 2 << r.lsh_f), rline_lds_bytes(1 << r.lsh_f, p.Px, e));
-            pass(3, 3 * p.nz * up(p.ny, 2 << r.lsh_i), rxinv_lds_bytes(r.lsh_i, p.Px, e));
-            if (p.zd) {
-                pass(5, up(p.hx, r.ky2), rline_lds_bytes(6 * r.ky2, p.Py, e));
-            } else if (p.three_d) {
-                pass(1, up(3 * (int64_t)p.nz * p.hx, r.y), rline_lds_bytes(r.y, p.Py, e));
-                pass(2, up(p.hx * (int64_t)p.Py, 1 << r.csh), rline_lds_bytes(3 << r.csh, p.Pz, e));
-            } else {
-                pass(4, up(p.hx, r.ky), rline_lds_bytes(3 * r.ky, p.Py, e));
-            }
-        } else {
-            const int npairs = (3 * p.nz * p.ny + 1) / 2;
-            pass(0, up(npairs, p.x_lines), 0);
-            pass(3, up(npairs, p.x_lines), 0);
-            pass(1, p.three_d ? up(3 * (int64_t)p.nz * p.hx, d.y_lines) : 0, 0);
-            pass(2, p.three_d ? up(p.hx * (int64_t)p.Py, p.k_tw) : up(p.hx, p.k_tw), 0);
-        }
-        for (int q = 0; q < BatchLayout::kPasses; ++q) L->prefix[q][s + 1] = L->prefix[q][s] + tiles[q];
+        const int npairs = (3 * p.nz * p.ny + 1) / 2;
+        const int tiles[4] = {
+            (npairs + p.x_lines - 1) / p.x_lines,
+            p.three_d ? (3 * p.nz * p.hx + d.y_lines - 1) / d.y_lines : 0,
+            p.three_d ? (int)((p.hx * (int64_t)p.Py + p.k_tw - 1) / p.k_tw) : (p.hx + p.k_tw - 1) / p.k_tw,
+            (npairs + p.x_lines - 1) / p.x_lines};
+        for (int q = 0; q < 4; ++q) L->prefix[q][s + 1] = L->prefix[q][s] + tiles[q];
     }
     L->prec = o.prec;
     L->esz = o.prec == MM_F32 ? 4 : 8;
@@ -1859,19 +1875,22 @@ mm_status batch_layout_plans(int32_t n, const mm_grid* grids, const mm_options* 
         else
             L->classes.clear();
     }
-    // LLG classes (every layout): the grids grouped by planes per thread
+    auto class_of = [&](int kind, int P) -> BatchClassHost& {
+        for (auto& e : L->classes)
+            if (e.kind == kind && e.P == P) return e;
+        L->classes.push_back(BatchClassHost{kind, P, {}, {0}, 0});
+        return L->classes.back();
+    };
+    auto add_to = [&](BatchClassHost& c, int s, int64_t tiles) {
+        c.members.push_back(s);
+        c.prefix.push_back(c.prefix.back() + (int)tiles);
+    };
+    if (L->rline) batch_rline_classes(n, L, class_of, add_to);
+    // every layout: the LLG stage's grids grouped by planes per thread, and all cells
     for (int s = 0; s < n; ++s) {
         const Plan& p = L->plans[s];
-        const int kz = llg_z_for(p.nz);
-        BatchClassHost* c = nullptr;
-        for (auto& e : L->classes)
-            if (e.kind == kBatchLlgKind && e.P == kz) c = &e;
-        if (!c) {
-            L->classes.push_back(BatchClassHost{kBatchLlgKind, kz, {}, {0}, 0});
-            c = &L->classes.back();
-        }
-        c->members.push_back(s);
-        c->prefix.push_back(c->prefix.back() + (int)llg_blocks(p.nx, p.ny, p.nz));
+        add_to(class_of(kBatchLlgKind, llg_z_for(p.nz)), s, llg_blocks(p.nx, p.ny, p.nz));
+        add_to(class_of(kBatchCellsKind, 0), s, (p.N + kBatchNT - 1) / kBatchNT);
     }
     int64_t at = 0;
     for (auto& c : L->classes) {
@@ -1892,7 +1911,7 @@ mm_status batch_layout_offsets(int32_t n, BatchLayout* L)
     };
     const size_t vec = (size_t)L->vec_elems * L->esz;
     L->o_desc = take(n * sizeof(BatchDesc));
-    L->o_prefix = take(BatchLayout::kPasses * (size_t)(n + 1) * sizeof(int));
+    L->o_prefix = take(4 * (size_t)(n + 1) * sizeof(int));
     L->o_mn = take(vec);
     L->o_ma = take(vec);
     L->o_mb = take(vec);
@@ -1933,6 +1952,20 @@ struct mm_batch {
 
 namespace {
 
+// The batch's device arrays as a class launch takes them (members and prefix to be set).
+template <typename T>
+BatchClass<T> batch_class(mm_batch* b)
+{
+    const BatchLayout& L = b->L;
+    BatchClass<T> bc{};
+    bc.d = b->at<BatchDesc>(L.o_desc);
+    bc.S = b->at<cpx<T>>(L.o_S);
+    bc.kern = b->at<T>(L.o_kern);
+    bc.tw = b->at<cpx<T>>(L.o_tw);
+    bc.out = b->at<T>(L.o_hd);
+    return bc;
+}
+
 // One demag field evaluation of every grid: the passes from m (in) to the
 // field in the hd region, as size-class launches (power-of-two padding) or one
 // runtime-radix launch per pass.
@@ -1942,13 +1975,8 @@ mm_status batch_demag(mm_batch* b, const T* in, hipStream_t st)
     const BatchLayout& L = b->L;
     const int* pre = b->at<int>(L.o_prefix);
     const int n = b->n;
-    if (L.fast) {
-        BatchClass<T> bc{};
-        bc.d = b->at<BatchDesc>(L.o_desc);
-        bc.S = b->at<cpx<T>>(L.o_S);
-        bc.kern = b->at<T>(L.o_kern);
-        bc.tw = b->at<cpx<T>>(L.o_tw);
-        bc.out = b->at<T>(L.o_hd);
+    if (L.fast || L.rline) {
+        BatchClass<T> bc = batch_class<T>(b);
         bc.in = in;
         const int* cints = b->at<int>(L.o_classes);
         auto run_classes = [&](int kind, int launch_kind, int inverse) -> mm_status {
@@ -1957,6 +1985,10 @@ mm_status batch_demag(mm_batch* b, const T* in, hipStream_t st)
                 bc.members = cints + c.off;
                 bc.prefix = cints + c.off + c.members.size();
                 bc.nmem = (int)c.members.size();
+                if (kind >= kBatchRKind) {
+                    HIP_TRY(launch_batch_rline<T>(launch_kind, c.P, bc, c.prefix.back(), inverse, c.lds, st));
+                    continue;
+                }
                 if (!launch_batch_class<T>(launch_kind, c.P, bc, c.prefix.back(), inverse, st))
                     return fail(MM_ENOTSUP, "no specialised pass of length %d", c.P);
                 HIP_TRY(hipGetLastError());
@@ -1964,6 +1996,14 @@ mm_status batch_demag(mm_batch* b, const T* in, hipStream_t st)
             return MM_OK;
         };
         mm_status r;
+        if (L.rline) {
+            if ((r = run_classes(kBatchRKind + kRPassX, kRPassX, 0)) != MM_OK) return r;
+            if ((r = run_classes(kBatchRKind + kRPassY, kRPassY, 0)) != MM_OK) return r;
+            for (int k : {kRPassKz, kRPassKy, kRPassKy2})
+                if ((r = run_classes(kBatchRKind + k, k, 0)) != MM_OK) return r;
+            if ((r = run_classes(kBatchRKind + kRPassY, kRPassY, 1)) != MM_OK) return r;
+            return run_classes(kBatchRInvKind, kRPassX, 1);
+        }
         if ((r = run_classes(0, 0, 0)) != MM_OK) return r;  // x forward
         if ((r = run_classes(1, 1, 0)) != MM_OK) return r;  // y forward
         if ((r = run_classes(2, 2, 0)) != MM_OK) return r;  // z k-space
@@ -1980,20 +2020,6 @@ mm_status batch_demag(mm_batch* b, const T* in, hipStream_t st)
     p.tw = b->at<cpx<T>>(L.o_tw);
     p.out = b->at<T>(L.o_hd);
     p.in = in;
-    if (L.rline) {
-        auto pass = [&](int which, int q, int inverse) {
-            p.prefix = pre + q * (n + 1);
-            return launch_batch_rline<T>(which, p, L.prefix[q][n], inverse, L.lds[q], st);
-        };
-        HIP_TRY(pass(0, 0, 0));
-        HIP_TRY(pass(1, 1, 0));
-        HIP_TRY(pass(2, 2, 0));
-        HIP_TRY(pass(4, 4, 0));
-        HIP_TRY(pass(5, 5, 0));
-        HIP_TRY(pass(1, 1, 1));
-        HIP_TRY(pass(3, 3, 0));
-        return MM_OK;
-    }
     p.prefix = pre + 0 * (n + 1);
     HIP_TRY(launch_batch_pass<T>(0, p, L.prefix[0][n], 0, st));
     p.prefix = pre + 1 * (n + 1);
@@ -2118,8 +2144,15 @@ mm_status batch_set_m_impl(mm_batch* b, const void* m, int on_device)
                            on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
     unsigned int* bad = reinterpret_cast<unsigned int*>(b->at<char>(L.o_flags));
     HIP_TRY(hipMemsetAsync(bad, 0, sizeof(unsigned int), st));
-    for (int s = 0; s < b->n; ++s)
-        HIP_TRY(launch_normalize<T>(mn + L.desc[s].moff, L.plans[s].N, bad, st));
+    BatchClass<T> bc = batch_class<T>(b);
+    const int* cints = b->at<int>(L.o_classes);
+    for (const BatchClassHost& c : L.classes) {
+        if (c.kind != kBatchCellsKind) continue;
+        bc.members = cints + c.off;
+        bc.prefix = cints + c.off + c.members.size();
+        bc.nmem = (int)c.members.size();
+        HIP_TRY(launch_batch_normalize<T>(bc, c.prefix.back(), mn, bad, st));
+    }
     unsigned int nbad = 0;
     HIP_TRY(hipMemcpyAsync(&nbad, bad, sizeof nbad, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -2988,8 +3021,8 @@ static mm_status batch_build(int32_t n, const mm_grid* grids, const mm_material*
     e = hipMemcpyAsync(b->at<char>(BL.o_desc), BL.desc.data(), n * sizeof(BatchDesc),
                        hipMemcpyHostToDevice, hs);
     if (e != hipSuccess) return bail(fail(MM_EHIP, "descriptor upload: %s", hipGetErrorString(e)));
-    std::vector<int> pre(BatchLayout::kPasses * (size_t)(n + 1));
-    for (int q = 0; q < BatchLayout::kPasses; ++q)
+    std::vector<int> pre(4 * (size_t)(n + 1));
+    for (int q = 0; q < 4; ++q)
         for (int s = 0; s <= n; ++s) pre[q * (n + 1) + s] = BL.prefix[q][s];
     e = hipMemcpyAsync(b->at<char>(BL.o_prefix), pre.data(), pre.size() * sizeof(int),
                        hipMemcpyHostToDevice, hs);

@@ -166,6 +166,26 @@ template hipError_t launch_batch_llg<float>(int, const BatchClass<float>&, int, 
 template hipError_t launch_batch_llg<double>(int, const BatchClass<double>&, int, const BatchLlg<double>&,
                                              hipStream_t);
 
+template <typename T>
+__global__ __launch_bounds__(kBatchNT) void kb_normalize(BatchClass<T> c, T* m, unsigned int* bad)
+{
+    const int q = find_sample(c.prefix, c.nmem, blockIdx.x);
+    const BatchDesc& d = c.d[c.members[q]];
+    const int64_t N = (int64_t)d.nx * d.ny * d.nz;
+    const int64_t cell = (int64_t)(blockIdx.x - c.prefix[q]) * kBatchNT + threadIdx.x;
+    if (cell < N) normalize_cell(m + d.moff, N, cell, bad);
+}
+
+template <typename T>
+hipError_t launch_batch_normalize(const BatchClass<T>& c, int tiles, T* m, unsigned int* bad, hipStream_t s)
+{
+    if (tiles <= 0) return hipSuccess;
+    hipLaunchKernelGGL(kb_normalize<T>, dim3(tiles), dim3(kBatchNT), 0, s, c, m, bad);
+    return hipGetLastError();
+}
+template hipError_t launch_batch_normalize<float>(const BatchClass<float>&, int, float*, unsigned int*, hipStream_t);
+template hipError_t launch_batch_normalize<double>(const BatchClass<double>&, int, double*, unsigned int*, hipStream_t);
+
 // ---- size classes: the specialised bodies, one launch per padded length
 template <typename T, int P, int L>
 __global__ __launch_bounds__(L * (P / Sched<P>::R0)) void kbf_xfwd(BatchClass<T> c)

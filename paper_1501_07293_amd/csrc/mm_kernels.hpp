@@ -523,12 +523,16 @@ int fast_ky_lines(int P);
 // kx bins per work-group of the two-plane y k-space pass (0 if P has none)
 int fast_ky2_lines(int P);
 
-// The runtime-length register passes over all grids, which: 0 x forward, 1 y (inverse
-// flag), 2 z k-space, 3 x inverse, 4 y k-space, 5 two-plane y k-space; lds: the largest
-// dynamic LDS a grid needs.
+// The runtime-length register passes: one launch over the grids of class c, whose
+// radices are at most rmax (10 or 16); lds: the largest dynamic LDS a grid needs.
+enum { kRPassX = 0, kRPassY = 1, kRPassKz = 2, kRPassKy = 3, kRPassKy2 = 4, kRPasses = 5 };
 template <typename T>
-hipError_t launch_batch_rline(int which, const BatchPass<T>& p, int total_tiles, int inverse, size_t lds,
+hipError_t launch_batch_rline(int pass, int rmax, const BatchClass<T>& c, int tiles, int inverse, size_t lds,
                               hipStream_t s);
+// m <- m / |m| over the cells of every grid of class c (tiles of kBatchNT cells); counts
+// zero-norm or non-finite cells into *bad.
+template <typename T>
+hipError_t launch_batch_normalize(const BatchClass<T>& c, int tiles, T* m, unsigned int* bad, hipStream_t s);
 // which: 0 x forward, 1 y (inverse flag), 2 k-space, 3 x inverse.
 template <typename T>
 hipError_t launch_batch_pass(int which, const BatchPass<T>& p, int total_tiles, int inverse, hipStream_t s);
@@ -538,6 +542,20 @@ template <typename T>
 hipError_t launch_batch_llg(int kz, const BatchClass<T>& c, int tiles, const BatchLlg<T>& g, hipStream_t s);
 
 // m <- m / |m| per cell; counts zero-norm or non-finite cells into *bad.
+template <typename T>
+__device__ inline void normalize_cell(T* m, int64_t N, int64_t c, unsigned int* bad)
+{
+    const T x = m[c], y = m[N + c], z = m[2 * N + c];
+    const T n2 = x * x + y * y + z * z;
+    if (!(n2 > (T)0) || !isfinite(n2)) {
+        atomicAdd(bad, 1u);
+        return;
+    }
+    const T inv = (T)1 / sqrt(n2);
+    m[c] = x * inv;
+    m[N + c] = y * inv;
+    m[2 * N + c] = z * inv;
+}
 template <typename T>
 hipError_t launch_normalize(T* m, int64_t N, unsigned int* bad, hipStream_t s);
 

@@ -236,16 +236,7 @@ __global__ void k_normalize(T* m, int64_t N, unsigned int* bad)
 {
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (c >= N) return;
-    const T x = m[c], y = m[N + c], z = m[2 * N + c];
-    const T n2 = x * x + y * y + z * z;
-    if (!(n2 > (T)0) || !isfinite(n2)) {
-        atomicAdd(bad, 1u);
-        return;
-    }
-    const T inv = (T)1 / sqrt(n2);
-    m[c] = x * inv;
-    m[N + c] = y * inv;
-    m[2 * N + c] = z * inv;
+    normalize_cell(m, N, c, bad);
 }
 
 static int blocks_for(int64_t n) { return (int)((n + 255) / 256); }
