@@ -126,6 +126,7 @@ struct Plan {
     int64_t S_planes, S_rows;  // spectrum [3][S_planes][hx][S_rows]
     int per;                   // periodic axes: bit 0 x, bit 1 y, bit 2 z
     bool yz;                   // 3-D: the fused y-z pass replaces y forward, z k-space, y inverse
+    bool yz_small;             // and takes their place by itself on small planes (not MM_FUSED_YZ)
     bool wg1;                  // one work-group runs the whole demag evaluation (small grids)
     int images;                // images on each side beyond the nearest (periodic axes)
     bool zd;                   // two cells along z: the two-plane y k-space pass replaces y forward,
@@ -134,6 +135,7 @@ struct Plan {
                                // x forward) with a second spectrum buffer, two launches per RK4
                                // stage fewer
     int fs_lines;              // its row pairs per work-group
+    bool fs_rt;                // in its runtime-length form
     int64_t oct_elems;         // per component (two-plane schedule: per coefficient plane)
     int kplanes;               // blocks of oct_elems in the kernel region (ncomp, or 10)
     // workspace offsets
@@ -145,6 +147,32 @@ struct Plan {
 // passes (whose x transposes move 128-byte segments) are bandwidth-bound, not
 // latency-bound.
 constexpr int64_t kFusedStageMaxCells = (int64_t)1 << 20;
+// Its runtime-length form (x lengths without a size-specialised pass) holds fewer rows a
+// work-group and moves 16-byte segments of the spectrum, so it stops earlier.  Measured per
+// RK4 step with graph replay, separate passes -> fused: 30x30x1 FP32 60.2 -> 48.7 us,
+// 100x100x1 69.1 -> 59.1, 45x45x10 98.8 -> 85.4, 200x100x4 115.8 -> 113.0 (FP64 160.7 -> 145.0),
+// 250x120x4 (120000 cells, 500 points) 133.0 -> 132.5 (195.6 -> 176.1); beyond, 301x60x6 (625
+// points) 140.1 -> 140.1, 300x100x1 (600 points) 79.4 -> 82.9, 301x190x6 (343140 cells)
+// 245.3 -> 317.2.
+constexpr int64_t kFusedStageMaxCellsRt = (int64_t)1 << 17;
+constexpr int kFusedStageMaxPxRt = 512;
+
+// Where the fused y-z pass takes the place of y forward, z k-space and y inverse.  One
+// launch saves two of 4-5 us, but a bin's whole plane then runs on one CU, so the line
+// lies at the plane's size (3 Py Pz complex elements).  Measured per RK4 step with graph
+// replay, three passes -> fused: against the runtime-length passes 60x40x3 (1440 elements)
+// FP32 89.9 -> 78.8 us, FP64 96.6 -> 92.4; 200x40x3 (1440) 99.8 -> 88.2 and 112.7 -> 104.2;
+// 100x30x5 (1800) 97.6 -> 84.8 and 104.6 -> 97.5; but FP64 planes two cells thick lose
+// (50x50x2 88.9 -> 94.1).  Against the size-specialised passes 8x8x8 (768) 64.8 -> 46.9 and
+// 68.2 -> 56.2, 8x16x8 (1536) FP32 53.0 -> 48.9, but FP64 56.8 -> 60.6; 256x64x4 (3072) FP32
+// 87.0 -> 88.3, 16x16x16 (3072) FP64 67.7 -> 85.1.
+bool yz_is_small(const Plan& p, bool generic)
+{
+    const int64_t plane = 3LL * p.Py * p.Pz;
+    const bool special = !generic && fast_first_radix(p.Py) > 0 && (p.Pz & (p.Pz - 1)) == 0;
+    if (special) return plane <= (p.esz == 8 ? 1024 : 2048);
+    return plane <= 4096 && !(p.esz == 8 && p.Pz <= 4);
+}
 
 // Shapes of the runtime-length passes in a batch: 256 threads a work-group, which every
 // grid fills (the launch holds the tiles of all of them).
@@ -238,7 +266,12 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_pl
     if (!fits(nt)) return fail(MM_ENOTSUP, "padded sizes %d x %d x %d exceed the FFT work-group capacity",
                                p->Px, p->Py, p->Pz);
     p->nt = nt;
-    p->yz = p->three_d && (o->flags & MM_FUSED_YZ) && 3LL * p->Py * p->Pz <= (int64_t)kElemsPerThread * nt;
+    (void)make_line_plan(p->Px, &p->lx);
+    (void)make_line_plan(p->Py, &p->ly);
+    (void)make_line_plan(p->Pz, &p->lz);
+    p->rs = rline_shapes(p->lx, p->ly, p->lz, p->nx, p->ny, p->nz, p->esz, 512, 256);
+    p->yz = p->three_d && (o->flags & MM_FUSED_YZ) && 3LL * p->Py * p->Pz <= (int64_t)kElemsPerThread * nt &&
+            p->rs.yz > 0;
     p->wg1 = (o->flags & MM_ONE_WG) && !(o->flags & MM_NO_DEMAG) &&
              3LL * p->Px * p->Py * p->Pz <= (int64_t)kElemsPerThread * nt;
     if (p->wg1) p->yz = false;
@@ -262,10 +295,6 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_pl
     }
     if (!make_fft_plan(p->Px, &p->fx) || !make_fft_plan(p->Py, &p->fy) || !make_fft_plan(p->Pz, &p->fz))
         return fail(MM_EINVAL, "padded sizes must be 7-smooth");
-    (void)make_line_plan(p->Px, &p->lx);
-    (void)make_line_plan(p->Py, &p->ly);
-    (void)make_line_plan(p->Pz, &p->lz);
-    p->rs = rline_shapes(p->lx, p->ly, p->lz, p->nx, p->ny, p->nz, p->esz, 512, 256);
     const int cap = kElemsPerThread * nt, ldscap = cap + 64;
     p->x_lines = std::min(cap / p->Px, ldscap / (p->Px + 1));
     p->y_tw = std::max(1, std::min(64, cap / p->Py));
@@ -275,13 +304,19 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_pl
     p->zd = p->nz == 2 && p->Pz == 4 && !(p->per & 4) && !p->yz && !p->wg1 && p->ny <= p->Py &&
             ((!(o->flags & MM_GENERIC_FFT) && fast_ky2_lines(p->Py) > 0 && !(p->esz == 8 && p->Py > 1024)) ||
              (two_plane && batch_shapes(*p).ky2 > 0));
+    p->yz_small = p->three_d && !p->yz && !p->zd && !p->wg1 && p->rs.yz > 0 && yz_is_small(*p, (o->flags & MM_GENERIC_FFT) != 0);
     // open, small (latency-bound), with the specialised passes: the fused stage pass
     // (the y / z passes of one-cell-thick and thicker grids run between its launches)
     p->fs_lines = 0;
-    if (p->per == 0 && !p->yz && !p->wg1 && p->N <= kFusedStageMaxCells &&
-        !(o->flags & (MM_GENERIC_FFT | MM_SPLIT_STAGE | MM_NO_DEMAG)) && 2 * p->ny <= p->Py &&
-        (p->three_d || fast_ky_lines(p->Py) > 0))
-        p->fs_lines = fused_stage_lines(p->Px, p->nx, p->ny * p->nz, p->esz);
+    p->fs_rt = false;
+    if (p->per == 0 && !p->yz && !p->wg1 && !(o->flags & (MM_GENERIC_FFT | MM_SPLIT_STAGE | MM_NO_DEMAG))) {
+        if (p->N <= kFusedStageMaxCells) p->fs_lines = fused_stage_lines(p->Px, p->nx, p->ny * p->nz, p->esz);
+        if (p->fs_lines == 0 && p->N <= kFusedStageMaxCellsRt && p->Px <= kFusedStageMaxPxRt &&
+            3 * (int64_t)p->nz * p->hx * p->Py * 2 * (int64_t)p->esz < kRLineBytes) {
+            p->fs_lines = rfused_lines(p->lx, p->nx, p->ny * p->nz, p->esz);
+            p->fs_rt = p->fs_lines > 0;
+        }
+    }
     p->fs = p->fs_lines > 0;
     // spectrum [3][nz][hx][S_rows]: the y pass expands ny rows to Py in place on 3-D grids
     p->S_planes = p->nz;
@@ -634,28 +669,32 @@ hipError_t pass_x_inverse(const PassCtx& c, T* h, hipStream_t st)
 }
 
 template <typename T>
+hipError_t pass_fused_stage(const PassCtx& c, const FusedStageArgs<T>& f, hipStream_t st)
+{
+    const Plan& p = c.p;
+    const bool ok = p.fs_rt ? launch_rfused_stage<T>(f, stage_tw(p, c.twx, p.Px), p.lx, p.fs_lines, st)
+                            : launch_fused_stage<T>(f, p.Px, p.fs_lines, st);
+    return ok ? hipGetLastError() : hipErrorInvalidValue;  // the plan checked that the pass exists
+}
+
+template <typename T>
+hipError_t pass_fused_adjoint(const PassCtx& c, const FusedAdjArgs<T>& f, hipStream_t st)
+{
+    const Plan& p = c.p;
+    const bool ok = p.fs_rt ? launch_rfused_adjoint<T>(f, stage_tw(p, c.twx, p.Px), p.lx, p.fs_lines, st)
+                            : launch_fused_adjoint<T>(f, p.Px, p.fs_lines, st);
+    return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+template <typename T>
 hipError_t pass_kspace_yz(const PassCtx& c, hipStream_t st)
 {
     const Plan& p = c.p;
-    KyzArgs a{};
-    a.buf = c.S;
-    a.comp_stride = (int64_t)p.nz * c.plane;
-    a.zs = c.plane;
-    a.Sy = (int)c.Sy;
-    a.hx = p.hx;
-    a.ny = p.ny;
-    a.nz = p.nz;
-    a.Py = p.Py;
-    a.Pz = p.Pz;
-    a.ply = p.fy;
-    a.plz = p.fz;
-    a.twy = c.twy;
-    a.twz = c.twz;
-    a.kern = c.kern;
-    a.k_cs = p.oct_elems;
-    a.k_zs = (int64_t)p.hx * (p.Py / 2 + 1);
-    a.k_xs = p.Py / 2 + 1;
-    return launch_kspace_yz<T>(a, p.nt, st);
+    const int zper = p.rs.yz / p.lz.TL;
+    const RYzArgs a{c.S, (int64_t)p.nz * c.plane, c.plane, (int)c.Sy, p.hx, p.ny, p.nz,
+                    stage_tw(p, c.twy, p.Py), stage_tw(p, c.twz, p.Pz), c.kern, p.oct_elems,
+                    (int64_t)p.hx * (p.Py / 2 + 1), p.Py / 2 + 1, p.rs.yz, zper, div_mul(zper), div_mul(p.Py)};
+    return launch_ryz<T>(a, p.ly, p.lz, st);
 }
 
 template <typename T>
@@ -695,6 +734,26 @@ hipError_t pass_demag_1wg(const PassCtx& c, const T* m, T* hd, hipStream_t st)
     return launch_demag_1wg<T>(a, p.nt, st);
 }
 
+// The passes between the x forward and the x inverse of one demag evaluation, in
+// place on c.S: the two-plane y pass, the fused y-z pass, or y forward, the k-space pass
+// (along z, or along y on one-cell-thick grids) and y inverse.
+template <typename T>
+mm_status demag_mid(mm_sim* s, const PassCtx& c, hipStream_t st)
+{
+    if (c.p.zd) {
+        LAUNCH(KSPACE, pass_kspace_y2<T>(c, st));
+        return MM_OK;
+    }
+    if (c.p.yz || c.p.yz_small) {
+        LAUNCH(KSPACE, pass_kspace_yz<T>(c, st));
+        return MM_OK;
+    }
+    if (c.p.three_d) LAUNCH(KY_FWD, pass_y<T>(c, 0, st));
+    LAUNCH(KSPACE, pass_kspace<T>(c, st));
+    if (c.p.three_d) LAUNCH(KY_INV, pass_y<T>(c, 1, st));
+    return MM_OK;
+}
+
 // Demag field (reduced, h = H/Ms) of msrc into hd: Eq. 14 with zero padding
 // (none along periodic axes); five passes, three with the fused y-z pass, or one
 // work-group for the whole evaluation of a small grid.
@@ -706,22 +765,8 @@ mm_status demag(mm_sim* s, const T* msrc, T* hd, hipStream_t st)
         LAUNCH(KSPACE, pass_demag_1wg<T>(c, msrc, hd, st));
         return MM_OK;
     }
-    if (c.p.yz) {
-        LAUNCH(KX_FWD, pass_x_forward<T>(c, msrc, st));
-        LAUNCH(KSPACE, pass_kspace_yz<T>(c, st));
-        LAUNCH(KX_INV, pass_x_inverse<T>(c, hd, st));
-        return MM_OK;
-    }
-    if (c.p.zd) {
-        LAUNCH(KX_FWD, pass_x_forward<T>(c, msrc, st));
-        LAUNCH(KSPACE, pass_kspace_y2<T>(c, st));
-        LAUNCH(KX_INV, pass_x_inverse<T>(c, hd, st));
-        return MM_OK;
-    }
     LAUNCH(KX_FWD, pass_x_forward<T>(c, msrc, st));
-    if (c.p.three_d) LAUNCH(KY_FWD, pass_y<T>(c, 0, st));
-    LAUNCH(KSPACE, pass_kspace<T>(c, st));
-    if (c.p.three_d) LAUNCH(KY_INV, pass_y<T>(c, 1, st));
+    if (mm_status r = demag_mid<T>(s, c, st); r != MM_OK) return r;
     LAUNCH(KX_INV, pass_x_inverse<T>(c, hd, st));
     return MM_OK;
 }
@@ -789,22 +834,6 @@ mm_status rk4_step(mm_sim* s, double dt, hipStream_t st)
     return MM_OK;
 }
 
-// The passes between the x forward and the x inverse of one demag evaluation, in
-// place on c.S: the two-plane y pass, or y forward, the k-space pass (along z, or
-// along y on one-cell-thick grids) and y inverse.
-template <typename T>
-mm_status demag_mid(mm_sim* s, const PassCtx& c, hipStream_t st)
-{
-    if (c.p.zd) {
-        LAUNCH(KSPACE, pass_kspace_y2<T>(c, st));
-        return MM_OK;
-    }
-    if (c.p.three_d) LAUNCH(KY_FWD, pass_y<T>(c, 0, st));
-    LAUNCH(KSPACE, pass_kspace<T>(c, st));
-    if (c.p.three_d) LAUNCH(KY_INV, pass_y<T>(c, 1, st));
-    return MM_OK;
-}
-
 // RK4 steps of a fused-stage plan (small, open).  The spectrum of the stage input
 // sits in S: the prologue forms it for m_n (x forward); each stage then runs the
 // y / z passes on it in place and the fused pass, which writes the stage output
@@ -839,8 +868,7 @@ mm_status rk4_fused_steps(mm_sim* s, int64_t nsteps, double dt, bool prologue, h
             f.g.stage = stg + 1;
             f.S_in = bufs[stg & 1];
             f.S_out = bufs[(stg + 1) & 1];
-            LAUNCH(KLLG, launch_fused_stage<T>(f, p.Px, p.fs_lines, st) ? hipGetLastError()
-                                                                            : hipErrorInvalidValue);
+            LAUNCH(KLLG, pass_fused_stage<T>(c, f, st));
         }
     }
     return MM_OK;
@@ -997,8 +1025,7 @@ mm_status euler_impl(mm_sim* s, int64_t nsteps, double dt, const mm_segment* g =
             f.g.out = bufs[(n + 1) & 1];
             f.S_in = sb[n & 1];
             f.S_out = sb[(n + 1) & 1];
-            LAUNCH(KLLG, launch_fused_stage<T>(f, p.Px, p.fs_lines, st) ? hipGetLastError()
-                                                                        : hipErrorInvalidValue);
+            LAUNCH(KLLG, pass_fused_stage<T>(c, f, st));
         }
         if (nsteps & 1)
             HIP_TRY(hipMemcpyAsync(bufs[0], bufs[1], 3 * (size_t)p.N * sizeof(T), hipMemcpyDeviceToDevice, st));
@@ -1384,9 +1411,7 @@ mm_status backward_segment(mm_sim* s, const AdjBufs<T>& b, int64_t len, double d
                 f.hout = b.at(n, 4 + stg);
                 f.S_in = bufs[stg & 1];
                 f.S_out = bufs[(stg + 1) & 1];
-                if (!launch_fused_stage<T>(f, p.Px, p.fs_lines, st))
-                    return fail(MM_ENOTSUP, "no fused stage pass of length %d", p.Px);
-                HIP_TRY(hipGetLastError());
+                HIP_TRY(pass_fused_stage<T>(c, f, st));
             }
         }
     }
@@ -1481,9 +1506,7 @@ mm_status backward_segment(mm_sim* s, const AdjBufs<T>& b, int64_t len, double d
                 } else {
                     fa.mode = 0;
                 }
-                if (!launch_fused_adjoint<T>(fa, p.Px, p.fs_lines, st))
-                    return fail(MM_ENOTSUP, "no fused adjoint pass of length %d", p.Px);
-                HIP_TRY(hipGetLastError());
+                HIP_TRY(pass_fused_adjoint<T>(c, fa, st));
             }
             std::swap(lam, accl);
         }
@@ -2451,7 +2474,7 @@ mm_status autotune(const mm_grid* g, const mm_material* mat, const mm_options* o
             const Plan& pj = plans[j];
             if (done[j] || pj.Px != pi.Px || pj.Py != pi.Py || pj.Pz != pi.Pz || pj.total != pi.total ||
                 pj.o_kern != pi.o_kern || pj.o_S != pi.o_S || pj.o_twz != pi.o_twz || pj.zd != pi.zd ||
-                pj.fs != pi.fs)
+                pj.fs != pi.fs || pj.fs_rt != pi.fs_rt || pj.yz_small != pi.yz_small)
                 continue;
             done[j] = true;
             if (r != MM_OK) continue;
@@ -2831,7 +2854,7 @@ mm_status mm_get_plan(mm_sim* s, mm_plan_info* out)
     out->x_lines = s->p.xl;
     out->x_lines_inv = s->p.xl_inv;
     out->two_plane = s->p.zd ? 1 : 0;
-    out->fused_stage = s->p.fs ? 1 : 0;
+    out->fused_stage = s->p.fs && !s->p.fs_rt ? 1 : 0;
     return MM_OK;
 }
 

@@ -176,36 +176,28 @@ __device__ inline void fused_block(const void* S_in, void* S_out, int64_t sy, co
 }
 
 
-// The RK4 / Euler stage of the block (mm_llg_body.hpp's llg_cell on the demag field
-// the x inverse left in LDS), then the x forward of the stage output.
-template <typename T, int P, int L, bool PREFETCH>
-__device__ inline void body_fused_stage(const FusedStageArgs<T>& f, int tile, cpx<T>* lds, T* cell)
-{
-    constexpr int NT = fused_threads<P, L>();
-    constexpr int ROWS = 2 * L, XH = P / 2;
-    const LlgArgs<T>& a = f.g;
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int tpp = (ny + ROWS - 1) / ROWS;
-    const int z = tile / tpp, yb = (tile - z * tpp) * ROWS;
-    const int tid = (int)threadIdx.x;
-    // The stage update's inputs of a chunk of CH of the thread's NC cells: m and its
-    // six neighbours (a missing neighbour is the cell itself, Eq. 7, which adds
-    // m - m = 0), m_n, the accumulator, Ku.  With PREFETCH, where all of a thread's
-    // cells form one chunk, these loads are issued right after the gather's, before
-    // the x inverse: the barriers of the transforms wait for LDS only, so their
-    // latency passes while the lines are transformed (the gather's loads, issued
-    // first, are the ones its LDS stores wait for).  The registers they hold lower
-    // the waves per SIMD, which only launches of few work-groups can spare.
-    constexpr int NC = (ROWS * XH + NT - 1) / NT, CH = NC < 3 ? NC : 3;
-    constexpr bool PRE = PREFETCH && NC <= CH;
-    const int64_t N = a.N, plane = (int64_t)nx * ny;
+// A block of cells as the fused passes hold it: rows yb .. yb + rows - 1 of plane z (those
+// below ny), component d of cell (r, i) at cell[(d rows + r) w + i], taken by nt threads,
+// cell idx = tid + q nt of the block at the thread's q-th turn.
+struct CellBlock {
+    int z, yb, rows, w, nt;
+};
+
+// The stage update's inputs of a chunk of CH of the thread's cells: m and its six
+// neighbours (a missing neighbour is the cell itself, Eq. 7, which adds m - m = 0), m_n,
+// the accumulator, Ku.
+template <typename T, int CH>
+struct StageIn {
     T mv[CH][3][7], mnv[CH][3], acv[CH][3], kan[CH];
-    auto load_chunk = [&](int q0) {
+    __device__ inline void load(const LlgArgs<T>& a, const CellBlock& b, int tid, int q0, int nc)
+    {
+        const int nx = a.nx, ny = a.ny, nz = a.nz, z = b.z;
+        const int64_t N = a.N, plane = (int64_t)nx * ny;
 #pragma unroll
         for (int q = 0; q < CH; ++q) {
-            const int idx = tid + (q0 + q) * NT;
-            const int r = idx / nx, i = idx - r * nx, j = yb + r;
-            const bool in = q0 + q < NC && idx < ROWS * nx && j < ny;
+            const int idx = tid + (q0 + q) * b.nt;
+            const int r = idx / nx, i = idx - r * nx, j = b.yb + r;
+            const bool in = q0 + q < nc && idx < b.rows * nx && j < ny;
             const int64_t c = in ? z * plane + (int64_t)j * nx + i : 0;
             const int64_t dxm = in && i > 0 ? -1 : 0, dxp = in && i < nx - 1 ? 1 : 0;
             const int64_t dym = in && j > 0 ? -(int64_t)nx : 0, dyp = in && j < ny - 1 ? (int64_t)nx : 0;
@@ -229,137 +221,168 @@ __device__ inline void body_fused_stage(const FusedStageArgs<T>& f, int tile, cp
             }
             kan[q] = a.ku ? a.ku[c] : a.can;
         }
-    };
+    }
+    // the update of the chunk, the demag field read from `cell` and the result left there
+    __device__ inline void update(const LlgArgs<T>& a, const CellBlock& b, int tid, int q0, int nc, T* cell,
+                                  T* hout) const
+    {
+        const int nx = a.nx;
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            const int idx = tid + (q0 + q) * b.nt;
+            const int r = idx / nx, i = idx - r * nx, j = b.yb + r;
+            if (q0 + q >= nc || idx >= b.rows * nx || j >= a.ny) break;
+            const int64_t c = b.z * ((int64_t)nx * a.ny) + (int64_t)j * nx + i;
+            T m[3], lap[3], hd[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const T mc = mv[q][d][0];
+                T s = (T)0;
+                s += mv[q][d][1] - mc;
+                s += mv[q][d][2] - mc;
+                s += mv[q][d][3] - mc;
+                s += mv[q][d][4] - mc;
+                s += mv[q][d][5] - mc;
+                s += mv[q][d][6] - mc;
+                m[d] = mc;
+                lap[d] = s;
+                hd[d] = cell[d * b.rows * b.w + r * b.w + i];
+            }
+            T res[3];
+            llg_cell<T>(a, c, m, lap, hd, mnv[q], acv[q], kan[q], res, hout);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) cell[d * b.rows * b.w + r * b.w + i] = res[d];
+        }
+    }
+};
 
-    // stage update of the block's cells: the demag field from LDS, the rest as the
-    // plain stage kernel reads it (the x, y, z neighbours in its order); the result
-    // overwrites the cell's field in LDS.  A thread takes up to NC cells and issues
-    // the loads of CH of them before their updates (the updates store to global
-    // memory, so the compiler would not hoist later loads above them): one memory
-    // latency per CH cells instead of one per cell.
+// The RK4 / Euler stage of the block (mm_llg_body.hpp's llg_cell on the demag field
+// the x inverse left in LDS), then the x forward of the stage output.
+template <typename T, int P, int L, bool PREFETCH>
+__device__ inline void body_fused_stage(const FusedStageArgs<T>& f, int tile, cpx<T>* lds, T* cell)
+{
+    constexpr int NT = fused_threads<P, L>();
+    constexpr int ROWS = 2 * L, XH = P / 2;
+    const LlgArgs<T>& a = f.g;
+    const int tpp = (a.ny + ROWS - 1) / ROWS;
+    const int z = tile / tpp, yb = (tile - z * tpp) * ROWS;
+    const int tid = (int)threadIdx.x;
+    const CellBlock b{z, yb, ROWS, XH, NT};
+    // With PREFETCH, where all of a thread's cells form one chunk, the update's loads are
+    // issued right after the gather's, before the x inverse: the barriers of the
+    // transforms wait for LDS only, so their latency passes while the lines are
+    // transformed (the gather's loads, issued first, are the ones its LDS stores wait
+    // for).  The registers they hold lower the waves per SIMD, which only launches of few
+    // work-groups can spare.  Otherwise a thread issues the loads of CH cells before their
+    // updates (the updates store to global memory, so the compiler would not hoist later
+    // loads above them): one memory latency per CH cells instead of one per cell.
+    constexpr int NC = (ROWS * XH + NT - 1) / NT, CH = NC < 3 ? NC : 3;
+    constexpr bool PRE = PREFETCH && NC <= CH;
+    StageIn<T, CH> in;
     auto update = [&](int, int) {
         for (int q0 = 0; q0 < NC; q0 += CH) {
-            if (!PRE) load_chunk(q0);
-#pragma unroll
-            for (int q = 0; q < CH; ++q) {
-                const int idx = tid + (q0 + q) * NT;
-                const int r = idx / nx, i = idx - r * nx, j = yb + r;
-                if (q0 + q >= NC || idx >= ROWS * nx || j >= ny) break;
-                const int64_t c = z * plane + (int64_t)j * nx + i;
-                T m[3], lap[3], hd[3];
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const T mc = mv[q][d][0];
-                    T s = (T)0;
-                    s += mv[q][d][1] - mc;
-                    s += mv[q][d][2] - mc;
-                    s += mv[q][d][3] - mc;
-                    s += mv[q][d][4] - mc;
-                    s += mv[q][d][5] - mc;
-                    s += mv[q][d][6] - mc;
-                    m[d] = mc;
-                    lap[d] = s;
-                    hd[d] = cell[d * ROWS * XH + r * XH + i];
-                }
-                T res[3];
-                llg_cell<T>(a, c, m, lap, hd, mnv[q], acv[q], kan[q], res, f.hout);
-#pragma unroll
-                for (int d = 0; d < 3; ++d) cell[d * ROWS * XH + r * XH + i] = res[d];
-            }
+            if (!PRE) in.load(a, b, tid, q0, NC);
+            in.update(a, b, tid, q0, NC, cell, f.hout);
         }
     };
     auto pre = [&] {
-        if constexpr (PRE) load_chunk(0);
+        if constexpr (PRE) in.load(a, b, tid, 0, NC);
     };
-    fused_block<T, P, L>(f.S_in, f.S_out, f.sy, f.tw, nx, ny, nz, tile, true, lds, cell, pre, update);
+    fused_block<T, P, L>(f.S_in, f.S_out, f.sy, f.tw, a.nx, a.ny, a.nz, tile, true, lds, cell, pre, update);
 }
 
-// One stage of the reverse sweep on the block (FusedAdjArgs): the apply on the
-// demag field of nu the x inverse left in LDS, then the stage before's nu (after
-// the renormalisation of the step before in mode 2), whose x forward goes to
-// S_out.  The exchange term of the apply reads nu at the six neighbours (a
-// missing one is the cell itself, as in k_adj_apply), hence nu_in and nu_out are
-// different buffers.  One cell's loads at a time per thread.
+// One stage of the reverse sweep for the block's cells (FusedAdjArgs): the apply on the
+// demag field of nu that the x inverse left in `cell`, then the stage before's nu (after the
+// renormalisation of the step before in mode 2), left in `cell` for its x forward.  The
+// exchange term of the apply reads nu at the six neighbours (a missing one is the cell
+// itself, as in k_adj_apply), hence nu_in and nu_out are different buffers.  One cell's
+// loads at a time per thread.
+template <typename T>
+__device__ inline void fused_adjoint_cells(const FusedAdjArgs<T>& f, const CellBlock& b, int tid, int nc, T* cell)
+{
+    const AdjArgs<T>& a = f.a;
+    const int nx = a.nx, ny = a.ny, nz = a.nz, z = b.z;
+    const int64_t N = a.N, plane = (int64_t)nx * ny;
+    for (int q = 0; q < nc; ++q) {
+        const int idx = tid + q * b.nt;
+        const int r = idx / nx, i = idx - r * nx, j = b.yb + r;
+        if (idx >= b.rows * nx || j >= ny) break;
+        const int64_t c = z * plane + (int64_t)j * nx + i;
+        const int64_t dxm = i > 0 ? -1 : 0, dxp = i < nx - 1 ? 1 : 0;
+        const int64_t dym = j > 0 ? -(int64_t)nx : 0, dyp = j < ny - 1 ? (int64_t)nx : 0;
+        const int64_t dzm = z > 0 ? -plane : 0, dzp = z < nz - 1 ? plane : 0;
+        // apply: out = loc + cex Lap nu + hd(nu), out_x += Ku nu_x
+        T out[3], nux = (T)0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const T* u = f.nu_in + d * N + c;
+            const T uc = u[0];
+            T acc = (T)0;
+            acc += u[dxm] - uc;
+            acc += u[dxp] - uc;
+            acc += u[dym] - uc;
+            acc += u[dyp] - uc;
+            acc += u[dzm] - uc;
+            acc += u[dzp] - uc;
+            T v = a.loc[d * N + c] + a.cex * acc;
+            v += cell[d * b.rows * b.w + r * b.w + i];
+            out[d] = v;
+            if (d == 0) nux = uc;
+        }
+        out[0] += (a.ku ? a.ku[c] : a.can) * nux;
+        T accl[3], l[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            accl[d] = a.accl[d * N + c] + out[d];
+            l[d] = f.cmu * a.mu[d * N + c] + f.ca * out[d];
+        }
+        // the accumulator carries on within the step; at a step boundary it is
+        // the covector of the step before, used right here
+        if (f.mode != 2) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) a.accl[d * N + c] = accl[d];
+        }
+        if (f.mode == 0) continue;
+        const T* ms = f.ms;
+        const T* hs = f.hs;
+        if (f.mode == 2) {
+            // the step before: lam is the accumulator just formed
+            T msr[4][3], hsr[4][3], mu[3];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                ld3(f.st[s], N, c, msr[s]);
+                ld3(f.st[4 + s], N, c, hsr[s]);
+            }
+            adj_renorm_cell(msr, hsr, accl, a.G, a.alpha, mu);
+            st3(a.mu, N, c, mu);
+            st3(f.accl_prev, N, c, mu);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) l[d] = mu[d] / (T)6;
+            ms = f.st[3];
+            hs = f.st[7];
+        }
+        T m[3], h[3], nu[3], loc[3];
+        ld3(ms, N, c, m);
+        ld3(hs, N, c, h);
+        adj_nu_cell(m, h, l, a.G, a.alpha, nu, loc);
+        st3(f.nu_out, N, c, nu);
+        st3(a.loc, N, c, loc);
+        if (a.dku) a.dku[c] += (double)nu[0] * (double)m[0] * a.kfac;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) cell[d * b.rows * b.w + r * b.w + i] = nu[d];
+    }
+}
+
 template <typename T, int P, int L>
 __device__ inline void body_fused_adjoint(const FusedAdjArgs<T>& f, int tile, cpx<T>* lds, T* cell)
 {
     constexpr int NT = fused_threads<P, L>();
     constexpr int ROWS = 2 * L, XH = P / 2, NC = (ROWS * XH + NT - 1) / NT;
     const AdjArgs<T>& a = f.a;
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int tid = (int)threadIdx.x;
-    const int64_t N = a.N, plane = (int64_t)nx * ny;
     auto update = [&](int z, int yb) {
-        for (int q = 0; q < NC; ++q) {
-            const int idx = tid + q * NT;
-            const int r = idx / nx, i = idx - r * nx, j = yb + r;
-            if (idx >= ROWS * nx || j >= ny) break;
-            const int64_t c = z * plane + (int64_t)j * nx + i;
-            const int64_t dxm = i > 0 ? -1 : 0, dxp = i < nx - 1 ? 1 : 0;
-            const int64_t dym = j > 0 ? -(int64_t)nx : 0, dyp = j < ny - 1 ? (int64_t)nx : 0;
-            const int64_t dzm = z > 0 ? -plane : 0, dzp = z < nz - 1 ? plane : 0;
-            // apply: out = loc + cex Lap nu + hd(nu), out_x += Ku nu_x
-            T out[3], nux = (T)0;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const T* u = f.nu_in + d * N + c;
-                const T uc = u[0];
-                T acc = (T)0;
-                acc += u[dxm] - uc;
-                acc += u[dxp] - uc;
-                acc += u[dym] - uc;
-                acc += u[dyp] - uc;
-                acc += u[dzm] - uc;
-                acc += u[dzp] - uc;
-                T v = a.loc[d * N + c] + a.cex * acc;
-                v += cell[d * ROWS * XH + r * XH + i];
-                out[d] = v;
-                if (d == 0) nux = uc;
-            }
-            out[0] += (a.ku ? a.ku[c] : a.can) * nux;
-            T accl[3], l[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                accl[d] = a.accl[d * N + c] + out[d];
-                l[d] = f.cmu * a.mu[d * N + c] + f.ca * out[d];
-            }
-            // the accumulator carries on within the step; at a step boundary it is
-            // the covector of the step before, used right here
-            if (f.mode != 2) {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) a.accl[d * N + c] = accl[d];
-            }
-            if (f.mode == 0) continue;
-            const T* ms = f.ms;
-            const T* hs = f.hs;
-            if (f.mode == 2) {
-                // the step before: lam is the accumulator just formed
-                T msr[4][3], hsr[4][3], mu[3];
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    ld3(f.st[s], N, c, msr[s]);
-                    ld3(f.st[4 + s], N, c, hsr[s]);
-                }
-                adj_renorm_cell(msr, hsr, accl, a.G, a.alpha, mu);
-                st3(a.mu, N, c, mu);
-                st3(f.accl_prev, N, c, mu);
-#pragma unroll
-                for (int d = 0; d < 3; ++d) l[d] = mu[d] / (T)6;
-                ms = f.st[3];
-                hs = f.st[7];
-            }
-            T m[3], h[3], nu[3], loc[3];
-            ld3(ms, N, c, m);
-            ld3(hs, N, c, h);
-            adj_nu_cell(m, h, l, a.G, a.alpha, nu, loc);
-            st3(f.nu_out, N, c, nu);
-            st3(a.loc, N, c, loc);
-            if (a.dku) a.dku[c] += (double)nu[0] * (double)m[0] * a.kfac;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) cell[d * ROWS * XH + r * XH + i] = nu[d];
-        }
+        fused_adjoint_cells(f, CellBlock{z, yb, ROWS, XH, NT}, (int)threadIdx.x, NC, cell);
     };
-    fused_block<T, P, L>(f.S_in, f.S_out, f.sy, f.tw, nx, ny, nz, tile, f.mode != 0, lds, cell, [] {}, update);
+    fused_block<T, P, L>(f.S_in, f.S_out, f.sy, f.tw, a.nx, a.ny, a.nz, tile, f.mode != 0, lds, cell, [] {}, update);
 }
 
 }  // namespace mm

@@ -97,24 +97,6 @@ struct KspArgs {
     int64_t k_cs, k_zs, k_xs;  // octant strides for component, kz, kx (ky is contiguous)
 };
 
-// Fused y-z pass (3-pass schedule): one work-group per x bin holds the whole
-// [3][Pz][Py] plane of that bin in LDS: y forward, z forward, Eq. 14 product,
-// z inverse, y inverse, in place in S = [3][nz][hx][Sy].  For 3-D grids whose
-// plane fits a work-group (3 Py Pz <= kElemsPerThread x threads).
-struct KyzArgs {
-    void* buf;
-    int64_t comp_stride;     // nz * hx * Sy
-    int64_t zs;              // hx * Sy: one z plane of S
-    int Sy, hx, ny, nz, Py, Pz;
-    FftPlan ply, plz;
-    const void* twy;
-    const void* twz;
-    const void* kern;        // octant [6][Pz/2+1][hx][Py/2+1]
-    int64_t k_cs, k_zs, k_xs;
-};
-template <typename T>
-hipError_t launch_kspace_yz(const KyzArgs& a, int nt, hipStream_t s);
-
 // Passes of any 7-smooth length by register radices chosen at run time (mm_rline.hpp,
 // mm_rline.hip).  `tws`: the stage twiddles of the length (LinePlan); dynamic LDS of
 // rline_lds() bytes.
@@ -168,12 +150,25 @@ struct RKy2Args {            // y k-space pass of a two-cell-thick grid (see Ky2
     int L;                   // x bins per work-group
     unsigned dmul;           // divides by Py
 };
+struct RYzArgs {             // y forward, z k-space and y inverse of one x bin in LDS
+    void* buf;
+    int64_t comp_stride;     // nz * hx * Sy
+    int64_t zs;              // hx * Sy: one z plane of S
+    int Sy, hx, ny, nz;
+    const void *twsy, *twsz;
+    const void* kern;        // octant [6][Pz/2+1][hx][Py/2+1]
+    int64_t k_cs, k_zs, k_xs;
+    int nt;                  // threads of a work-group
+    int zper;                // z lines a round takes
+    unsigned zmul, ymul;     // divide by zper, by Py
+};
 // Work-group shapes of these passes for one grid: lines (or columns) per work-group.
 // Zero where the pass has no such shape (the length's schedule, threads or LDS).
 struct RShape {
     int lsh_f, lsh_i;        // x forward, x inverse (log2 of the lines), -1: none
     int y, ky, ky2;          // lines of the y passes, x bins of the y k-space passes
     int csh;                 // log2 of the columns of the z k-space pass, -1: none
+    int yz;                  // threads of the fused y-z pass, 0: none
 };
 bool make_line_plan(int P, LinePlan* s);
 // multiplier with which n / d = umulhi(n, mul) for n d < 2^32, d > 1
@@ -195,6 +190,9 @@ template <typename T>
 hipError_t launch_rkz(const RKzArgs& a, const LinePlan& s, hipStream_t st);
 template <typename T>
 hipError_t launch_rky(const RKyArgs& a, const LinePlan& s, hipStream_t st);
+size_t ryz_lds_bytes(int Py, int Pz, size_t esz);
+template <typename T>
+hipError_t launch_ryz(const RYzArgs& a, const LinePlan& y, const LinePlan& z, hipStream_t st);
 
 // Compile-time specialised passes for power-of-two sizes (mm_fast.hip).  Each
 // launcher returns false (and launches nothing) when no specialisation fits.
@@ -420,6 +418,26 @@ struct FusedAdjArgs {
 };
 template <typename T>
 bool launch_fused_adjoint(const FusedAdjArgs<T>& a, int Px, int L, hipStream_t s);
+// Both for x lengths without a size-specialised pass (mm_rfused.hpp): L row pairs a
+// work-group (1, 2 or 4, 0 where none fits), tws the stage twiddles of the length.
+struct RFusedArgs {
+    const void* S_in;
+    void* S_out;
+    int64_t sy;
+    const void* tws;
+    int nx, ny, nz, L;
+    int rsh;             // log2 of the rows, 2 L
+    unsigned hmul;       // divides by hx
+};
+__host__ __device__ constexpr int rfused_region(int L, int P)
+{
+    return L * (P | 1) > 2 * L * (P / 2 + 1) ? L * (P | 1) : 2 * L * (P / 2 + 1);
+}
+int rfused_lines(const LinePlan& s, int nx, int rows, size_t esz);
+template <typename T>
+bool launch_rfused_stage(const FusedStageArgs<T>& f, const void* tws, const LinePlan& s, int L, hipStream_t st);
+template <typename T>
+bool launch_rfused_adjoint(const FusedAdjArgs<T>& f, const void* tws, const LinePlan& s, int L, hipStream_t st);
 template <typename T>
 hipError_t launch_adj_renorm(const AdjArgs<T>& a, hipStream_t s);
 template <typename T>

@@ -35,13 +35,6 @@ __global__ __launch_bounds__(NT) void k_col_fft(ColArgs a)
 }
 
 template <typename T, int NT>
-__global__ __launch_bounds__(NT) void k_kspace_yz(KyzArgs a)
-{
-    __shared__ cpx<T> lds[lds_elems(NT)];
-    body_kspace_yz<T, NT>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
-}
-
-template <typename T, int NT>
 __global__ __launch_bounds__(NT) void k_demag_1wg(Demag1Args a)
 {
     __shared__ cpx<T> lds[lds_elems(NT)];
@@ -143,14 +136,6 @@ hipError_t launch_kspace(const KspArgs& a, int nt, hipStream_t s)
 }
 
 template <typename T>
-hipError_t launch_kspace_yz(const KyzArgs& a, int nt, hipStream_t s)
-{
-    if (a.hx <= 0) return hipSuccess;
-    MM_LAUNCH_NT(k_kspace_yz, T, a.hx, nt, s, a);
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_demag_1wg(const Demag1Args& a, int nt, hipStream_t s)
 {
     // the padded volume of the three components must fit the work-group's LDS
@@ -169,8 +154,6 @@ template bool launch_kspace_fixed<float>(const KspArgs&, int, hipStream_t);
 template bool launch_kspace_fixed<double>(const KspArgs&, int, hipStream_t);
 template hipError_t launch_kspace<float>(const KspArgs&, int, hipStream_t);
 template hipError_t launch_kspace<double>(const KspArgs&, int, hipStream_t);
-template hipError_t launch_kspace_yz<float>(const KyzArgs&, int, hipStream_t);
-template hipError_t launch_kspace_yz<double>(const KyzArgs&, int, hipStream_t);
 template hipError_t launch_demag_1wg<float>(const Demag1Args&, int, hipStream_t);
 template hipError_t launch_demag_1wg<double>(const Demag1Args&, int, hipStream_t);
 

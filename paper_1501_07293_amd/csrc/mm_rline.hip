@@ -1,5 +1,7 @@
 // mm_rline.hip -- kernels of the runtime-length register passes (bodies in
 // mm_rline.hpp), the choice of a line's radices and of the work-group shapes.
+#include <algorithm>
+
 #include "mm_rline.hpp"
 
 namespace mm {
@@ -32,6 +34,16 @@ template <typename T, int RM>
 __global__ __launch_bounds__(kRMaxThreads) void k_rky(RKyArgs a, LinePlan s)
 {
     body_rky<T, RM>(a, s, xcd_tile(blockIdx.x, gridDim.x), reinterpret_cast<cpx<T>*>(rline_smem));
+}
+
+// FP32 work-groups of up to 1024 threads (128 registers a thread hold every radix)
+template <typename T>
+constexpr int ryz_max_threads() { return sizeof(T) == 4 ? 1024 : kRMaxThreads; }
+
+template <typename T, int RM>
+__global__ __launch_bounds__(ryz_max_threads<T>()) void k_ryz(RYzArgs a, LinePlan y, LinePlan z)
+{
+    body_ryz<T, RM>(a, y, z, xcd_tile(blockIdx.x, gridDim.x), reinterpret_cast<cpx<T>*>(rline_smem));
 }
 
 // p[i] = exp(-2 pi i r k / (span R)) for the entry's stage, r and k
@@ -124,6 +136,7 @@ bool make_line_plan(int P, LinePlan* s)
 constexpr size_t kRLdsBudget = 64 * 1024;  // dynamic LDS of a work-group
 
 size_t rline_lds_bytes(int lines, int P, size_t esz) { return (size_t)lines * rline_len(P) * 2 * esz; }
+size_t ryz_lds_bytes(int Py, int Pz, size_t esz) { return (size_t)3 * Pz * rline_len(Py) * 2 * esz; }
 size_t rxinv_lds_bytes(int lsh, int P, size_t esz)
 {
     const size_t lines = rline_lds_bytes(1 << lsh, P, esz), raw = (size_t)(2 << lsh) * (P / 2 + 1) * 2 * esz;
@@ -133,7 +146,7 @@ size_t rxinv_lds_bytes(int lsh, int P, size_t esz)
 RShape rline_shapes(const LinePlan& x, const LinePlan& y, const LinePlan& z, int nx, int ny, int nz, size_t esz,
                     int max_threads, int min_groups)
 {
-    RShape r{-1, -1, 0, 0, 0, -1};
+    RShape r{-1, -1, 0, 0, 0, -1, 0};
     const int pairs = (ny + 1) / 2;
     if (x.ns > 0) {
         // 128-byte transposed segments (8 row pairs in FP32, 4 in FP64), more where a
@@ -176,6 +189,15 @@ RShape rline_shapes(const LinePlan& x, const LinePlan& y, const LinePlan& z, int
         while (c > 0 && (!fits(c) || ((3 * z.TL << c) > 256 && c > 4))) --c;
         // the pass addresses the whole spectrum from one descriptor
         if (fits(c) && 3 * nz * ncols * 2 * (int64_t)esz < kBufEnd) r.csh = c;
+    }
+    if (y.ns > 0 && z.ns > 0 && nz > 1 && y.TL <= kRMaxThreads && z.TL <= kRMaxThreads &&
+        ryz_lds_bytes(y.P, z.P, esz) <= kLdsBudget &&
+        3 * (int64_t)nz * (x.P / 2 + 1) * y.P * 2 * (int64_t)esz < kRLineBytes) {
+        // as many threads as the longer of the two line sets takes: there are about as
+        // many bins as CUs or fewer, so what counts is the number of rounds
+        const int cap = esz == 4 ? 1024 : kRMaxThreads;
+        const int want = std::max(3 * nz * y.TL, 3 * y.P * z.TL);
+        r.yz = std::min(cap, std::max(256, (want + 63) / 64 * 64));
     }
     return r;
 }
@@ -244,12 +266,31 @@ hipError_t launch_rky(const RKyArgs& a, const LinePlan& s, hipStream_t st)
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_ryz(const RYzArgs& a, const LinePlan& y, const LinePlan& z, hipStream_t st)
+{
+    const size_t lds = ryz_lds_bytes(y.P, z.P, sizeof(T));
+    if (a.nt > ryz_max_threads<T>() || y.TL > a.nt || z.TL > a.nt || lds > (size_t)kLdsBudget) return hipErrorInvalidValue;
+    if (a.hx <= 0) return hipSuccess;
+    auto go = [&](auto kern) {
+        if (lds > kRLdsBudget) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kern, dim3(a.hx), dim3(a.nt), lds, st, a, y, z);
+        return hipGetLastError();
+    };
+    return small_radices(y) && small_radices(z) ? go(k_ryz<T, 10>) : go(k_ryz<T, 16>);
+}
+
 #define MM_INST(T)                                                                       \
     template hipError_t launch_stage_twiddles<T>(void*, const LinePlan&, hipStream_t);   \
     template hipError_t launch_rxline<T>(const RXArgs&, const LinePlan&, int, hipStream_t); \
     template hipError_t launch_ryline<T>(const RYArgs&, const LinePlan&, int, hipStream_t); \
     template hipError_t launch_rkz<T>(const RKzArgs&, const LinePlan&, hipStream_t);     \
-    template hipError_t launch_rky<T>(const RKyArgs&, const LinePlan&, hipStream_t);
+    template hipError_t launch_rky<T>(const RKyArgs&, const LinePlan&, hipStream_t);     \
+    template hipError_t launch_ryz<T>(const RYzArgs&, const LinePlan&, const LinePlan&, hipStream_t);
 MM_INST(float)
 MM_INST(double)
 #undef MM_INST

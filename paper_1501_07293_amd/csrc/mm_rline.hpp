@@ -124,27 +124,28 @@ struct LineStage {
 struct LineRegs {
     int P, ns, TL;
     unsigned tmul;
-    LineStage st[kMaxLineStages];
-    __device__ inline explicit LineRegs(const LinePlan& s)
-        : P(sgpr(s.P)), ns(sgpr(s.ns)), TL(sgpr(s.TL)), tmul((unsigned)sgpr((int)s.tmul))
+    LineStage s0, s1, s2, s3, s4;  // named, not an array: every access is a register
+    static __device__ inline LineStage load(const LinePlan& s, int q)
     {
-#pragma unroll
-        for (int q = 0; q < kMaxLineStages; ++q)
-            st[q] = LineStage{sgpr(s.R[q]), sgpr(s.p[q]), sgpr(s.m[q]), sgpr(s.toff[q]), (unsigned)sgpr((int)s.pmul[q])};
+        return LineStage{sgpr(s.R[q]), sgpr(s.p[q]), sgpr(s.m[q]), sgpr(s.toff[q]), (unsigned)sgpr((int)s.pmul[q])};
+    }
+    __device__ inline explicit LineRegs(const LinePlan& s)
+        : P(sgpr(s.P)), ns(sgpr(s.ns)), TL(sgpr(s.TL)), tmul((unsigned)sgpr((int)s.tmul)), s0(load(s, 0)),
+          s1(load(s, 1)), s2(load(s, 2)), s3(load(s, 3)), s4(load(s, 4))
+    {
+        static_assert(kMaxLineStages == 5, "stages named by hand");
     }
     __device__ inline LineStage stage(int q) const
     {
-        static_assert(kMaxLineStages == 5, "stages picked by hand");
         // by value through readfirstlane: a choice between the fields' addresses would
         // put the schedule into private memory
-        auto pick = [q](int a1, int a2, int a3, int a4) {
-            a1 = sgpr(a1), a2 = sgpr(a2), a3 = sgpr(a3), a4 = sgpr(a4);
-            return q == 1 ? a1 : (q == 2 ? a2 : (q == 3 ? a3 : a4));
+        auto pick = [q](int a0, int a1, int a2, int a3, int a4) {
+            a0 = sgpr(a0), a1 = sgpr(a1), a2 = sgpr(a2), a3 = sgpr(a3), a4 = sgpr(a4);
+            return q == 0 ? a0 : (q == 1 ? a1 : (q == 2 ? a2 : (q == 3 ? a3 : a4)));
         };
-        return LineStage{pick(st[1].R, st[2].R, st[3].R, st[4].R), pick(st[1].p, st[2].p, st[3].p, st[4].p),
-                         pick(st[1].m, st[2].m, st[3].m, st[4].m),
-                         pick(st[1].toff, st[2].toff, st[3].toff, st[4].toff),
-                         (unsigned)pick((int)st[1].pmul, (int)st[2].pmul, (int)st[3].pmul, (int)st[4].pmul)};
+        return LineStage{pick(s0.R, s1.R, s2.R, s3.R, s4.R), pick(s0.p, s1.p, s2.p, s3.p, s4.p),
+                         pick(s0.m, s1.m, s2.m, s3.m, s4.m), pick(s0.toff, s1.toff, s2.toff, s3.toff, s4.toff),
+                         (unsigned)pick((int)s0.pmul, (int)s1.pmul, (int)s2.pmul, (int)s3.pmul, (int)s4.pmul)};
     }
 };
 
@@ -226,16 +227,18 @@ __device__ inline LaneOf rline_lane(const LineRegs& s, int lines)
 // compiler keeps the values of all cases side by side (up to 256 registers, spilled).
 constexpr int kPastEnd = 0x40000000;
 
-template <typename T, int RM, bool SYNC, bool PUT_LDS, class Get, class Put>
-__device__ inline void rline_fft(const LineRegs& s, const cpx<T>* __restrict__ tws, cpx<T>* ln, int u, bool real,
-                                 Get get, Put put)
+// ES: entries from one element of the line to the next in LDS (0: es, a run-time value).
+template <typename T, int RM, bool SYNC, bool PUT_LDS, int ES = 1, class Get, class Put>
+__device__ __forceinline__ void rline_fft(const LineRegs& s, const cpx<T>* __restrict__ tws, cpx<T>* ln, int u, bool real,
+                                          Get get, Put put, int es = 1)
 {
     const int ns = s.ns;
+    if constexpr (ES != 0) es = ES;
     {
-        const int m = s.st[0].m;
+        const int m = s.s0.m;
         const int i = u < m ? u : 0;
         const int io = PUT_LDS || (real && u < m) ? i : kPastEnd;
-        switch (s.st[0].R) {
+        switch (s.s0.R) {
 #define X(RR)                                                                         \
     case RR:                                                                          \
         if constexpr (RR <= RM) {                                                     \
@@ -246,8 +249,8 @@ __device__ inline void rline_fft(const LineRegs& s, const cpx<T>* __restrict__ t
             if (ns == 1) {                                                            \
                 _Pragma("unroll") for (int r = 0; r < RR; ++r) put(io + r, v[r]);     \
             } else {                                                                  \
-                cpx<T>* o = ln + i * RR;                                              \
-                _Pragma("unroll") for (int r = 0; r < RR; ++r) o[r] = v[r];           \
+                cpx<T>* o = ln + i * RR * es;                                         \
+                _Pragma("unroll") for (int r = 0; r < RR; ++r) o[r * es] = v[r];      \
             }                                                                         \
         }                                                                             \
         break;
@@ -271,12 +274,12 @@ __device__ inline void rline_fft(const LineRegs& s, const cpx<T>* __restrict__ t
         if constexpr (RR <= RM) {                                                             \
             cpx<T> v[RR], tw[RR];                                                             \
             _Pragma("unroll") for (int r = 1; r < RR; ++r) tw[r] = ld_tw(w + (r - 1) * p, kb); \
-            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = ln[i + r * m];              \
+            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = ln[(i + r * m) * es];       \
             _Pragma("unroll") for (int r = 1; r < RR; ++r) v[r] = cmul(v[r], tw[r]);          \
             Dft<T, RR>::run(v);                                                               \
             __syncthreads();                                                                  \
-            cpx<T>* o = ln + (i - k) * RR + k;                                                \
-            _Pragma("unroll") for (int r = 0; r < RR; ++r) o[r * p] = v[r];                   \
+            cpx<T>* o = ln + ((i - k) * RR + k) * es;                                         \
+            _Pragma("unroll") for (int r = 0; r < RR; ++r) o[r * p * es] = v[r];              \
         }                                                                                     \
         break;
             MM_RADIX_CASES(X)
@@ -301,7 +304,7 @@ __device__ inline void rline_fft(const LineRegs& s, const cpx<T>* __restrict__ t
         if constexpr (RR <= RM) {                                                             \
             cpx<T> v[RR], tw[RR];                                                             \
             _Pragma("unroll") for (int r = 1; r < RR; ++r) tw[r] = ld_tw(w + (r - 1) * m, kb); \
-            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = ln[i + r * m];              \
+            _Pragma("unroll") for (int r = 0; r < RR; ++r) v[r] = ln[(i + r * m) * es];       \
             _Pragma("unroll") for (int r = 1; r < RR; ++r) v[r] = cmul(v[r], tw[r]);          \
             Dft<T, RR>::run(v);                                                               \
             if (PUT_LDS) __syncthreads();                                                     \
@@ -634,6 +637,111 @@ __device__ inline void body_rky2(const RKy2Args& a, const LinePlan& pl, int tile
     rline_fft<T, RM, true, false>(
         s, (const cpx<T>*)a.tws, ln, w.u, w.real, [&](int e) { return ln[e]; },
         [&](int e, cpx<T> x) { buf_st(g, e < ny ? at + (unsigned)e * CS : kBufNone, conj(x)); });
+}
+
+// ------------------------------------------------------- y, z and k-space in one
+// Small 3-D grids: one work-group per x bin holds the bin's plane [3][Pz][Py] in LDS and
+// runs the y lines of its nz planes, every z line, the Eq. 14 product and the way back:
+// one launch where y forward, z k-space and y inverse are three dependent ones of 4 to 5
+// us each at these sizes, and no Py-long spectrum in memory.  Lines are taken in rounds
+// of as many as the threads hold.  What bounds it is the chain of LDS stages: bins are
+// too few to fill the chip several times over.
+constexpr int kRyzChunk = 4;  // product elements a thread loads spectra for at a time
+
+template <typename T, int RM>
+__device__ inline void body_ryz(const RYzArgs& a, const LinePlan& ply, const LinePlan& plz, int kx, cpx<T>* lds)
+{
+    const LineRegs sy(ply), sz(plz);
+    const int Py = sy.P, Pz = sz.P, LP = rline_len(Py), PL = Pz * LP;
+    const int t = (int)threadIdx.x, NT = blockDim.x, ny = a.ny, nz = a.nz;
+    constexpr unsigned CS = sizeof(cpx<T>);
+    const Buf g = buf_of((const cpx<T>*)a.buf + (int64_t)kx * a.Sy);
+    const T* K = (const T*)a.kern + kx * a.k_xs;
+    // Eq. 14 spectra of this thread's elements [ky + Py kz], kRyzChunk of them at a time
+    T kv[kRyzChunk][6];
+    auto load_k = [&](int i0) {
+#pragma unroll
+        for (int it = 0; it < kRyzChunk; ++it) {
+            const int idx = i0 + t + it * NT;
+            int kz = div_by(idx, a.ymul), ky = idx - kz * Py;
+            if (2 * ky > Py) ky = Py - ky;
+            if (2 * kz > Pz) kz = Pz - kz;
+            const T* Kp = K + (idx < Py * Pz ? kz * a.k_zs + ky : 0);
+#pragma unroll
+            for (int c = 0; c < 6; ++c) kv[it][c] = Kp[c * a.k_cs];
+        }
+    };
+    // the padding planes enter the z lines as zeros
+    for (int i = t; i < 3 * (Pz - nz) * LP; i += NT) {
+        const int c = i / ((Pz - nz) * LP), r = i - c * (Pz - nz) * LP;
+        lds[c * PL + nz * LP + r] = cpx<T>{(T)0, (T)0};
+    }
+    const int yper = NT / sy.TL, zper = a.zper;
+    // y lines: line q = c nz + z, from memory into plane c, row z
+    auto y_line = [&](int q0, int& q, bool& real, int& u) {
+        const LaneOf w = rline_lane(sy, min(yper, 3 * nz - q0));
+        q = q0 + w.l;
+        real = w.real;
+        u = w.u;
+    };
+    for (int q0 = 0; q0 < 3 * nz; q0 += yper) {
+        int q, u;
+        bool real;
+        y_line(q0, q, real, u);
+        const int c = q / nz, z = q - c * nz;
+        const unsigned at = ((unsigned)c * (unsigned)a.comp_stride + (unsigned)z * (unsigned)a.zs) * CS;
+        cpx<T>* ln = lds + c * PL + z * LP;
+        rline_fft<T, RM, false, true>(
+            sy, (const cpx<T>*)a.twsy, ln, u, real,
+            [&](int e) { return buf_ld<cpx<T>>(g, e < ny ? at + (unsigned)e * CS : kBufNone); },
+            [&](int e, cpx<T> x) { ln[e] = x; });
+    }
+    load_k(0);
+    __syncthreads();
+    // z lines: line q = c Py + y, lanes line-fastest (neighbouring entries of a row)
+    auto z_lines = [&]() __attribute__((always_inline)) {
+        for (int q0 = 0; q0 < 3 * Py; q0 += zper) {
+            int u = sz.TL == 1 ? 0 : div_by(t, a.zmul);
+            int q = q0 + t - u * zper;
+            const bool real = u < sz.TL && q < 3 * Py;
+            if (!real) u = 0, q = q0;
+            const int c = div_by(q, a.ymul);
+            cpx<T>* ln = lds + c * PL + (q - c * Py);
+            rline_fft<T, RM, true, true, 0>(
+                sz, (const cpx<T>*)a.twsz, ln, u, real, [&](int e) { return ln[e * LP]; },
+                [&](int e, cpx<T> x) { ln[e * LP] = x; }, LP);
+        }
+        __syncthreads();
+    };
+    z_lines();
+    for (int i0 = 0; i0 < Py * Pz; i0 += kRyzChunk * NT) {
+        if (i0 > 0) load_k(i0);
+#pragma unroll
+        for (int it = 0; it < kRyzChunk; ++it) {
+            const int idx = i0 + t + it * NT;
+            if (idx < Py * Pz) {
+                // mirrored frequencies: xy odd in y, xz odd in z, yz odd in both
+                const int kz = div_by(idx, a.ymul), ky = idx - kz * Py;
+                const T my = 2 * ky > Py ? (T)-1 : (T)1, mz = 2 * kz > Pz ? (T)-1 : (T)1;
+                const T k[6] = {kv[it][0], my * kv[it][1], mz * kv[it][2], kv[it][3], my * mz * kv[it][4], kv[it][5]};
+                cpx<T>* q = lds + kz * LP + ky;
+                tensor_product(q, q + PL, q + 2 * PL, k);
+            }
+        }
+    }
+    __syncthreads();
+    z_lines();
+    for (int q0 = 0; q0 < 3 * nz; q0 += yper) {
+        int q, u;
+        bool real;
+        y_line(q0, q, real, u);
+        const int c = q / nz, z = q - c * nz;
+        const unsigned at = ((unsigned)c * (unsigned)a.comp_stride + (unsigned)z * (unsigned)a.zs) * CS;
+        cpx<T>* ln = lds + c * PL + z * LP;
+        rline_fft<T, RM, true, false>(
+            sy, (const cpx<T>*)a.twsy, ln, u, real, [&](int e) { return ln[e]; },
+            [&](int e, cpx<T> x) { buf_st(g, e < ny ? at + (unsigned)e * CS : kBufNone, conj(x)); });
+    }
 }
 
 }  // namespace mm
