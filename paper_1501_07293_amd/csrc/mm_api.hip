@@ -178,7 +178,12 @@ bool yz_is_small(const Plan& p, bool generic)
 // grid fills (the launch holds the tiles of all of them).
 RShape batch_shapes(const Plan& p)
 {
-    return rline_shapes(p.lx, p.ly, p.lz, p.nx, p.ny, p.nz, p.esz, 256, 0);
+    RShape r = rline_shapes(p.lx, p.ly, p.lz, p.nx, p.ny, p.nz, p.esz, kBatchNT, 0);
+    // y k-space lines too wide for 256 threads (three or six of them at once) take 512
+    const RShape wide = rline_shapes(p.lx, p.ly, p.lz, p.nx, p.ny, p.nz, p.esz, 2 * kBatchNT, 0);
+    if (r.ky == 0) r.ky = wide.ky;
+    if (r.ky2 == 0) r.ky2 = wide.ky2;
+    return r;
 }
 
 // two_plane: a batch of runtime-length passes takes the two-plane schedule too
@@ -605,6 +610,7 @@ hipError_t pass_kspace(const PassCtx& c, hipStream_t st)
         KzArgs kz{c.S, (int64_t)p.nz * c.plane, (int)c.plane, p.nz, p.Py, c.twz, c.kern, p.oct_elems,
                   k_zs, k_xs};
         if (c.fast && launch_kspace_z<T>(kz, p.Pz, st)) return hipGetLastError();
+        if (c.fast && launch_kspace_z_mixed<T>(kz, p.Pz, st)) return hipGetLastError();
         k.comp_stride = (int64_t)p.nz * c.plane;
         k.ncols = (int)c.plane;
         k.cols_per_row = (int)c.plane;
@@ -1643,7 +1649,8 @@ struct BatchClassHost {
     int P;
     std::vector<int> members, prefix;
     size_t off;  // element offset of members, then prefix, in the device int array
-    size_t lds = 0;  // dynamic LDS of a work-group (register passes)
+    size_t lds = 0;  // dynamic LDS and threads of a work-group (register passes; P then holds
+    int nt = 0;      // the largest radix + 1000 per 256 threads)
 };
 
 bool fast_supported(int kind, int P, size_t esz)
@@ -1755,10 +1762,12 @@ void batch_rline_classes(int32_t n, BatchLayout* L, ClassOf class_of, AddTo add_
         for (int q = 0; q < l.ns; ++q) r = std::max(r, l.R[q]);
         return r <= 10 ? 10 : 16;
     };
-    auto pass = [&](int kind, int s, const LinePlan& l, int64_t tiles, size_t lds) {
-        BatchClassHost& c = class_of(kind, rmax(l));
+    auto pass = [&](int kind, int s, const LinePlan& l, int64_t tiles, size_t lds, int threads = kBatchNT) {
+        const int nt = threads <= kBatchNT ? kBatchNT : 2 * kBatchNT;
+        BatchClassHost& c = class_of(kind, rmax(l) + 1000 * (nt / kBatchNT));
         add_to(c, s, tiles);
         c.lds = std::max(c.lds, lds);
+        c.nt = nt;
     };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return L->plans[a].Px < L->plans[b].Px; });
     for (int s : order) {
@@ -1772,12 +1781,14 @@ void batch_rline_classes(int32_t n, BatchLayout* L, ClassOf class_of, AddTo add_
         const Plan& p = L->plans[s];
         const RShape& r = L->desc[s].rs;
         if (p.zd) {
-            pass(kBatchRKind + kRPassKy2, s, p.ly, up(p.hx, r.ky2), rline_lds_bytes(6 * r.ky2, p.Py, p.esz));
+            pass(kBatchRKind + kRPassKy2, s, p.ly, up(p.hx, r.ky2), rline_lds_bytes(6 * r.ky2, p.Py, p.esz),
+                 6 * r.ky2 * p.ly.TL);
         } else if (p.three_d) {
             pass(kBatchRKind + kRPassY, s, p.ly, up(3 * (int64_t)p.nz * p.hx, r.y), rline_lds_bytes(r.y, p.Py, p.esz));
             pass(kBatchRKind + kRPassKz, s, p.lz, up(p.hx * (int64_t)p.Py, 1 << r.csh), rline_lds_bytes(3 << r.csh, p.Pz, p.esz));
         } else {
-            pass(kBatchRKind + kRPassKy, s, p.ly, up(p.hx, r.ky), rline_lds_bytes(3 * r.ky, p.Py, p.esz));
+            pass(kBatchRKind + kRPassKy, s, p.ly, up(p.hx, r.ky), rline_lds_bytes(3 * r.ky, p.Py, p.esz),
+                 3 * r.ky * p.ly.TL);
         }
     }
 }
@@ -2009,7 +2020,7 @@ mm_status batch_demag(mm_batch* b, const T* in, hipStream_t st)
                 bc.prefix = cints + c.off + c.members.size();
                 bc.nmem = (int)c.members.size();
                 if (kind >= kBatchRKind) {
-                    HIP_TRY(launch_batch_rline<T>(launch_kind, c.P, bc, c.prefix.back(), inverse, c.lds, st));
+                    HIP_TRY(launch_batch_rline<T>(launch_kind, c.P % 1000, c.nt, bc, c.prefix.back(), inverse, c.lds, st));
                     continue;
                 }
                 if (!launch_batch_class<T>(launch_kind, c.P, bc, c.prefix.back(), inverse, st))

@@ -8,7 +8,7 @@ namespace mm {
 extern __shared__ __align__(16) char batch_smem[];
 
 template <typename T, int RM, bool INV>
-__global__ __launch_bounds__(kBatchNT) void kbr_x(BatchClass<T> p)
+__global__ __launch_bounds__(2 * kBatchNT) void kbr_x(BatchClass<T> p)
 {
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int s = find_sample(p.prefix, p.nmem, tile);
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kBatchNT) void kbr_x(BatchClass<T> p)
 }
 
 template <typename T, int RM, bool INV>
-__global__ __launch_bounds__(kBatchNT) void kbr_y(BatchClass<T> p)
+__global__ __launch_bounds__(2 * kBatchNT) void kbr_y(BatchClass<T> p)
 {
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int s = find_sample(p.prefix, p.nmem, tile);
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kBatchNT) void kbr_y(BatchClass<T> p)
 }
 
 template <typename T, int RM>
-__global__ __launch_bounds__(kBatchNT) void kbr_kz(BatchClass<T> p)
+__global__ __launch_bounds__(2 * kBatchNT) void kbr_kz(BatchClass<T> p)
 {
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int s = find_sample(p.prefix, p.nmem, tile);
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kBatchNT) void kbr_kz(BatchClass<T> p)
 }
 
 template <typename T, int RM>
-__global__ __launch_bounds__(kBatchNT) void kbr_ky(BatchClass<T> p)
+__global__ __launch_bounds__(2 * kBatchNT) void kbr_ky(BatchClass<T> p)
 {
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int s = find_sample(p.prefix, p.nmem, tile);
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kBatchNT) void kbr_ky(BatchClass<T> p)
 }
 
 template <typename T, int RM>
-__global__ __launch_bounds__(kBatchNT) void kbr_ky2(BatchClass<T> p)
+__global__ __launch_bounds__(2 * kBatchNT) void kbr_ky2(BatchClass<T> p)
 {
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int s = find_sample(p.prefix, p.nmem, tile);
@@ -71,9 +71,10 @@ __global__ __launch_bounds__(kBatchNT) void kbr_ky2(BatchClass<T> p)
 }
 
 template <typename T, int RM>
-static hipError_t batch_rline_go(int pass, const BatchClass<T>& c, int tiles, int inverse, size_t lds, hipStream_t s)
+static hipError_t batch_rline_go(int pass, int nt, const BatchClass<T>& c, int tiles, int inverse, size_t lds,
+                                 hipStream_t s)
 {
-    const dim3 grid(tiles), block(kBatchNT);
+    const dim3 grid(tiles), block(nt);
     switch (pass) {
     case kRPassX:
         if (inverse)
@@ -95,14 +96,15 @@ static hipError_t batch_rline_go(int pass, const BatchClass<T>& c, int tiles, in
 }
 
 template <typename T>
-hipError_t launch_batch_rline(int pass, int rmax, const BatchClass<T>& c, int tiles, int inverse, size_t lds,
-                              hipStream_t s)
+hipError_t launch_batch_rline(int pass, int rmax, int nt, const BatchClass<T>& c, int tiles, int inverse,
+                              size_t lds, hipStream_t s)
 {
+    if (nt != kBatchNT && nt != 2 * kBatchNT) return hipErrorInvalidValue;
     if (tiles <= 0) return hipSuccess;
-    return rmax <= 10 ? batch_rline_go<T, 10>(pass, c, tiles, inverse, lds, s)
-                      : batch_rline_go<T, 16>(pass, c, tiles, inverse, lds, s);
+    return rmax <= 10 ? batch_rline_go<T, 10>(pass, nt, c, tiles, inverse, lds, s)
+                      : batch_rline_go<T, 16>(pass, nt, c, tiles, inverse, lds, s);
 }
-template hipError_t launch_batch_rline<float>(int, int, const BatchClass<float>&, int, int, size_t, hipStream_t);
-template hipError_t launch_batch_rline<double>(int, int, const BatchClass<double>&, int, int, size_t, hipStream_t);
+template hipError_t launch_batch_rline<float>(int, int, int, const BatchClass<float>&, int, int, size_t, hipStream_t);
+template hipError_t launch_batch_rline<double>(int, int, int, const BatchClass<double>&, int, int, size_t, hipStream_t);
 
 }  // namespace mm

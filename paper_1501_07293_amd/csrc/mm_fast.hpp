@@ -176,8 +176,9 @@ __device__ inline void finish_line(cpx<T>* ln, int u, cpx<T>* v, const LineTw<T,
 template <typename T, int N>
 __device__ inline void fft_reg(cpx<T>* x, const cpx<T>* __restrict__ tw)
 {
-    constexpr int NS = Sched<N>::NS;
-    if constexpr (NS == 1) {
+    if constexpr ((N & (N - 1)) != 0) {
+        Dft<T, N>::run(x);  // lengths other than powers of two: one DFT
+    } else if constexpr (Sched<N>::NS == 1) {
         Dft<T, N>::run(x);
     } else {
         constexpr int R0 = Sched<N>::R0, R1 = Sched<N>::R1;

@@ -215,6 +215,152 @@ struct Dft<T, 7> {
     __device__ static inline void run(cpx<T>* v) { dft_odd<T, 7>(v); }
 };
 
+// ------------------------------------------------------- composite register DFTs
+// Coprime factors by the prime-factor map (no twiddles): with N = A B,
+// n = (B n1 + A n2) mod N, k = (B b k1 + A a k2) mod N, B b = 1 mod A, A a = 1 mod B.
+constexpr int inv_mod(int x, int m)
+{
+    for (int i = 1; i < m; ++i)
+        if (x * i % m == 1) return i;
+    return 1;
+}
+
+template <typename T, int A, int B>
+__device__ inline void dft_pfa(cpx<T>* v)
+{
+    constexpr int N = A * B;
+    cpx<T> a[B][A];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) a[n2][n1] = v[(B * n1 + A * n2) % N];
+        Dft<T, A>::run(a[n2]);
+    }
+    constexpr int e1 = B * inv_mod(B % A, A), e2 = A * inv_mod(A % B, B);
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+        cpx<T> b[B];
+#pragma unroll
+        for (int n2 = 0; n2 < B; ++n2) b[n2] = a[n2][k1];
+        Dft<T, B>::run(b);
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) v[(e1 * k1 + e2 * k2) % N] = b[k2];
+    }
+}
+
+template <typename T>
+struct Dft<T, 6> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 2, 3>(v); }
+};
+template <typename T>
+struct Dft<T, 10> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 2, 5>(v); }
+};
+template <typename T>
+struct Dft<T, 12> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 4, 3>(v); }
+};
+template <typename T>
+struct Dft<T, 14> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 2, 7>(v); }
+};
+template <typename T>
+struct Dft<T, 15> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 3, 5>(v); }
+};
+// 9 = 3 x 3 with the twiddles exp(-2 pi i n2 k1 / 9)
+template <typename T>
+struct Dft<T, 9> {
+    __device__ static inline void run(cpx<T>* v)
+    {
+        const cpx<T> w1 = {(T)0.76604444311897803520, (T)-0.64278760968653932632};
+        const cpx<T> w2 = {(T)0.17364817766693034885, (T)-0.98480775301220805937};
+        const cpx<T> w4 = {(T)-0.93969262078590838405, (T)-0.34202014332566873304};
+        cpx<T> a[3][3];
+#pragma unroll
+        for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+            for (int n1 = 0; n1 < 3; ++n1) a[n2][n1] = v[3 * n1 + n2];
+            Dft<T, 3>::run(a[n2]);
+        }
+        a[1][1] = cmul(a[1][1], w1);
+        a[1][2] = cmul(a[1][2], w2);
+        a[2][1] = cmul(a[2][1], w2);
+        a[2][2] = cmul(a[2][2], w4);
+#pragma unroll
+        for (int k1 = 0; k1 < 3; ++k1) {
+            cpx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
+            Dft<T, 3>::run(b);
+#pragma unroll
+            for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = b[k2];
+        }
+    }
+};
+template <typename T>
+struct Dft<T, 18> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 2, 9>(v); }
+};
+template <typename T>
+struct Dft<T, 20> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 4, 5>(v); }
+};
+template <typename T>
+struct Dft<T, 21> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 3, 7>(v); }
+};
+template <typename T>
+struct Dft<T, 24> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 8, 3>(v); }
+};
+template <typename T>
+struct Dft<T, 28> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 4, 7>(v); }
+};
+template <typename T>
+struct Dft<T, 30> {
+    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 2, 15>(v); }
+};
+// 25 = 5 x 5: exp(-2 pi i j / 25) for the products j = n2 k1, n2 and k1 in 1 .. 4
+template <typename T>
+__device__ inline cpx<T> w25(int j)
+{
+    switch (j) {
+    case 1: return {(T)0.96858316112863108, (T)-0.24868988716485479};
+    case 2: return {(T)0.87630668004386358, (T)-0.48175367410171532};
+    case 3: return {(T)0.72896862742141155, (T)-0.68454710592868862};
+    case 4: return {(T)0.53582679497899655, (T)-0.84432792550201508};
+    case 6: return {(T)0.062790519529313527, (T)-0.99802672842827156};
+    case 8: return {(T)-0.42577929156507272, (T)-0.90482705246601947};
+    case 9: return {(T)-0.63742398974868975, (T)-0.77051324277578925};
+    case 12: return {(T)-0.99211470131447776, (T)-0.12533323356430454};
+    default: return {(T)-0.63742398974868952, (T)0.77051324277578936};  // 16
+    }
+}
+template <typename T>
+struct Dft<T, 25> {
+    __device__ static inline void run(cpx<T>* v)
+    {
+        cpx<T> a[5][5];
+#pragma unroll
+        for (int n2 = 0; n2 < 5; ++n2) {
+#pragma unroll
+            for (int n1 = 0; n1 < 5; ++n1) a[n2][n1] = v[5 * n1 + n2];
+            Dft<T, 5>::run(a[n2]);
+        }
+#pragma unroll
+        for (int n2 = 1; n2 < 5; ++n2)
+#pragma unroll
+            for (int k1 = 1; k1 < 5; ++k1) a[n2][k1] = cmul(a[n2][k1], w25<T>(n2 * k1));
+#pragma unroll
+        for (int k1 = 0; k1 < 5; ++k1) {
+            cpx<T> b[5] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1], a[4][k1]};
+            Dft<T, 5>::run(b);
+#pragma unroll
+            for (int k2 = 0; k2 < 5; ++k2) v[k1 + 5 * k2] = b[k2];
+        }
+    }
+};
+
 // Radix schedule of the power-of-two lengths compiled per size: stage radices
 // R0, R1, R2 (NS stages), R0 >= the others so the first stage takes the most
 // points per thread.

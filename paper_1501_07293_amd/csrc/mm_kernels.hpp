@@ -270,6 +270,11 @@ bool launch_xline(const XLineArgs& a, int P, int inverse, hipStream_t s);
 template <typename T>
 bool launch_kspace_z(const KzArgs& a, int PZ, hipStream_t s);
 
+// The same for lengths other than powers of two, up to 30 points (one line in a thread's
+// registers); false for the others.
+template <typename T>
+bool launch_kspace_z_mixed(const KzArgs& a, int PZ, hipStream_t s);
+
 template <typename T>
 hipError_t launch_row_r2c(const RowR2CArgs& a, int nt, hipStream_t s);
 template <typename T>
@@ -451,6 +456,7 @@ template <typename T>
 hipError_t launch_normalize_vjp(const T* v, const T* gu, T* gv, int64_t N, hipStream_t s);
 
 // ---------------------------------------------------------------- batched
+constexpr int kBatchNT = 256;  // threads per work-group of a batch's passes
 // One grid of a batch (device-resident descriptor).  Offsets count elements
 // of the batch arrays: moff in the [3][N] vector arrays, soff in the complex
 // spectrum, koff in the real kernel octants, twx/twy/twz in the complex
@@ -481,7 +487,6 @@ struct BatchPass {
     const T* kern;
     const cpx<T>* tw;
 };
-constexpr int kBatchNT = 256;  // threads per work-group of a batch's passes
 // The grid whose tiles hold `tile`: prefix[lo] <= tile < prefix[lo + 1]; grids without
 // tiles are skipped.
 __device__ inline int find_sample(const int* prefix, int n, int tile)
@@ -542,11 +547,12 @@ int fast_ky_lines(int P);
 int fast_ky2_lines(int P);
 
 // The runtime-length register passes: one launch over the grids of class c, whose
-// radices are at most rmax (10 or 16); lds: the largest dynamic LDS a grid needs.
+// radices are at most rmax (10 or 16), nt (256 or 512) threads a work-group; lds: the
+// largest dynamic LDS a grid needs.
 enum { kRPassX = 0, kRPassY = 1, kRPassKz = 2, kRPassKy = 3, kRPassKy2 = 4, kRPasses = 5 };
 template <typename T>
-hipError_t launch_batch_rline(int pass, int rmax, const BatchClass<T>& c, int tiles, int inverse, size_t lds,
-                              hipStream_t s);
+hipError_t launch_batch_rline(int pass, int rmax, int nt, const BatchClass<T>& c, int tiles, int inverse,
+                              size_t lds, hipStream_t s);
 // m <- m / |m| over the cells of every grid of class c (tiles of kBatchNT cells); counts
 // zero-norm or non-finite cells into *bad.
 template <typename T>

@@ -23,88 +23,6 @@
 
 namespace mm {
 
-// ------------------------------------------------------- composite register DFTs
-// Coprime factors by the prime-factor map (no twiddles): with N = A B,
-// n = (B n1 + A n2) mod N, k = (B b k1 + A a k2) mod N, B b = 1 mod A, A a = 1 mod B.
-constexpr int inv_mod(int x, int m)
-{
-    for (int i = 1; i < m; ++i)
-        if (x * i % m == 1) return i;
-    return 1;
-}
-
-template <typename T, int A, int B>
-__device__ inline void dft_pfa(cpx<T>* v)
-{
-    constexpr int N = A * B;
-    cpx<T> a[B][A];
-#pragma unroll
-    for (int n2 = 0; n2 < B; ++n2) {
-#pragma unroll
-        for (int n1 = 0; n1 < A; ++n1) a[n2][n1] = v[(B * n1 + A * n2) % N];
-        Dft<T, A>::run(a[n2]);
-    }
-    constexpr int e1 = B * inv_mod(B % A, A), e2 = A * inv_mod(A % B, B);
-#pragma unroll
-    for (int k1 = 0; k1 < A; ++k1) {
-        cpx<T> b[B];
-#pragma unroll
-        for (int n2 = 0; n2 < B; ++n2) b[n2] = a[n2][k1];
-        Dft<T, B>::run(b);
-#pragma unroll
-        for (int k2 = 0; k2 < B; ++k2) v[(e1 * k1 + e2 * k2) % N] = b[k2];
-    }
-}
-
-template <typename T>
-struct Dft<T, 6> {
-    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 2, 3>(v); }
-};
-template <typename T>
-struct Dft<T, 10> {
-    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 2, 5>(v); }
-};
-template <typename T>
-struct Dft<T, 12> {
-    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 4, 3>(v); }
-};
-template <typename T>
-struct Dft<T, 14> {
-    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 2, 7>(v); }
-};
-template <typename T>
-struct Dft<T, 15> {
-    __device__ static inline void run(cpx<T>* v) { dft_pfa<T, 3, 5>(v); }
-};
-// 9 = 3 x 3 with the twiddles exp(-2 pi i n2 k1 / 9)
-template <typename T>
-struct Dft<T, 9> {
-    __device__ static inline void run(cpx<T>* v)
-    {
-        const cpx<T> w1 = {(T)0.76604444311897803520, (T)-0.64278760968653932632};
-        const cpx<T> w2 = {(T)0.17364817766693034885, (T)-0.98480775301220805937};
-        const cpx<T> w4 = {(T)-0.93969262078590838405, (T)-0.34202014332566873304};
-        cpx<T> a[3][3];
-#pragma unroll
-        for (int n2 = 0; n2 < 3; ++n2) {
-#pragma unroll
-            for (int n1 = 0; n1 < 3; ++n1) a[n2][n1] = v[3 * n1 + n2];
-            Dft<T, 3>::run(a[n2]);
-        }
-        a[1][1] = cmul(a[1][1], w1);
-        a[1][2] = cmul(a[1][2], w2);
-        a[2][1] = cmul(a[2][1], w2);
-        a[2][2] = cmul(a[2][2], w4);
-#pragma unroll
-        for (int k1 = 0; k1 < 3; ++k1) {
-            cpx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
-            Dft<T, 3>::run(b);
-#pragma unroll
-            for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = b[k2];
-        }
-    }
-};
-
 // ------------------------------------------------------------------ the line
 // LDS length of a line: odd, so that consecutive lines start on different banks.
 __host__ __device__ constexpr int rline_len(int P) { return P | 1; }

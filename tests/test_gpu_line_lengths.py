@@ -25,8 +25,8 @@ LENGTHS = [2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 15, 16,
 LONG = [2187, 2401, 3125, 4096, 6250]
 
 
-def demag_error(dims, pad, precision, **kw):
-    sim = mmag.Sim(*dims, CELL, Ku=500.0, precision=precision, pad=pad, generic_fft=True, **kw)
+def demag_error(dims, pad, precision, generic=True):
+    sim = mmag.Sim(*dims, CELL, Ku=500.0, precision=precision, pad=pad, generic_fft=generic)
     p = sim.plan()
     for k, v in zip(("px", "py", "pz"), pad):
         assert v == 0 or p[k] == v, p
@@ -65,11 +65,20 @@ def test_z_lines(P, precision):
 
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("P", [3, 5, 6, 7, 9, 10, 12, 14, 15, 18, 20, 21, 24, 25, 28, 30, 35])
+def test_z_lines_in_registers(P, precision):
+    # lines of one thread up to 30 points (35: the pass that exchanges through LDS), on
+    # planes too large for the fused y-z pass
+    n = (P + 1) // 2
+    assert demag_error((2, 700 // P + 2, n), (0, 0, P), precision, generic=False) <= TOL[precision]
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
 def test_batch_of_every_length_and_thickness(precision):
     # one handle over grids of 1 to 4 planes whose default padding takes one to four
     # stages along x and y; each grid's field against the direct sum
     grids = [(1, 1, 1), (2, 3, 1), (5, 8, 2), (25, 7, 1), (7, 32, 2), (43, 10, 1), (10, 61, 2), (92, 5, 1),
-             (5, 122, 2), (6, 9, 3), (30, 11, 4), (128, 3, 1), (3, 128, 2)]
+             (5, 122, 2), (5, 125, 2), (6, 9, 3), (30, 11, 4), (128, 3, 1), (3, 128, 2)]
     hext = np.zeros((len(grids), 3))
     b = mmag.BatchSim(grids, CELL, Ku=500.0, hext=hext, precision=precision)
     assert b.info()["size_classes"] == 0
