@@ -19,11 +19,14 @@ __global__ __launch_bounds__(L * (P / Sched<P>::R0)) void k_xfwd(XLineArgs a)
     body_xfwd<T, P, L, FULL>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
 }
 
+// C: the columns kzl_tile<T, P>() that share an XCD
 template <typename T, int P, int C>
-__global__ __launch_bounds__(3 * C * (P / Sched<P>::R0)) void k_kspace_zl(KzArgs a)
+__global__ __launch_bounds__((3 * kzl_cols<T, P>() * (P / Sched<P>::R0))) void k_kspace_zl(KzArgs a)
 {
-    __shared__ cpx<T> lds[3 * C * padded_len<P>()];
-    body_kspace_zl<T, P, C>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
+    constexpr int CW = kzl_cols<T, P>();
+    static_assert(C % CW == 0, "whole work-groups a tile");
+    __shared__ cpx<T> lds[3 * CW * padded_len<P>()];
+    body_kspace_zl<T, P, CW>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
 }
 
 template <typename T, int P, int L, bool FULL>
@@ -187,13 +190,17 @@ bool launch_kspace_z(const KzArgs& a, int PZ, hipStream_t s)
         return true;
     };
     if (PZ >= 128 && 2 * a.nz <= PZ) {
+        // one descriptor each for the spectrum and the octant
+        if (3 * a.comp_stride * 2 * (int64_t)sizeof(T) >= kRLineBytes ||
+            6 * a.k_cs * (int64_t)sizeof(T) >= kRLineBytes)
+            return false;
         switch (PZ) {
-        case 128: return zl(k_kspace_zl<T, 128, kzl_cols<T, 128>()>, kzl_cols<T, 128>(), 128 / Sched<128>::R0);
-        case 256: return zl(k_kspace_zl<T, 256, kzl_cols<T, 256>()>, kzl_cols<T, 256>(), 256 / Sched<256>::R0);
-        case 512: return zl(k_kspace_zl<T, 512, kzl_cols<T, 512>()>, kzl_cols<T, 512>(), 512 / Sched<512>::R0);
+        case 128: return zl(k_kspace_zl<T, 128, kzl_tile<T, 128>()>, kzl_cols<T, 128>(), 128 / Sched<128>::R0);
+        case 256: return zl(k_kspace_zl<T, 256, kzl_tile<T, 256>()>, kzl_cols<T, 256>(), 256 / Sched<256>::R0);
+        case 512: return zl(k_kspace_zl<T, 512, kzl_tile<T, 512>()>, kzl_cols<T, 512>(), 512 / Sched<512>::R0);
         case 1024:
             if constexpr (sizeof(T) == 4)
-                return zl(k_kspace_zl<T, 1024, kzl_cols<T, 1024>()>, kzl_cols<T, 1024>(), 1024 / Sched<1024>::R0);
+                return zl(k_kspace_zl<T, 1024, kzl_tile<T, 1024>()>, kzl_cols<T, 1024>(), 1024 / Sched<1024>::R0);
             return false;
         default: return false;
         }

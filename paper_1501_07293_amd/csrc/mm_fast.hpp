@@ -25,6 +25,7 @@
 // launchers pick it when 2n > P.  (The z pass keeps whole lines: pruned there
 // it measured slower.)
 #pragma once
+#include "mm_buf.hpp"
 #include "mm_fft.hpp"
 #include "mm_kernels.hpp"
 
@@ -502,16 +503,32 @@ __device__ inline void body_kspace_z(const KzArgs& a, int tile, cpx<T>* sh)
 // zero, the kept outputs are the first nz).  Lanes run column fastest, so each
 // load and store of one z point covers the C columns as one contiguous segment,
 // and the octant loads of the product run along ky.
-// Columns per work-group: as many as 1024 threads (3 C (P / R0)) and the LDS (3 C
-// padded lines) allow, up to 32: the segments are what the pass waits on (128^3
-// cube, Pz = 256, FP32: 8 columns 244 us per Euler step, 16 columns 209 us).  At
-// 1024 points at most 512 threads, whose 256 registers a thread hold the lines
-// without spilling (FP64 spills even so and keeps the LDS-staged pass).
+// Columns per work-group: eight, fewer where 384 threads (FP64 768) hold fewer.  A
+// work-group of 16 columns alone fills a CU, so loads, transforms and stores follow one
+// another; with eight, two work-groups overlap, and the 32-byte octant segments cost less
+// than that since each octant entry is loaded once for kz and P - kz.  Measured alone, us a
+// launch, one entry per frequency at the columns of before -> pairs at those -> pairs at
+// these: 128^3 cube (P = 256) FP32 16 columns 101 -> 89 -> 81 (8 columns; with an entry per
+// frequency 121); 64^3 FP32 32 columns 16.9 -> 11.9 with 8, FP64 16 columns 24.8 -> 18.9 with
+// 8; 256^3 FP32 4 columns 1428 -> 1203 with 2, FP64 2 columns 2628 but 2133 with 4; FP64
+// 128^3 235 with 4, 198 with 8.
+// Neighbouring work-groups run on one XCD (xcd_tile): kzl_tile columns, one 128-byte
+// segment per z point at FP32 and 256 points, are worked by kzl_tile / kzl_cols of them,
+// which find each other's half segments in its L2.
 template <typename T, int P>
-constexpr int kzl_cols()
+constexpr int kzl_tile()
 {
     constexpr int TL = P / Sched<P>::R0, MAXT = P >= 1024 ? 512 : 1024;
     int c = 32;
+    while (c > 1 && (3 * c * TL > MAXT || 3 * c * padded_len<P>() * (int)sizeof(cpx<T>) > kLdsBudget)) c /= 2;
+    return c;
+}
+
+template <typename T, int P>
+constexpr int kzl_cols()
+{
+    constexpr int TL = P / Sched<P>::R0, MAXT = sizeof(T) == 8 ? 768 : 384;
+    int c = 8;
     while (c > 1 && (3 * c * TL > MAXT || 3 * c * padded_len<P>() * (int)sizeof(cpx<T>) > kLdsBudget)) c /= 2;
     return c;
 }
@@ -525,49 +542,48 @@ __device__ inline void body_kspace_zl(const KzArgs& a, int tile, cpx<T>* lds)
     const int l = t % C, u = (t / C) % TL, comp = t / (C * TL);
     const int col = tile * C + l;
     const bool ok = col < a.ncols;
-    const int64_t zs = a.ncols;
-    cpx<T>* g = (cpx<T>*)a.buf + comp * a.comp_stride + (ok ? col : 0);
+    // 32-bit byte offsets from one descriptor, the steps along z and over the octant's
+    // components in scalar registers
+    constexpr unsigned CS = sizeof(cpx<T>), TS = sizeof(T);
+    const Buf g = buf_of(a.buf), K = buf_of(a.kern);
+    const unsigned zs = (unsigned)a.ncols * CS;  // bytes from one z point to the next
+    const unsigned at = ((unsigned)comp * (unsigned)a.comp_stride + (unsigned)col) * CS + (unsigned)u * zs;
     cpx<T>* ln = lds + (comp * C + l) * LP;
     LineTw<T, P> W;
     W.load(u, (const cpx<T>*)a.tw);
+    const int nz = ok ? a.nz : 0;
     cpx<T> v[R0];
 #pragma unroll
     for (int r = 0; r < R0; ++r) {
-        const int e = u + TL * r;
         cpx<T> x = {(T)0, (T)0};
-        if (2 * r < R0 && ok && e < a.nz) x = g[e * zs];  // e >= P/2 is zero padding
+        if (2 * r < R0)  // e >= P/2 is zero padding
+            x = buf_ld<cpx<T>>(g, u + TL * r < nz ? at : kBufNone, (unsigned)(TL * r) * zs);
         v[r] = x;
     }
-    // Eq. 14 spectra of the product elements this thread takes (element idx: column
-    // idx % C, kz = idx / C), loaded with the data so their latency overlaps the
-    // forward transform; negative frequencies mirror with the component parities
-    // (xy odd in y, xz odd in z, yz odd in y and z)
-    constexpr int NI = (C * P + NT - 1) / NT;
-    const T* K = (const T*)a.kern;
+    // Eq. 14 spectra of the frequency pairs this thread takes (pair idx: column idx % C,
+    // kz = idx / C and P - kz, which share one octant entry), loaded with the data so their
+    // latency overlaps the forward transform; negative frequencies mirror with the
+    // component parities (xy odd in y, xz odd in z, yz odd in y and z)
+    constexpr int H = P / 2, NI = (C * (H + 1) + NT - 1) / NT;
+    const unsigned kcs = (unsigned)a.k_cs * TS;
     T kv[NI][6];
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
         const int idx = t + it * NT;
-        const int l2 = idx % C, e = idx / C, col2 = tile * C + l2;
-        const bool in = idx < C * P && col2 < a.ncols;
-        const int cc = in ? col2 : 0;
-        const int kx = cc / a.Py;
-        int ky = cc - kx * a.Py, kz = e;
-        T sy = (T)1, sz = (T)1;
+        const int l2 = idx % C, kz = idx / C, col2 = tile * C + l2;
+        const bool in = kz <= H && col2 < a.ncols;
+        const int kx = col2 / a.Py;
+        int ky = col2 - kx * a.Py;
+        T sy = (T)1;
         if (2 * ky > a.Py) {
             ky = a.Py - ky;
             sy = (T)-1;
         }
-        if (2 * kz > P) {
-            kz = P - kz;
-            sz = (T)-1;
-        }
-        const T* Kp = K + (in ? kz * a.k_zs + kx * a.k_xs + ky : 0);
+        const unsigned ko = ((unsigned)kz * (unsigned)a.k_zs + (unsigned)kx * (unsigned)a.k_xs + (unsigned)ky) * TS;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) kv[it][c] = Kp[c * a.k_cs];
+        for (int c = 0; c < 6; ++c) kv[it][c] = buf_ld<T>(K, in ? ko : kBufNone, (unsigned)c * kcs);
         kv[it][1] *= sy;
-        kv[it][2] *= sz;
-        kv[it][4] *= sy * sz;
+        kv[it][4] *= sy;
     }
     Dft<T, R0>::run(v);
     finish_line<T, P>(ln, u, v, W, [&](int e, cpx<T> val) { ln[pad16(e)] = val; });
@@ -575,17 +591,21 @@ __device__ inline void body_kspace_zl(const KzArgs& a, int tile, cpx<T>* lds)
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
         const int idx = t + it * NT;
-        const int l2 = idx % C, e = idx / C;
-        if (idx >= C * P || tile * C + l2 >= a.ncols) continue;
-        const T kxx = kv[it][0], kxy = kv[it][1], kxz = kv[it][2], kyy = kv[it][3], kyz = kv[it][4],
-                kzz = kv[it][5];
-        cpx<T>* px = lds + (0 * C + l2) * LP + pad16(e);
-        cpx<T>* py = lds + (1 * C + l2) * LP + pad16(e);
-        cpx<T>* pz = lds + (2 * C + l2) * LP + pad16(e);
-        const cpx<T> mx = *px, my = *py, mz = *pz;
-        *px = conj(cpx<T>{kxx * mx.re + kxy * my.re + kxz * mz.re, kxx * mx.im + kxy * my.im + kxz * mz.im});
-        *py = conj(cpx<T>{kxy * mx.re + kyy * my.re + kyz * mz.re, kxy * mx.im + kyy * my.im + kyz * mz.im});
-        *pz = conj(cpx<T>{kxz * mx.re + kyz * my.re + kzz * mz.re, kxz * mx.im + kyz * my.im + kzz * mz.im});
+        const int l2 = idx % C, kz = idx / C;
+        if (kz > H || tile * C + l2 >= a.ncols) continue;
+        auto product = [&](int e, T kxx, T kxy, T kxz, T kyy, T kyz, T kzz) {
+            cpx<T>* px = lds + (0 * C + l2) * LP + pad16(e);
+            cpx<T>* py = lds + (1 * C + l2) * LP + pad16(e);
+            cpx<T>* pz = lds + (2 * C + l2) * LP + pad16(e);
+            const cpx<T> mx = *px, my = *py, mz = *pz;
+            *px = conj(cpx<T>{kxx * mx.re + kxy * my.re + kxz * mz.re, kxx * mx.im + kxy * my.im + kxz * mz.im});
+            *py = conj(cpx<T>{kxy * mx.re + kyy * my.re + kyz * mz.re, kxy * mx.im + kyy * my.im + kyz * mz.im});
+            *pz = conj(cpx<T>{kxz * mx.re + kyz * my.re + kzz * mz.re, kxz * mx.im + kyz * my.im + kzz * mz.im});
+        };
+        const T* k = kv[it];
+        product(kz, k[0], k[1], k[2], k[3], k[4], k[5]);
+        // the mirrored point P - kz: xz and yz odd in z
+        if (kz > 0 && kz < H) product(P - kz, k[0], k[1], -k[2], k[3], -k[4], k[5]);
     }
     __syncthreads();
 #pragma unroll
@@ -593,7 +613,8 @@ __device__ inline void body_kspace_zl(const KzArgs& a, int tile, cpx<T>* lds)
     Dft<T, R0>::run(v);
     __syncthreads();  // stage-1 reads of every line are done before LDS is rewritten
     finish_line<T, P, true>(ln, u, v, W, [&](int e, cpx<T> val) {
-        if (ok && e < a.nz) g[e * zs] = conj(val);  // inverse by conjugation
+        // inverse by conjugation; e - u is a constant of the unrolled stage
+        buf_st(g, e < nz ? at : kBufNone, conj(val), (unsigned)(e - u) * zs);
     });
 }
 
