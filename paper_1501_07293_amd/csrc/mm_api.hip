@@ -631,7 +631,7 @@ hipError_t pass_kspace(const PassCtx& c, hipStream_t st)
         if (c.fast && launch_kspace_y<T>(ky, p.Py, st)) return hipGetLastError();
         if (p.rs.ky > 0) {
             const RKyArgs ra{c.S, c.plane, c.Sy, p.hx, p.ny, stage_tw(p, c.twy, p.Py), c.kern, p.oct_elems, k_xs,
-                             p.rs.ky, div_mul(p.Py)};
+                             p.rs.ky, div_mul(p.Py / 2 + 1)};
             return launch_rky<T>(ra, p.ly, st);
         }
         k.comp_stride = c.plane;
@@ -1844,7 +1844,7 @@ mm_status batch_layout_plans(int32_t n, const mm_grid* grids, const mm_options* 
         d.ly = p.ly;
         d.lz = p.lz;
         d.rs = batch_shapes(p);
-        d.pymul = div_mul(p.Py);
+        d.pymul = div_mul(p.Py / 2 + 1);
         L->vec_elems += 3 * p.N;
         L->S_elems += 3 * (int64_t)p.nz * p.hx * p.S_rows;
         L->kern_elems += (int64_t)p.kplanes * p.oct_elems;

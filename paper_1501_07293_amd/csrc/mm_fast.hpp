@@ -716,6 +716,25 @@ __device__ inline void body_kspace_z_split(const KzArgs& a, int tile, cpx<T>* sh
     }
 }
 
+// Eq. 14 for a frequency pair ky, P - ky of a one-cell-thick grid: the components at q and
+// at its mirror q2, stride apart, times xx, xy, yy, zz (xy odd in ky), stored conjugated
+// (the inverse transform runs as a forward one).  Both points are read before either is
+// written; where ky is its own mirror, q2 = q and only q is written.
+template <typename T>
+__device__ inline void thin_product(cpx<T>* q, cpx<T>* q2, bool mirror, int stride, T xx, T xy, T yy, T zz)
+{
+    const cpx<T> mx = q[0], my = q[stride], mz = q[2 * stride];
+    const cpx<T> nx = q2[0], ny = q2[stride], nz = q2[2 * stride];
+    q[0] = conj(cpx<T>{xx * mx.re + xy * my.re, xx * mx.im + xy * my.im});
+    q[stride] = conj(cpx<T>{xy * mx.re + yy * my.re, xy * mx.im + yy * my.im});
+    q[2 * stride] = conj(cpx<T>{zz * mz.re, zz * mz.im});
+    if (mirror) {
+        q2[0] = conj(cpx<T>{xx * nx.re - xy * ny.re, xx * nx.im - xy * ny.im});
+        q2[stride] = conj(cpx<T>{yy * ny.re - xy * nx.re, yy * ny.im - xy * nx.im});
+        q2[2 * stride] = conj(cpx<T>{zz * nz.re, zz * nz.im});
+    }
+}
+
 // ------------------------------------------------------------ y k-space (2-D)
 // One-cell-thick grids: the k-space pass runs along y.  A work-group holds L
 // x-bins, three component lines each: forward FFT (stage 1 from global memory),
@@ -746,18 +765,17 @@ __device__ inline void body_kspace_y(const KyArgs& a, int tile, cpx<T>* lds)
         if ((FULL || 2 * r < R0) && ok && e < a.ny) x = g[e];  // e >= P/2 is zero padding
         v[r] = x;
     }
-    // the spectra of the product elements this thread takes do not depend on the
-    // data: loaded here, their latency overlaps the forward transform
-    constexpr int NI = (L * P + NT - 1) / NT;
+    // the spectra of the frequency pairs ky, P - ky this thread takes (they share one
+    // entry) do not depend on the data: loaded here, their latency overlaps the forward
+    // transform
+    constexpr int H1 = P / 2 + 1, NI = (L * H1 + NT - 1) / NT;
     const T* K = (const T*)a.kern;
     T kv[NI][4];
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
         const int idx = (int)threadIdx.x + it * NT;
-        const int l2 = idx / P, e = idx - l2 * P, kx2 = tile * L + l2;
-        int ky = e;
-        if (2 * ky > P) ky = P - ky;
-        const bool in = idx < L * P && kx2 < a.hx;
+        const int l2 = idx / H1, ky = idx - l2 * H1, kx2 = tile * L + l2;
+        const bool in = idx < L * H1 && kx2 < a.hx;
         const T* Kp = K + (in ? (int64_t)kx2 * a.k_xs + ky : 0);
 #pragma unroll
         for (int c = 0; c < 4; ++c) kv[it][c] = Kp[c * a.k_cs];
@@ -773,17 +791,12 @@ __device__ inline void body_kspace_y(const KyArgs& a, int tile, cpx<T>* lds)
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
         const int idx = (int)threadIdx.x + it * NT;
-        const int l2 = idx / P, e = idx - l2 * P, kx2 = tile * L + l2;
-        if (idx >= L * P || kx2 >= a.hx) continue;
-        const T sy = 2 * e > P ? (T)-1 : (T)1;
-        const T kxx = kv[it][0], kxy = sy * kv[it][1], kyy = kv[it][2], kzz = kv[it][3];
-        cpx<T>* px = lds + (0 * L + l2) * LP + pad16(e);
-        cpx<T>* py = lds + (1 * L + l2) * LP + pad16(e);
-        cpx<T>* pz = lds + (2 * L + l2) * LP + pad16(e);
-        const cpx<T> mx = *px, my = *py, mz = *pz;
-        *px = conj(cpx<T>{kxx * mx.re + kxy * my.re, kxx * mx.im + kxy * my.im});
-        *py = conj(cpx<T>{kxy * mx.re + kyy * my.re, kxy * mx.im + kyy * my.im});
-        *pz = conj(cpx<T>{kzz * mz.re, kzz * mz.im});
+        const int l2 = idx / H1, ky = idx - l2 * H1, kx2 = tile * L + l2;
+        if (idx >= L * H1 || kx2 >= a.hx) continue;
+        cpx<T>* q = lds + l2 * LP;
+        const bool mirror = ky > 0 && ky < P / 2;
+        thin_product(q + pad16(ky), q + pad16(mirror ? P - ky : ky), mirror, L * LP, kv[it][0], kv[it][1], kv[it][2],
+                     kv[it][3]);
     }
     __syncthreads();
 #pragma unroll
@@ -872,18 +885,16 @@ __device__ inline void body_kspace_y2(const Ky2Args& a, int tile, cpx<T>* lds)
         if ((FULL || 2 * r < R0) && ok && e < a.ny) x = g[e];  // e >= P/2 is zero padding
         v[r] = x;
     }
-    // the coefficients of this thread's product elements, loaded with the data
-    constexpr int NI = (L * P + NT - 1) / NT;
+    // the coefficients of this thread's frequency pairs ky, P - ky, loaded with the data
+    constexpr int H1 = P / 2 + 1, NI = (L * H1 + NT - 1) / NT;
     const T* K = (const T*)a.kern;
     const int64_t cs = a.k_cs;
     T kv[NI][kTwoPlaneTablePlanes];
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
         const int idx = (int)threadIdx.x + it * NT;
-        const int l2 = idx / P, e = idx - l2 * P, kx2 = tile * L + l2;
-        int ky = e;
-        if (2 * ky > P) ky = P - ky;
-        const bool in = idx < L * P && kx2 < a.hx;
+        const int l2 = idx / H1, ky = idx - l2 * H1, kx2 = tile * L + l2;
+        const bool in = idx < L * H1 && kx2 < a.hx;
         const T* Kp = K + (in ? (int64_t)kx2 * a.k_xs + ky : 0);
 #pragma unroll
         for (int c = 0; c < kTwoPlaneTablePlanes; ++c) kv[it][c] = Kp[c * cs];
@@ -899,10 +910,11 @@ __device__ inline void body_kspace_y2(const Ky2Args& a, int tile, cpx<T>* lds)
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
         const int idx = (int)threadIdx.x + it * NT;
-        const int l2 = idx / P, e = idx - l2 * P, kx2 = tile * L + l2;
-        if (idx >= L * P || kx2 >= a.hx) continue;
-        const T sy = 2 * e > P ? (T)-1 : (T)1;
-        two_plane_product<T>(lds + l2 * LP + pad16(e), L * LP, sy, kv[it]);
+        const int l2 = idx / H1, ky = idx - l2 * H1, kx2 = tile * L + l2;
+        if (idx >= L * H1 || kx2 >= a.hx) continue;
+        cpx<T>* q = lds + l2 * LP;
+        two_plane_product<T>(q + pad16(ky), L * LP, (T)1, kv[it]);
+        if (ky > 0 && ky < P / 2) two_plane_product<T>(q + pad16(P - ky), L * LP, (T)-1, kv[it]);
     }
     __syncthreads();
 #pragma unroll

@@ -138,7 +138,7 @@ struct RKyArgs {             // y k-space pass of a one-cell-thick grid, lines (
     const void* kern;        // octant [4][1][hx][Py/2+1]: xx, xy, yy, zz
     int64_t k_cs, k_xs;
     int L;                   // x bins per work-group
-    unsigned dmul;           // divides by Py
+    unsigned dmul;           // divides by Py / 2 + 1
 };
 struct RKy2Args {            // y k-space pass of a two-cell-thick grid (see Ky2Args)
     void* buf;
@@ -148,7 +148,7 @@ struct RKy2Args {            // y k-space pass of a two-cell-thick grid (see Ky2
     const void* kern;
     int64_t k_cs, k_xs;
     int L;                   // x bins per work-group
-    unsigned dmul;           // divides by Py
+    unsigned dmul;           // divides by Py / 2 + 1
 };
 struct RYzArgs {             // y forward, z k-space and y inverse of one x bin in LDS
     void* buf;
@@ -474,7 +474,7 @@ struct BatchDesc {
     FftPlan fx, fy, fz;
     LinePlan lx, ly, lz;  // the runtime-length register passes' schedules and shapes
     RShape rs;
-    unsigned pymul;       // divides by Py
+    unsigned pymul;       // divides by Py / 2 + 1
 };
 template <typename T>
 struct BatchPass {

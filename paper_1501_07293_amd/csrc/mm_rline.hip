@@ -187,8 +187,9 @@ RShape rline_shapes(const LinePlan& x, const LinePlan& y, const LinePlan& z, int
             return (3 * z.TL << q) <= max_threads && rline_lds_bytes(3 << q, z.P, esz) <= kRLdsBudget;
         };
         while (c > 0 && (!fits(c) || ((3 * z.TL << c) > 256 && c > 4))) --c;
-        // the pass addresses the whole spectrum from one descriptor
-        if (fits(c) && 3 * nz * ncols * 2 * (int64_t)esz < kBufEnd) r.csh = c;
+        // the pass addresses the whole spectrum from one descriptor, and the octant from another
+        const int64_t oct = 6 * (int64_t)(z.P / 2 + 1) * (x.P / 2 + 1) * (y.P / 2 + 1) * (int64_t)esz;
+        if (fits(c) && 3 * nz * ncols * 2 * (int64_t)esz < kBufEnd && oct < kBufEnd) r.csh = c;
     }
     if (y.ns > 0 && z.ns > 0 && nz > 1 && y.TL <= kRMaxThreads && z.TL <= kRMaxThreads &&
         ryz_lds_bytes(y.P, z.P, esz) <= kLdsBudget &&

@@ -351,8 +351,9 @@ __device__ inline void tensor_product(cpx<T>* px, cpx<T>* py, cpx<T>* pz, const 
     *pz = conj(cpx<T>{k[2] * mx.re + k[4] * my.re + k[5] * mz.re, k[2] * mx.im + k[4] * my.im + k[5] * mz.im});
 }
 
-// Product elements a thread takes: C P of them over at least 3 C P / R threads, R <= 16.
-constexpr int kRzProduct = 6;
+// Frequency pairs k, P - k a thread takes (they share one octant entry up to the parities):
+// C (P / 2 + 1) of them over at least 3 C P / R threads, R <= 16 and R <= P.
+constexpr int kRzProduct = 3;
 
 // Along z (3-D grids): C = 1 << a.csh adjacent columns (kx, ky), three component lines
 // each; lanes run column-fastest, so a load or store of one z point is one segment of C
@@ -373,24 +374,23 @@ __device__ inline void body_rkz(const RKzArgs& a, const LinePlan& pl, int tile, 
     const Buf g = buf_of(a.buf);
     const unsigned zs = (unsigned)a.ncols * CS, at = ((unsigned)comp * (unsigned)a.comp_stride + (unsigned)col) * CS;
     cpx<T>* ln = lds + (comp * C + l) * LP;
-    const T* K = (const T*)a.kern;
+    constexpr unsigned TS = sizeof(T);
+    const Buf K = buf_of(a.kern);
     T kv[kRzProduct][6];
 #pragma unroll
     for (int it = 0; it < kRzProduct; ++it) {
         const int idx = t + it * NT;
-        const int l2 = idx & (C - 1), e = idx >> a.csh, col2 = tile * C + l2;
+        const int l2 = idx & (C - 1), kz = idx >> a.csh, col2 = tile * C + l2;
+        const int kx = col2 / a.Py;
+        int ky = col2 - kx * a.Py;
+        const T sy = 2 * ky > a.Py ? (T)-1 : (T)1;
+        if (2 * ky > a.Py) ky = a.Py - ky;
+        const bool in = 2 * kz <= P && col2 < a.ncols;
+        const unsigned ko = ((unsigned)kz * (unsigned)a.k_zs + (unsigned)kx * (unsigned)a.k_xs + (unsigned)ky) * TS;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) kv[it][c] = (T)0;
-        if (e < P && col2 < a.ncols) {
-            const int kx = col2 / a.Py;
-            int ky = col2 - kx * a.Py, kz = e;
-            const bool my = 2 * ky > a.Py, mz = 2 * kz > P;
-            if (my) ky = a.Py - ky;
-            if (mz) kz = P - kz;
-            const T* Kp = K + kz * a.k_zs + kx * a.k_xs + ky;
-#pragma unroll
-            for (int c = 0; c < 6; ++c) kv[it][c] = Kp[c * a.k_cs];
-        }
+        for (int c = 0; c < 6; ++c) kv[it][c] = buf_ld<T>(K, in ? ko : kBufNone, (unsigned)c * (unsigned)a.k_cs * TS);
+        kv[it][1] *= sy;  // mirrored ky: xy and yz odd in y
+        kv[it][4] *= sy;
     }
     const int nz = ok ? a.nz : 0;
     rline_fft<T, RM, false, true>(
@@ -401,14 +401,16 @@ __device__ inline void body_rkz(const RKzArgs& a, const LinePlan& pl, int tile, 
 #pragma unroll
     for (int it = 0; it < kRzProduct; ++it) {
         const int idx = t + it * NT;
-        const int l2 = idx & (C - 1), e = idx >> a.csh, col2 = tile * C + l2;
-        if (e < P && col2 < a.ncols) {
-            // mirrored frequencies: xy odd in y, xz odd in z, yz odd in both
-            const int kx = col2 / a.Py, ky = col2 - kx * a.Py;
-            const T sy = 2 * ky > a.Py ? (T)-1 : (T)1, sz = 2 * e > P ? (T)-1 : (T)1;
-            const T k[6] = {kv[it][0], sy * kv[it][1], sz * kv[it][2], kv[it][3], sy * sz * kv[it][4], kv[it][5]};
-            cpx<T>* q = lds + l2 * LP + e;
-            tensor_product(q, q + C * LP, q + 2 * C * LP, k);
+        const int l2 = idx & (C - 1), kz = idx >> a.csh;
+        if (2 * kz <= P && tile * C + l2 < a.ncols) {
+            const T(&k)[6] = kv[it];
+            cpx<T>* q = lds + l2 * LP;
+            tensor_product(q + kz, q + C * LP + kz, q + 2 * C * LP + kz, k);
+            if (kz > 0 && 2 * kz < P) {  // the mirrored point: xz and yz odd in z
+                const T m[6] = {k[0], k[1], -k[2], k[3], -k[4], k[5]};
+                q += P - kz;
+                tensor_product(q, q + C * LP, q + 2 * C * LP, m);
+            }
         }
     }
     __syncthreads();
@@ -432,19 +434,18 @@ __device__ inline void body_rky(const RKyArgs& a, const LinePlan& pl, int tile, 
     const Buf g = buf_of(a.buf);
     const unsigned at = ((unsigned)comp * (unsigned)a.comp_stride + (unsigned)kx * (unsigned)a.line_stride) * CS;
     cpx<T>* ln = lds + w.l * LP;
-    const T* K = (const T*)a.kern;
+    constexpr unsigned TS = sizeof(T);
+    const Buf K = buf_of(a.kern);
+    const int H1 = P / 2 + 1;
     T kv[kRzProduct][4];
 #pragma unroll
     for (int it = 0; it < kRzProduct; ++it) {
         const int idx = t + it * NT;
-        const int l2 = div_by(idx, a.dmul), e = idx - l2 * P, kx2 = tile * L + l2;
+        const int l2 = div_by(idx, a.dmul), ky = idx - l2 * H1, kx2 = tile * L + l2;
+        const unsigned ko = ((unsigned)kx2 * (unsigned)a.k_xs + (unsigned)ky) * TS;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) kv[it][c] = (T)0;
-        if (l2 < L && kx2 < a.hx) {
-            const T* Kp = K + (int64_t)kx2 * a.k_xs + (2 * e > P ? P - e : e);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) kv[it][c] = Kp[c * a.k_cs];
-        }
+        for (int c = 0; c < 4; ++c)
+            kv[it][c] = buf_ld<T>(K, l2 < L && kx2 < a.hx ? ko : kBufNone, (unsigned)c * (unsigned)a.k_cs * TS);
     }
     const int ny = ok ? a.ny : 0;
     rline_fft<T, RM, false, true>(
@@ -455,16 +456,11 @@ __device__ inline void body_rky(const RKyArgs& a, const LinePlan& pl, int tile, 
 #pragma unroll
     for (int it = 0; it < kRzProduct; ++it) {
         const int idx = t + it * NT;
-        const int l2 = div_by(idx, a.dmul), e = idx - l2 * P;
+        const int l2 = div_by(idx, a.dmul), ky = idx - l2 * H1;
         if (l2 < L && tile * L + l2 < a.hx) {
-            const T sy = 2 * e > P ? (T)-1 : (T)1;
-            cpx<T>* qx = lds + l2 * LP + e;
-            cpx<T>*qy = qx + L * LP, *qz = qy + L * LP;
-            const cpx<T> mx = *qx, my = *qy, mz = *qz;
-            const T kxx = kv[it][0], kxy = sy * kv[it][1], kyy = kv[it][2], kzz = kv[it][3];
-            *qx = conj(cpx<T>{kxx * mx.re + kxy * my.re, kxx * mx.im + kxy * my.im});
-            *qy = conj(cpx<T>{kxy * mx.re + kyy * my.re, kxy * mx.im + kyy * my.im});
-            *qz = conj(cpx<T>{kzz * mz.re, kzz * mz.im});
+            cpx<T>* q = lds + l2 * LP;
+            const bool mirror = ky > 0 && 2 * ky < P;
+            thin_product(q + ky, q + (mirror ? P - ky : ky), mirror, L * LP, kv[it][0], kv[it][1], kv[it][2], kv[it][3]);
         }
     }
     __syncthreads();
@@ -474,9 +470,9 @@ __device__ inline void body_rky(const RKyArgs& a, const LinePlan& pl, int tile, 
 }
 
 // Along y on grids two cells thick, the z coupling taken directly (Ky2Args): L x bins,
-// six lines each (component, plane).  The product elements a thread takes: L P over at
-// least 6 L P / R threads.
-constexpr int kRy2Product = 3;
+// six lines each (component, plane).  The frequency pairs a thread takes: L (P / 2 + 1) over
+// at least 6 L P / R threads.
+constexpr int kRy2Product = 2;
 
 template <typename T, int RM>
 __device__ inline void body_rky2(const RKy2Args& a, const LinePlan& pl, int tile, cpx<T>* lds)
@@ -492,16 +488,18 @@ __device__ inline void body_rky2(const RKy2Args& a, const LinePlan& pl, int tile
     const unsigned at = ((unsigned)(cz >> 1) * (unsigned)a.comp_stride + (unsigned)(cz & 1) * (unsigned)a.plane_stride +
                          (unsigned)kx * (unsigned)a.line_stride) * CS;
     cpx<T>* ln = lds + w.l * LP;
-    const T* K = (const T*)a.kern;
+    constexpr unsigned TS = sizeof(T);
+    const Buf K = buf_of(a.kern);
+    const int H1 = P / 2 + 1;
     T kv[kRy2Product][kTwoPlaneTablePlanes];
 #pragma unroll
     for (int it = 0; it < kRy2Product; ++it) {
         const int idx = t + it * NT;
-        const int l2 = div_by(idx, a.dmul), e = idx - l2 * P, kx2 = tile * L + l2;
-        const bool in = l2 < L && kx2 < a.hx;
-        const T* Kp = K + (in ? (int64_t)kx2 * a.k_xs + (2 * e > P ? P - e : e) : 0);
+        const int l2 = div_by(idx, a.dmul), ky = idx - l2 * H1, kx2 = tile * L + l2;
+        const unsigned ko = ((unsigned)kx2 * (unsigned)a.k_xs + (unsigned)ky) * TS;
 #pragma unroll
-        for (int c = 0; c < kTwoPlaneTablePlanes; ++c) kv[it][c] = Kp[c * a.k_cs];
+        for (int c = 0; c < kTwoPlaneTablePlanes; ++c)
+            kv[it][c] = buf_ld<T>(K, l2 < L && kx2 < a.hx ? ko : kBufNone, (unsigned)c * (unsigned)a.k_cs * TS);
     }
     const int ny = ok ? a.ny : 0;
     rline_fft<T, RM, false, true>(
@@ -512,8 +510,12 @@ __device__ inline void body_rky2(const RKy2Args& a, const LinePlan& pl, int tile
 #pragma unroll
     for (int it = 0; it < kRy2Product; ++it) {
         const int idx = t + it * NT;
-        const int l2 = div_by(idx, a.dmul), e = idx - l2 * P;
-        if (l2 < L && tile * L + l2 < a.hx) two_plane_product<T>(lds + l2 * LP + e, L * LP, 2 * e > P ? (T)-1 : (T)1, kv[it]);
+        const int l2 = div_by(idx, a.dmul), ky = idx - l2 * H1;
+        if (l2 < L && tile * L + l2 < a.hx) {
+            cpx<T>* q = lds + l2 * LP;
+            two_plane_product<T>(q + ky, L * LP, (T)1, kv[it]);
+            if (ky > 0 && 2 * ky < P) two_plane_product<T>(q + P - ky, L * LP, (T)-1, kv[it]);
+        }
     }
     __syncthreads();
     rline_fft<T, RM, true, false>(
