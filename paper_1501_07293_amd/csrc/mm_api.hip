@@ -126,6 +126,7 @@ struct Plan {
     int64_t S_planes, S_rows;  // spectrum [3][S_planes][hx][S_rows]
     int per;                   // periodic axes: bit 0 x, bit 1 y, bit 2 z
     bool yz;                   // 3-D: the fused y-z pass replaces y forward, z k-space, y inverse
+    int plane_nt, plane_lines; // threads of the plane pass (0: not used), its y lines a round
     bool yz_small;             // and takes their place by itself on small planes (not MM_FUSED_YZ)
     bool wg1;                  // one work-group runs the whole demag evaluation (small grids)
     int images;                // images on each side beyond the nearest (periodic axes)
@@ -309,7 +310,10 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_pl
     p->zd = p->nz == 2 && p->Pz == 4 && !(p->per & 4) && !p->yz && !p->wg1 && p->ny <= p->Py &&
             ((!(o->flags & MM_GENERIC_FFT) && fast_ky2_lines(p->Py) > 0 && !(p->esz == 8 && p->Py > 1024)) ||
              (two_plane && batch_shapes(*p).ky2 > 0));
-    p->yz_small = p->three_d && !p->yz && !p->zd && !p->wg1 && p->rs.yz > 0 && yz_is_small(*p, (o->flags & MM_GENERIC_FFT) != 0);
+    p->plane_nt = 0;
+    if (p->three_d && !p->yz && !p->zd && !p->wg1 && !(o->flags & MM_GENERIC_FFT))
+        p->plane_nt = plane_threads(p->ly, p->Pz, p->hx, p->nz, p->esz, &p->plane_lines);
+    p->yz_small = p->three_d && p->plane_nt == 0 && !p->yz && !p->zd && !p->wg1 && p->rs.yz > 0 && yz_is_small(*p, (o->flags & MM_GENERIC_FFT) != 0);
     // open, small (latency-bound), with the specialised passes: the fused stage pass
     // (the y / z passes of one-cell-thick and thicker grids run between its launches)
     p->fs_lines = 0;
@@ -704,6 +708,16 @@ hipError_t pass_kspace_yz(const PassCtx& c, hipStream_t st)
 }
 
 template <typename T>
+hipError_t pass_plane(const PassCtx& c, hipStream_t st)
+{
+    const Plan& p = c.p;
+    const RYzArgs a{c.S, (int64_t)p.nz * c.plane, c.plane, (int)c.Sy, p.hx, p.ny, p.nz, stage_tw(p, c.twy, p.Py), nullptr,
+                    c.kern, p.oct_elems, (int64_t)p.hx * (p.Py / 2 + 1), p.Py / 2 + 1, p.plane_nt, p.plane_lines,
+                    div_mul(p.nz), 0};
+    return launch_plane<T>(a, p.ly, p.Pz, st);
+}
+
+template <typename T>
 hipError_t pass_kspace_y2(const PassCtx& c, hipStream_t st)
 {
     const Plan& p = c.p;
@@ -741,13 +755,17 @@ hipError_t pass_demag_1wg(const PassCtx& c, const T* m, T* hd, hipStream_t st)
 }
 
 // The passes between the x forward and the x inverse of one demag evaluation, in
-// place on c.S: the two-plane y pass, the fused y-z pass, or y forward, the k-space pass
+// place on c.S: the two-plane y pass, the plane pass, the fused y-z pass, or y forward, the k-space pass
 // (along z, or along y on one-cell-thick grids) and y inverse.
 template <typename T>
 mm_status demag_mid(mm_sim* s, const PassCtx& c, hipStream_t st)
 {
     if (c.p.zd) {
         LAUNCH(KSPACE, pass_kspace_y2<T>(c, st));
+        return MM_OK;
+    }
+    if (c.p.plane_nt > 0) {
+        LAUNCH(KSPACE, pass_plane<T>(c, st));
         return MM_OK;
     }
     if (c.p.yz || c.p.yz_small) {
@@ -2485,7 +2503,7 @@ mm_status autotune(const mm_grid* g, const mm_material* mat, const mm_options* o
             const Plan& pj = plans[j];
             if (done[j] || pj.Px != pi.Px || pj.Py != pi.Py || pj.Pz != pi.Pz || pj.total != pi.total ||
                 pj.o_kern != pi.o_kern || pj.o_S != pi.o_S || pj.o_twz != pi.o_twz || pj.zd != pi.zd ||
-                pj.fs != pi.fs || pj.fs_rt != pi.fs_rt || pj.yz_small != pi.yz_small)
+                pj.fs != pi.fs || pj.fs_rt != pi.fs_rt || pj.yz_small != pi.yz_small || pj.plane_nt != pi.plane_nt)
                 continue;
             done[j] = true;
             if (r != MM_OK) continue;

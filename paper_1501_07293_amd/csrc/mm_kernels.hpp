@@ -171,6 +171,10 @@ struct RShape {
     int yz;                  // threads of the fused y-z pass, 0: none
 };
 bool make_line_plan(int P, LinePlan* s);
+// threads of a work-group of the plane pass (0: no such shape) and the y lines of a round
+int plane_threads(const LinePlan& y, int Pz, int hx, int nz, size_t esz, int* yper);
+template <typename T>
+hipError_t launch_plane(const RYzArgs& a, const LinePlan& y, int Pz, hipStream_t st);
 // multiplier with which n / d = umulhi(n, mul) for n d < 2^32, d > 1
 constexpr unsigned div_mul(int d) { return d <= 1 ? 0u : (unsigned)(((unsigned long long)1 << 32) / (unsigned)d + 1); }
 // max_threads: of a work-group; min_groups: launches of fewer work-groups take fewer
