@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmmag.so")
 # the two largest first, so that the pool compiles them side by side
-SOURCES = ["mm_fast.hip", "mm_fused.hip", "mm_rline.hip", "mm_rfused.hip", "mm_zline.hip", "mm_plane.hip", "mm_api.hip", "mm_passes.hip", "mm_tensor.hip", "mm_llg.hip",
+SOURCES = ["mm_fast.hip", "mm_fused.hip", "mm_rline.hip", "mm_rfused.hip", "mm_zline.hip", "mm_plane.hip", "mm_tiny.hip", "mm_api.hip", "mm_passes.hip", "mm_tensor.hip", "mm_llg.hip",
            "mm_adjoint.hip", "mm_batch.hip", "mm_batch_rline.hip"]
 ARCH = os.environ.get("MMAG_ARCH", "gfx950")
 

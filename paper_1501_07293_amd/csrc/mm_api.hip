@@ -137,6 +137,8 @@ struct Plan {
                                // stage fewer
     int fs_lines;              // its row pairs per work-group
     bool fs_rt;                // in its runtime-length form
+    int tiny;                  // RK4 steps of the whole grid in one work-group: its threads, or 0
+    LinePlan tx, ty;           // and its schedules
     int64_t oct_elems;         // per component (two-plane schedule: per coefficient plane)
     int kplanes;               // blocks of oct_elems in the kernel region (ncomp, or 10)
     // workspace offsets
@@ -327,6 +329,7 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_pl
         }
     }
     p->fs = p->fs_lines > 0;
+    p->tiny = p->fs && p->nz == 1 ? tiny_plan(p->nx, p->ny, p->Px, p->Py, p->esz, &p->tx, &p->ty) : 0;
     // spectrum [3][nz][hx][S_rows]: the y pass expands ny rows to Py in place on 3-D grids
     p->S_planes = p->nz;
     p->S_rows = (p->three_d && !p->zd) ? p->Py : p->ny;
@@ -829,11 +832,14 @@ hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 // stage 4 writes the renormalised result back into m_n.
 template <typename T>
 mm_status rk4_fused_steps(mm_sim* s, int64_t nsteps, double dt, bool prologue, hipStream_t st);
+template <typename T>
+mm_status rk4_tiny_steps(mm_sim* s, int64_t nsteps, double dt, hipStream_t st);
 
 template <typename T>
 mm_status rk4_step(mm_sim* s, double dt, hipStream_t st)
 {
     const Plan& p = s->p;
+    if (p.tiny && s->prof_kernel < 0) return rk4_tiny_steps<T>(s, 1, dt, st);
     if (p.fs) return rk4_fused_steps<T>(s, 1, dt, true, st);
     T* mn = s->at<T>(p.o_mn);
     T* ma = s->at<T>(p.o_ma);
@@ -855,6 +861,23 @@ mm_status rk4_step(mm_sim* s, double dt, hipStream_t st)
         a.stage = stg + 1;
         LAUNCH(KLLG, launch_llg_stage<T>(a, st));
     }
+    return MM_OK;
+}
+
+// RK4 steps of a grid that one work-group holds: the state in, the state out.
+template <typename T>
+mm_status rk4_tiny_steps(mm_sim* s, int64_t nsteps, double dt, hipStream_t st)
+{
+    const Plan& p = s->p;
+    const PassCtx c = pass_ctx(s);
+    TinyArgs<T> t{};
+    t.g = llg_args<T>(s, dt);
+    t.m = s->at<T>(p.o_mn);
+    t.twx = c.twx;
+    t.twy = c.twy;
+    t.kern = c.kern;
+    t.k_cs = p.oct_elems;
+    LAUNCH(KLLG, launch_tiny_steps<T>(t, nsteps, p.tx, p.ty, p.tiny, st));
     return MM_OK;
 }
 
@@ -1106,6 +1129,8 @@ mm_status fused_step_impl(mm_sim* s, int64_t nsteps, double dt, bool use_graph)
 {
     hipStream_t st = s->stream;
     if (nsteps <= 0) return MM_OK;
+    // one launch: nothing to capture (timings by pass are of the separate passes)
+    if (s->p.tiny && s->prof_kernel < 0) return rk4_tiny_steps<T>(s, nsteps, dt, st);
     if (!use_graph) return rk4_fused_steps<T>(s, nsteps, dt, true, st);
     // 32 steps a graph: on the 128x128x1 film 49.9 -> 49.4 us per step against 8
     // (fewer graph launches; a rollout segment of 50 steps is one chunk and 18 steps)
@@ -2503,7 +2528,8 @@ mm_status autotune(const mm_grid* g, const mm_material* mat, const mm_options* o
             const Plan& pj = plans[j];
             if (done[j] || pj.Px != pi.Px || pj.Py != pi.Py || pj.Pz != pi.Pz || pj.total != pi.total ||
                 pj.o_kern != pi.o_kern || pj.o_S != pi.o_S || pj.o_twz != pi.o_twz || pj.zd != pi.zd ||
-                pj.fs != pi.fs || pj.fs_rt != pi.fs_rt || pj.yz_small != pi.yz_small || pj.plane_nt != pi.plane_nt)
+                pj.fs != pi.fs || pj.fs_rt != pi.fs_rt || pj.yz_small != pi.yz_small ||
+                pj.plane_nt != pi.plane_nt || pj.tiny != pi.tiny)
                 continue;
             done[j] = true;
             if (r != MM_OK) continue;

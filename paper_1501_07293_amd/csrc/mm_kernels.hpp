@@ -170,7 +170,7 @@ struct RShape {
     int csh;                 // log2 of the columns of the z k-space pass, -1: none
     int yz;                  // threads of the fused y-z pass, 0: none
 };
-bool make_line_plan(int P, LinePlan* s);
+bool make_line_plan(int P, LinePlan* s, int lines = 0, int max_threads = 0);
 // threads of a work-group of the plane pass (0: no such shape) and the y lines of a round
 int plane_threads(const LinePlan& y, int Pz, int hx, int nz, size_t esz, int* yper);
 template <typename T>
@@ -367,6 +367,24 @@ struct FusedStageArgs {
 int fused_stage_lines(int Px, int nx, int rows, size_t esz);
 template <typename T>
 bool launch_fused_stage(const FusedStageArgs<T>& a, int Px, int L, hipStream_t s);
+
+// RK4 steps of a one-cell-thick open grid that one work-group holds (mm_tiny.hip).
+template <typename T>
+struct TinyArgs {
+    LlgArgs<T> g;                // fields, constants and sizes (its state pointers unused)
+    T* m;                        // the state, advanced in place
+    const void *twx, *twy;       // exp(-2 pi i k / P), k < P, of the two lengths
+    const void* kern;            // octant [4][1][hx][Py/2+1]: xx, xy, yy, zz
+    int64_t k_cs;
+    int64_t nsteps;              // set by the launcher, as what follows
+    unsigned hmul, h1mul, npmul; // divide by hx, Py / 2 + 1, ceil(ny / 2)
+};
+// threads of the work-group and its schedules along x and y; 0 where the grid does not fit
+// one, or is better off with separate passes
+int tiny_plan(int nx, int ny, int Px, int Py, size_t esz, LinePlan* x, LinePlan* y);
+template <typename T>
+hipError_t launch_tiny_steps(TinyArgs<T> a, int64_t nsteps, const LinePlan& x, const LinePlan& y, int nt,
+                             hipStream_t st);
 
 // Per-term field in A/m: term 0 exch, 1 anis, 2 demag, 3 ext, 4 effective.
 template <typename T>

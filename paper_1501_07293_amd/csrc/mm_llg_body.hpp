@@ -8,6 +8,27 @@
 
 namespace mm {
 
+// The stage increment of a cell (Eq. 2 for the field of Eqs. 3-8, times the step) from its
+// m, Laplacian, demag field and reduced anisotropy constant; returns the reduced effective
+// field in h.
+template <typename T>
+__device__ inline void llg_increment(const LlgArgs<T>& a, const T (&m)[3], const T (&lap)[3], const T (&hd)[3], T kan,
+                                     T (&F)[3], T (&h)[3])
+{
+    h[0] = a.cex * lap[0] + kan * m[0] + a.hx + hd[0];
+    h[1] = a.cex * lap[1] + a.hy + hd[1];
+    h[2] = a.cex * lap[2] + a.hz + hd[2];
+    const T tx = m[1] * h[2] - m[2] * h[1];
+    const T ty = m[2] * h[0] - m[0] * h[2];
+    const T tz = m[0] * h[1] - m[1] * h[0];
+    const T dx = m[1] * tz - m[2] * ty;
+    const T dy = m[2] * tx - m[0] * tz;
+    const T dz = m[0] * ty - m[1] * tx;
+    F[0] = -a.gdt * (tx + a.alpha * dx);
+    F[1] = -a.gdt * (ty + a.alpha * dy);
+    F[2] = -a.gdt * (tz + a.alpha * dz);
+}
+
 // The stage update of cell c (Eq. 2 for the field of Eqs. 3-8, then the RK4 stage
 // combine, or the explicit Euler step) from its m, Laplacian, demag field, m_n,
 // RK4 accumulator and reduced anisotropy constant; writes the stage output (and
@@ -19,20 +40,12 @@ __device__ inline void llg_cell(const LlgArgs<T>& a, int64_t c, const T (&m)[3],
                                 T* heff = nullptr)
 {
     const int64_t N = a.N;
-    const T h[3] = {a.cex * lap[0] + kan * m[0] + a.hx + hd[0], a.cex * lap[1] + a.hy + hd[1],
-                    a.cex * lap[2] + a.hz + hd[2]};
+    T F[3], h[3];
+    llg_increment<T>(a, m, lap, hd, kan, F, h);
     if (heff) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) heff[d * N + c] = h[d];
     }
-    const T tx = m[1] * h[2] - m[2] * h[1];
-    const T ty = m[2] * h[0] - m[0] * h[2];
-    const T tz = m[0] * h[1] - m[1] * h[0];
-    const T dx = m[1] * tz - m[2] * ty;
-    const T dy = m[2] * tx - m[0] * tz;
-    const T dz = m[0] * ty - m[1] * tx;
-    const T F[3] = {-a.gdt * (tx + a.alpha * dx), -a.gdt * (ty + a.alpha * dy),
-                    -a.gdt * (tz + a.alpha * dz)};
     if (a.stage == 0) {  // explicit Euler with renormalisation
         T v[3];
 #pragma unroll

@@ -84,7 +84,9 @@ static double radix_cost(int R, bool first)
     return d;
 }
 
-bool make_line_plan(int P, LinePlan* s)
+// lines > 0: for that many lines side by side in one work-group of up to max_threads, with
+// radices up to 8: what counts is a thread's chain, times the rounds the lines take.
+bool make_line_plan(int P, LinePlan* s, int lines, int max_threads)
 {
     *s = LinePlan{};
     if (P < 2 || P > 8192) return false;
@@ -99,7 +101,10 @@ bool make_line_plan(int P, LinePlan* s)
             for (int i = 1; i < n; ++i) rmin = cur[i] < rmin ? cur[i] : rmin;
             double c = 0;
             for (int i = 0; i < n; ++i) c += radix_cost(cur[i], i == 0 && n > 1) + 40.0;
-            c *= (double)(P / rmin) / P;
+            if (lines > 0)
+                c *= (lines * (P / rmin) + max_threads - 1) / max_threads;
+            else
+                c *= (double)(P / rmin) / P;
             if (c < cbest) {
                 cbest = c;
                 nbest = n;
@@ -109,7 +114,7 @@ bool make_line_plan(int P, LinePlan* s)
         }
         if (n == kMaxLineStages) return;
         for (int r : set)
-            if (rest % r == 0) {
+            if (rest % r == 0 && (lines <= 0 || r <= 8)) {
                 cur[n] = r;
                 self(self, rest / r, n + 1);
             }
