@@ -60,7 +60,7 @@ typedef enum {
 /* Option flags. */
 #define MM_NO_DEMAG 0x1u   /* drop the demag term (exchange, anisotropy, applied only) */
 #define MM_USE_GRAPH 0x2u  /* mm_step replays a captured hipGraph of whole RK4 steps */
-#define MM_GENERIC_FFT 0x4u /* use the runtime-radix FFT passes even where a size-specialised
+#define MM_GENERIC_FFT 0x4u /* use the runtime-length FFT passes even where a size-specialised
                                pass exists (both give the same result up to rounding) */
 #define MM_POW2_PAD 0x10u  /* automatic padded sizes are the next power of two >= 2n-1 (instead of
                                the smallest 7-smooth size), so the size-specialised passes apply;
@@ -92,36 +92,40 @@ typedef enum {
  * adjoint): mm_batch_create returns MM_ENOTSUP for periodic grids. */
 /* 3-D grids whose [3][Pz][Py] spectrum plane of one x bin fits a work-group
  * (3 Py Pz <= 16 x threads, e.g. 256x64x4): run the y forward, z k-space and y
- * inverse passes as one fused pass (three passes per field evaluation instead of
- * five).  Off by default: with one work-group per x bin it measured slower than
- * the five passes on such films (256x64x4 FP32: 0.17 against 0.10 ms per RK4
- * step); MM_AUTOTUNE times both schedules where the fused one applies. */
+ * inverse passes as one fused pass whose z lines exchange through LDS (three passes
+ * per field evaluation instead of five).  Off by default: on the smaller planes the
+ * library runs a fused pass by itself, with up to 12 points along z one that keeps the
+ * z lines in registers (256x64x4 FP32: 76 against 88 us per RK4 step with this flag and
+ * 87 with five passes; plan_info still counts five), and on the larger ones five passes
+ * are faster; MM_AUTOTUNE times both schedules where this one applies. */
 #define MM_FUSED_YZ 0x400u
 /* Grids whose padded volume of the three components fits one work-group's LDS
  * (3 px py pz <= 16 x threads, e.g. 32x8x1 at 64x16 points): one work-group runs
  * the whole demag evaluation (every x, y and z transform of the padded volume,
  * the Eq. 14 product and the inverse) in a single launch instead of three or
- * five.  Off by default: it measured slower than the multi-pass schedules (the
- * 32x8x1 strip, FP32: 116 against 61 us per RK4 step), since one work-group runs
- * every stage back to back.  Ignored where the volume does not fit or MM_NO_DEMAG
+ * five.  Off by default: it measured slower than the default schedules (the
+ * 32x8x1 strip, FP32: 116 against 25 us per RK4 step): it transforms every line of
+ * the padded volume, and the state leaves the work-group between stages.  Ignored where the volume does not fit or MM_NO_DEMAG
  * is set; takes precedence over MM_FUSED_YZ; MM_AUTOTUNE times it where it
  * applies. */
 #define MM_ONE_WG 0x800u
-/* Grids of up to 2^20 cells with open boundaries and a size-specialised x pass
- * run each RK4 stage as the y / z passes (the y k-space pass of one-cell-thick
+/* Grids of up to 2^20 cells with open boundaries and a size-specialised x pass (up to
+ * 2^17 cells with any other x length up to 512) run each RK4 stage as the y / z passes (the y k-space pass of one-cell-thick
  * grids, the two-plane pass of grids two cells thick, else y forward, z k-space,
  * y inverse) and one fused pass doing the x inverse, the stage update and the x
  * forward of the stage output on a block of rows of one plane (the demag field
  * never leaves LDS): two launches per stage fewer.  Small grids are bound by the
  * latency of dependent launches, not by bandwidth (the 128x128x1 film: four
- * launches of 4-7 us per stage).  Results equal the separate passes to rounding.
+ * launches of 4-7 us per stage).  One-cell-thick grids that fit a work-group (a
+ * spectrum of up to 1024 entries in FP32, 256 in FP64) run all stages of all steps of
+ * mm_step in one launch.  Results equal the separate passes to rounding.
  * This flag keeps the separate passes. */
 #define MM_SPLIT_STAGE 0x2000u
 #define MM_PERIODIC_X 0x80u
 #define MM_PERIODIC_Y 0x100u
 #define MM_PERIODIC_Z 0x200u
 #define MM_AUTOTUNE 0x8u    /* mm_create times the candidate schedules of this grid (padded sizes
-                               7-smooth vs power of two, specialised vs runtime-radix passes,
+                               7-smooth vs power of two, specialised vs runtime-length passes,
                                256 vs 512 threads, x lines per work-group, fused y-z pass, one
                                work-group) and keeps the fastest.  The candidates run in the
                                caller's workspace when it holds every one of them (the size
@@ -131,7 +135,7 @@ typedef enum {
                                process and, if MMAG_TUNE_CACHE names a file, across processes,
                                keyed by the GPU (architecture, name, compute units), the grid
                                and the options.  mm_batch_create times the batch layouts
-                               (7-smooth padding, power-of-two padding with runtime-radix passes,
+                               (7-smooth padding, power-of-two padding with runtime-length passes,
                                power-of-two padding with size-class passes) on one field
                                evaluation each and keeps the fastest (mm_batch_get_info reports
                                it); MM_POW2_PAD and MM_GENERIC_FFT are then ignored.  Explicit
@@ -164,7 +168,7 @@ typedef struct {
                             0 = automatic (FP32 8 forward, 4 inverse; FP64 4 and 4 at
                             1024 points), 4, 8 or 16 (both passes;
                             16 only where its LDS tile and
-                            work-group fit; otherwise that pass runs the runtime-radix body) */
+                            work-group fit; otherwise that pass runs the runtime-length body) */
     int32_t images;      /* periodic axes: images on each side beyond the nearest, 0..64 */
 } mm_options;
 
@@ -176,9 +180,10 @@ typedef struct {
     int64_t spectrum_elems; /* elements of the kernel spectrum: the octant, ncomp*(pz/2+1)*hx*(py/2+1),
                                or with two_plane the 10*hx*(py/2+1) coefficient planes */
     int32_t passes;      /* FFT passes per field evaluation (1 with MM_ONE_WG in use, 3 for
-                            nz == 1, the two-plane schedule or the fused y-z pass, else 5) */
+                            nz == 1, the two-plane schedule or MM_FUSED_YZ in use, else 5,
+                            also where a fused y-z pass runs by itself) */
     double kernel_imag_ratio; /* max |Im| / max |Re| of the FP64 kernel spectrum (should be ~1e-16) */
-    int32_t generic_fft; /* 1 when the runtime-radix passes are forced */
+    int32_t generic_fft; /* 1 when the runtime-length passes are forced */
     int32_t tuned;       /* 1 when the schedule came from the autotuner */
     int32_t candidates;  /* schedules the autotuner timed (0 if cached or not tuned) */
     double tuned_demag_ms; /* the chosen schedule's time per demag evaluation, ms (0 if not tuned) */
@@ -193,7 +198,8 @@ typedef struct {
                             xy0, xy1, sxz, yy0, yy1, syz, zz0, zz1 (suffix 0: z offset 0; 1: z
                             offset +1, the observer above the source; at offset +1 the xz and
                             yz spectra are i sxz and i syz) */
-    int32_t fused_stage; /* 1: RK4 stages run the fused stage pass (see MM_SPLIT_STAGE) */
+    int32_t fused_stage; /* 1: RK4 stages run the size-specialised fused stage pass (see
+                            MM_SPLIT_STAGE); 0 also where its runtime-length form runs */
 } mm_plan_info;
 
 typedef struct mm_sim mm_sim;
@@ -343,7 +349,7 @@ typedef struct {
     int32_t n;               /* grids */
     int32_t pow2_pad;        /* 1: padded sizes are powers of two; 0: 7-smooth */
     int32_t size_classes;    /* 1: the size-class passes (one launch per padded length per
-                                pass); 0: the runtime-radix passes (one launch per pass) */
+                                pass); 0: the runtime-length passes (one launch per pass) */
     int32_t tuned;           /* 1: chosen by MM_AUTOTUNE */
     int32_t tune_candidates; /* layouts timed */
     int32_t fast_pad;        /* 1: padded sizes from the specialised set (MM_FAST_PAD) */

@@ -1722,7 +1722,7 @@ struct BatchLayout {
     size_t o_desc, o_prefix, o_mn, o_ma, o_mb, o_acc, o_hd, o_S, o_kern, o_tw, o_flags, o_scratch, total;
     int prec;
     size_t esz;
-    bool plan_generic = false;  // the plans were built with the runtime-radix passes forced
+    bool plan_generic = false;  // the plans were built with the runtime-length passes forced
     std::vector<std::array<int, 2>> pad;  // per grid explicit (px, py), 0 = automatic
 };
 
@@ -1740,7 +1740,7 @@ mm_status batch_layout(int32_t n, const mm_grid* grids, const mm_options* opt, B
     mm_options o = opt ? *opt : mm_options{};
     o.threads = 256;
     // size classes (the specialised passes) are wanted with power-of-two or fast
-    // padding; otherwise every grid runs the runtime-radix passes, whose plans
+    // padding; otherwise every grid runs the runtime-length passes, whose plans
     // must not take the two-plane schedule.  If some grid has no size class, the
     // layout is built again that way, with the register passes where every grid has
     // them, else with the LDS-staged ones.
@@ -2045,7 +2045,7 @@ BatchClass<T> batch_class(mm_batch* b)
 
 // One demag field evaluation of every grid: the passes from m (in) to the
 // field in the hd region, as size-class launches (power-of-two padding) or one
-// runtime-radix launch per pass.
+// runtime-length launch per pass.
 template <typename T>
 mm_status batch_demag(mm_batch* b, const T* in, hipStream_t st)
 {
@@ -2281,8 +2281,8 @@ mm_status batch_field_impl(mm_batch* b, int term, void* out, int on_device)
 }
 
 // ---------------------------------------------------------------- batch autotuner
-// Candidate layouts of a batch: 7-smooth padding with the runtime-radix passes
-// (the default), power-of-two padding with the runtime-radix passes, and
+// Candidate layouts of a batch: 7-smooth padding with the runtime-length passes
+// (the default), power-of-two padding with the runtime-length passes, and
 // power-of-two padding with the size-class passes when every padded length has
 // one.  A candidate whose padded sizes equal an earlier one's is dropped.
 std::vector<mm_options> batch_tune_candidates(int32_t n, const mm_grid* grids, const mm_options* opt)
@@ -2438,8 +2438,8 @@ mm_status time_demag(mm_sim* s, hipStream_t st, double* ms_out)
 }
 
 // Candidate schedules of a grid: padded sizes (7-smooth default vs the power of
-// two that the specialised passes handle), specialised vs runtime-radix
-// passes, and the runtime-radix work-group size.
+// two that the specialised passes handle), specialised vs runtime-length
+// passes, and the runtime-length work-group size.
 std::vector<mm_options> tune_candidates(const mm_grid* g, const mm_options* o)
 {
     // a periodic axis has one size, its period (requested as 0)

@@ -2,8 +2,10 @@
 // advanced together.  Every pass of a field evaluation (and the LLG stage) is
 // ONE kernel launch over all grids: the launch's tiles are the concatenation
 // of every grid's tiles, and a work-group finds its grid by binary search in
-// the per-pass tile prefix sums, then runs the same device body as the
-// single-grid runtime-radix kernels with that grid's descriptor.
+// the per-pass tile prefix sums, then runs the same device body as a
+// single-grid kernel with that grid's descriptor.  Here are the size classes'
+// specialised passes (kbf_*) and the LDS-staged ones (kb_*) for the grids whose lines
+// the register passes of runtime length (mm_batch_rline.hip) cannot take.
 #include "mm_fast.hpp"
 #include "mm_generic.hpp"
 #include "mm_llg_body.hpp"

@@ -719,7 +719,9 @@ __device__ inline void body_kspace_z_split(const KzArgs& a, int tile, cpx<T>* sh
 // Eq. 14 for a frequency pair ky, P - ky of a one-cell-thick grid: the components at q and
 // at its mirror q2, stride apart, times xx, xy, yy, zz (xy odd in ky), stored conjugated
 // (the inverse transform runs as a forward one).  Both points are read before either is
-// written; where ky is its own mirror, q2 = q and only q is written.
+// written (one after the other they made an RK4 step of a 166x42x1 film 1.5% longer); where ky
+// is its own mirror, q2 = q and only q is written.  One octant entry for the pair, in place of
+// one each: 512x512x1 FP64 195 -> 170 us per RK4 step.
 template <typename T>
 __device__ inline void thin_product(cpx<T>* q, cpx<T>* q2, bool mirror, int stride, T xx, T xy, T yy, T zz)
 {

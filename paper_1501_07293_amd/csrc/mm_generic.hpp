@@ -1,9 +1,11 @@
-// mm_generic.hpp -- device bodies of the runtime-radix FFT passes (any
-// 7-smooth length), shared by the single-grid kernels (mm_passes.hip) and the
-// batched kernels (mm_batch.hip).  Each body works one tile of its pass; the
-// caller supplies the tile index, the LDS buffer (lds_elems(NT) entries) and
-// the radix schedule (by reference, so a schedule held in memory is indexed in
-// place rather than copied into registers).
+// mm_generic.hpp -- device bodies of the LDS-staged FFT passes (any 7-smooth length): the
+// FP64 setup of the kernel spectrum, the passes of grids whose lines the register passes
+// (mm_rline.hpp) cannot take (work-groups of more than 512 threads, or buffers past 2 GiB),
+// and the one-work-group form.  Shared by the single-grid kernels (mm_passes.hip) and the
+// batched kernels (mm_batch.hip).  Each body works one tile of its pass; the caller
+// supplies the tile index, the LDS buffer (lds_elems(NT) entries) and the radix schedule
+// (by reference, so a schedule held in memory is indexed in place rather than copied into
+// registers).
 #pragma once
 #include "mm_demag1.hpp"
 #include "mm_fft.hpp"

@@ -1,5 +1,7 @@
 // mm_passes.hip -- the FFT passes of the demag convolution (Sec. 2.3, Eq. 14
-// with the zero padding of Fig. 1 / Listing 4), as LDS-staged batched FFTs.
+// with the zero padding of Fig. 1 / Listing 4), as LDS-staged batched FFTs: the setup
+// and what neither the size-specialised (mm_fast.hip) nor the register passes of runtime
+// length (mm_rline.hip) take.
 //
 // Per field evaluation on an nx x ny x nz grid padded to Px x Py x Pz:
 //   row_r2c : x, real -> half spectrum, input pruned to nx of Px

@@ -14,7 +14,13 @@
 //
 // What these replace ran every length through one LDS-staged body with 16 elements a
 // thread: a division and a remainder per element to find its line, 215 to 233
-// registers (two waves a SIMD) and strided twiddle reads.
+// registers (two waves a SIMD) and strided twiddle reads.  Measured per RK4 step, all passes
+// of a stage together (and with the fused stage and plane passes where they apply), before ->
+// now: 200x200x1 FP32 237 -> 80 us, FP64 261 -> 93; 100x100x10 368 -> 121 and 495 -> 169;
+// 301x190x6 729 -> 228 and 1155 -> 327; 360x300x10 periodic in x and y 655 -> 269 and 1031 ->
+// 435; 96x96x96 880 -> 490 and 1687 -> 861.  What bounds them now: on grids of some 10^5 cells
+// the latency of their dependent launches and LDS stages, on the larger ones the caches and
+// memory (the stage update beside them runs at the copy rate there).
 //
 // Spectrum layout: as everywhere, S = [3][nz][hx][Sy].
 #pragma once

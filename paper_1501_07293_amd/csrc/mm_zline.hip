@@ -3,7 +3,9 @@
 //
 // One thread holds a whole z line of one component, as in the power-of-two pass; the
 // runtime-length pass (mm_rline.hpp) exchanges its stages through LDS and holds a radix's
-// worth of registers for every length it serves.
+// worth of registers for every length it serves.  Memory and its own butterflies bound it alike;
+// per launch, that pass -> this one: 301x190x6 (12 points) FP32 15.7 -> 9.9 us, 360x300x10
+// periodic in x and y (20 points) 24.9 -> 12.3.
 #include "mm_fast.hpp"
 
 namespace mm {
