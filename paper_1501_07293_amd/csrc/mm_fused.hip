@@ -8,7 +8,7 @@ namespace mm {
 constexpr int kFusedPrefetchGroups = 256;
 
 template <typename T, int P, int L, bool PREFETCH>
-__global__ __launch_bounds__((fused_threads<P, L>())) void k_fused_stage(FusedStageArgs<T> a)
+__global__ __launch_bounds__((fused_threads<T, P, L, PREFETCH>())) void k_fused_stage(FusedStageArgs<T> a)
 {
     __shared__ cpx<T> lds[3 * fused_region<P, L>()];
     __shared__ T cell[3 * 2 * L * (P / 2)];
@@ -16,7 +16,7 @@ __global__ __launch_bounds__((fused_threads<P, L>())) void k_fused_stage(FusedSt
 }
 
 template <typename T, int P, int L>
-__global__ __launch_bounds__((fused_threads<P, L>())) void k_fused_adjoint(FusedAdjArgs<T> a)
+__global__ __launch_bounds__((fused_threads<T, P, L>())) void k_fused_adjoint(FusedAdjArgs<T> a)
 {
     __shared__ cpx<T> lds[3 * fused_region<P, L>()];
     __shared__ T cell[3 * 2 * L * (P / 2)];
@@ -31,20 +31,23 @@ static bool fused_dispatch(const FusedStageArgs<T>& a, int L, hipStream_t s)
     // are latency-bound: their stage-update loads go out with the gather's.  On the
     // 128x128x1 film 49.9 -> 47.8 us per RK4 step; with more work-groups the lower
     // occupancy costs more (256x256x16 FP32 388 -> 404 us, 64^3 FP64 297 -> 318 us)
-    auto go = [&](auto kern, auto kern_pre, int lines, int threads) {
+    auto go = [&](auto kern, auto kern_pre, int lines, int threads, int few) {
         const int grid = a.g.nz * ((a.g.ny + 2 * lines - 1) / (2 * lines));
         if (grid <= kFusedPrefetchGroups)
-            hipLaunchKernelGGL(kern_pre, dim3(grid), dim3(threads), 0, s, a);
+            hipLaunchKernelGGL(kern_pre, dim3(grid), dim3(few), 0, s, a);
         else
             hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, s, a);
         return true;
     };
     if constexpr (fused_lds_bytes<T, P, 4>() <= kLdsBudget && 3 * 4 * TL <= 1024)
-        if (L == 4) return go(k_fused_stage<T, P, 4, false>, k_fused_stage<T, P, 4, true>, 4, fused_threads<P, 4>());
+        if (L == 4) return go(k_fused_stage<T, P, 4, false>, k_fused_stage<T, P, 4, true>, 4,
+                            fused_threads<T, P, 4>(), fused_threads<T, P, 4, true>());
     if constexpr (fused_lds_bytes<T, P, 2>() <= kLdsBudget && 3 * 2 * TL <= 1024)
-        if (L == 2) return go(k_fused_stage<T, P, 2, false>, k_fused_stage<T, P, 2, true>, 2, fused_threads<P, 2>());
+        if (L == 2) return go(k_fused_stage<T, P, 2, false>, k_fused_stage<T, P, 2, true>, 2,
+                            fused_threads<T, P, 2>(), fused_threads<T, P, 2, true>());
     if constexpr (fused_lds_bytes<T, P, 1>() <= kLdsBudget && 3 * TL <= 1024)
-        if (L == 1) return go(k_fused_stage<T, P, 1, false>, k_fused_stage<T, P, 1, true>, 1, fused_threads<P, 1>());
+        if (L == 1) return go(k_fused_stage<T, P, 1, false>, k_fused_stage<T, P, 1, true>, 1,
+                            fused_threads<T, P, 1>(), fused_threads<T, P, 1, true>());
     return false;
 }
 
@@ -79,11 +82,11 @@ static bool fused_adj_dispatch(const FusedAdjArgs<T>& a, int L, hipStream_t s)
         return true;
     };
     if constexpr (fused_lds_bytes<T, P, 4>() <= kLdsBudget && 3 * 4 * TL <= 1024)
-        if (L == 4) return go(k_fused_adjoint<T, P, 4>, 4, fused_threads<P, 4>());
+        if (L == 4) return go(k_fused_adjoint<T, P, 4>, 4, fused_threads<T, P, 4>());
     if constexpr (fused_lds_bytes<T, P, 2>() <= kLdsBudget && 3 * 2 * TL <= 1024)
-        if (L == 2) return go(k_fused_adjoint<T, P, 2>, 2, fused_threads<P, 2>());
+        if (L == 2) return go(k_fused_adjoint<T, P, 2>, 2, fused_threads<T, P, 2>());
     if constexpr (fused_lds_bytes<T, P, 1>() <= kLdsBudget && 3 * TL <= 1024)
-        if (L == 1) return go(k_fused_adjoint<T, P, 1>, 1, fused_threads<P, 1>());
+        if (L == 1) return go(k_fused_adjoint<T, P, 1>, 1, fused_threads<T, P, 1>());
     return false;
 }
 

@@ -30,11 +30,20 @@ constexpr int fused_lds_bytes() { return (int)(3 * fused_region<P, L>() * sizeof
 // that below 256, and the gather, the stage update and the transposed store then
 // run with 256 (one cell update per thread at 128x128x1 instead of six in one wave),
 // the extra threads joining only the barriers of the line transforms.
-template <int P, int L>
-constexpr int fused_threads() { return 3 * L * (P / Sched<P>::R0) > 256 ? 3 * L * (P / Sched<P>::R0) : 256; }
+// FEW, for launches of at most a work-group a CU: up to 512 threads, one a cell, since a
+// thread's second cell is as long a chain as its first.  RK4 step, FP32: 512x512x1 124.7 ->
+// 116.0 us, 256x256x1 59.0 -> 57.7, 256x64x4 75.2 -> 74.4; FP64 256x64x2 72.2 -> 71.1, but
+// 1024 points spill in FP64 with 512 threads (512x512x1 175 -> 268 us) and keep theirs.
+template <typename T, int P, int L, bool FEW = false>
+constexpr int fused_threads()
+{
+    constexpr int lines = 3 * L * (P / Sched<P>::R0), base = lines > 256 ? lines : 256;
+    constexpr int cells = L * P < 512 ? L * P : 512;
+    return FEW && cells > base && !(sizeof(T) == 8 && P > 512) ? cells : base;
+}
 
 // Work-group `tile` takes rows 2L t .. 2L t + 2L - 1 of plane z (tile = z tpp + t,
-// tpp = ceil(ny / 2L)); fused_threads<P, L>() threads, the first 3 L (P / R0) of
+// tpp = ceil(ny / 2L)); NT threads, the first 3 L (P / R0) of
 // them (component, line l, lane u) for the line transforms.  Spectrum element
 // (c, z, kx, y) at ((c nz + z) hx + kx) sy + y.  Needs 2 nx <= P (the pruned x
 // lines) and open boundaries.
@@ -43,12 +52,11 @@ constexpr int fused_threads() { return 3 * L * (P / Sched<P>::R0) > 256 ? 3 * L 
 // real values; `pre` runs right after the gather's loads are issued), then
 // `update` (which reads the cells' field there and leaves in their place what is
 // to be transformed), then, if fwd, the x forward of `cell` into S_out.
-template <typename T, int P, int L, class Pre, class Update>
+template <typename T, int P, int L, int NT, class Pre, class Update>
 __device__ inline void fused_block(const void* S_in, void* S_out, int64_t sy, const void* tw, int nx, int ny,
                                    int nz, int tile, bool fwd, cpx<T>* lds, T* cell, Pre pre, Update update)
 {
     constexpr int R0 = Sched<P>::R0, TL = P / R0, NL = 3 * L * TL, LP = padded_len<P>();
-    constexpr int NT = fused_threads<P, L>();
     constexpr int HX = P / 2 + 1, ROWS = 2 * L, REG = fused_region<P, L>(), XH = P / 2;
     const int tpp = (ny + ROWS - 1) / ROWS;
     const int z = tile / tpp, yb = (tile - z * tpp) * ROWS;
@@ -261,7 +269,7 @@ struct StageIn {
 template <typename T, int P, int L, bool PREFETCH>
 __device__ inline void body_fused_stage(const FusedStageArgs<T>& f, int tile, cpx<T>* lds, T* cell)
 {
-    constexpr int NT = fused_threads<P, L>();
+    constexpr int NT = fused_threads<T, P, L, PREFETCH>();
     constexpr int ROWS = 2 * L, XH = P / 2;
     const LlgArgs<T>& a = f.g;
     const int tpp = (a.ny + ROWS - 1) / ROWS;
@@ -288,7 +296,7 @@ __device__ inline void body_fused_stage(const FusedStageArgs<T>& f, int tile, cp
     auto pre = [&] {
         if constexpr (PRE) in.load(a, b, tid, 0, NC);
     };
-    fused_block<T, P, L>(f.S_in, f.S_out, f.sy, f.tw, a.nx, a.ny, a.nz, tile, true, lds, cell, pre, update);
+    fused_block<T, P, L, NT>(f.S_in, f.S_out, f.sy, f.tw, a.nx, a.ny, a.nz, tile, true, lds, cell, pre, update);
 }
 
 // One stage of the reverse sweep for the block's cells (FusedAdjArgs): the apply on the
@@ -376,13 +384,13 @@ __device__ inline void fused_adjoint_cells(const FusedAdjArgs<T>& f, const CellB
 template <typename T, int P, int L>
 __device__ inline void body_fused_adjoint(const FusedAdjArgs<T>& f, int tile, cpx<T>* lds, T* cell)
 {
-    constexpr int NT = fused_threads<P, L>();
+    constexpr int NT = fused_threads<T, P, L>();
     constexpr int ROWS = 2 * L, XH = P / 2, NC = (ROWS * XH + NT - 1) / NT;
     const AdjArgs<T>& a = f.a;
     auto update = [&](int z, int yb) {
         fused_adjoint_cells(f, CellBlock{z, yb, ROWS, XH, NT}, (int)threadIdx.x, NC, cell);
     };
-    fused_block<T, P, L>(f.S_in, f.S_out, f.sy, f.tw, a.nx, a.ny, a.nz, tile, f.mode != 0, lds, cell, [] {}, update);
+    fused_block<T, P, L, NT>(f.S_in, f.S_out, f.sy, f.tw, a.nx, a.ny, a.nz, tile, f.mode != 0, lds, cell, [] {}, update);
 }
 
 }  // namespace mm

@@ -49,6 +49,10 @@ static bool rfused_args(RFusedArgs* g, const LinePlan& s, const void* S_in, void
     *g = RFusedArgs{S_in, S_out, sy, tws, nx, ny, nz, L, L == 4 ? 3 : (L == 2 ? 2 : 1), div_mul(s.P / 2 + 1)};
     *grid = nz * ((ny + 2 * L - 1) / (2 * L));
     *nt = rfused_threads(L, s);
+    // a work-group a CU or fewer: a thread a cell, up to 512.  RK4 step, FP32: 150x100x1 70.1 ->
+    // 65.7 us, 250x60x2 82.9 -> 78.6, 200x100x4 98.1 -> 95.0; FP64 loses (200x40x1 72.9 -> 78.7,
+    // 200x100x4 119.3 -> 122.4)
+    if (esz == 4 && *grid <= kRfPrefetchGroups) *nt = std::max(*nt, std::min(kRfMaxThreads, (2 * L * nx + 63) / 64 * 64));
     *lds = rfused_lds(L, s.P, nx, esz);
     return s.ns > 0 && (L == 1 || L == 2 || L == 4) && *nt <= kRfMaxThreads && *lds <= kRfLds;
 }
