@@ -329,7 +329,8 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_pl
         }
     }
     p->fs = p->fs_lines > 0;
-    p->tiny = p->fs && p->nz == 1 ? tiny_plan(p->nx, p->ny, p->Px, p->Py, p->esz, &p->tx, &p->ty) : 0;
+    // its product is that of the four spectra of an unpadded z axis
+    p->tiny = p->fs && !p->three_d ? tiny_plan(p->nx, p->ny, p->Px, p->Py, p->esz, &p->tx, &p->ty) : 0;
     // spectrum [3][nz][hx][S_rows]: the y pass expands ny rows to Py in place on 3-D grids
     p->S_planes = p->nz;
     p->S_rows = (p->three_d && !p->zd) ? p->Py : p->ny;
@@ -877,6 +878,7 @@ mm_status rk4_tiny_steps(mm_sim* s, int64_t nsteps, double dt, hipStream_t st)
     t.twy = c.twy;
     t.kern = c.kern;
     t.k_cs = p.oct_elems;
+    t.ncomp = p.ncomp;
     LAUNCH(KLLG, launch_tiny_steps<T>(t, nsteps, p.tx, p.ty, p.tiny, st));
     return MM_OK;
 }

@@ -376,6 +376,7 @@ struct TinyArgs {
     const void *twx, *twy;       // exp(-2 pi i k / P), k < P, of the two lengths
     const void* kern;            // octant [4][1][hx][Py/2+1]: xx, xy, yy, zz
     int64_t k_cs;
+    int ncomp;                   // components of the octant: 4
     int64_t nsteps;              // set by the launcher, as what follows
     unsigned hmul, h1mul, npmul; // divide by hx, Py / 2 + 1, ceil(ny / 2)
 };

@@ -237,7 +237,8 @@ hipError_t launch_tiny_steps(TinyArgs<T> a, int64_t nsteps, const LinePlan& x, c
 {
     const int nx = a.g.nx, ny = a.g.ny;
     const size_t lds = tiny_lds_bytes(nx, ny, x.P, y.P, sizeof(T));
-    if (nt < 1 || nt > kTinyMaxThreads || lds > kTinyLds || a.g.nz != 1 || a.g.per != 0) return hipErrorInvalidValue;
+    if (nt < 1 || nt > kTinyMaxThreads || lds > kTinyLds || a.g.nz != 1 || a.g.per != 0 || a.ncomp != 4)
+        return hipErrorInvalidValue;
     a.hmul = div_mul(x.P / 2 + 1);
     a.h1mul = div_mul(y.P / 2 + 1);
     a.npmul = div_mul((ny + 1) / 2);
