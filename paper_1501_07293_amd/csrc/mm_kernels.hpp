@@ -160,7 +160,7 @@ struct RYzArgs {             // y forward, z k-space and y inverse of one x bin 
     int64_t k_cs, k_zs, k_xs;
     int nt;                  // threads of a work-group
     int zper;                // z lines a round takes
-    unsigned zmul, ymul;     // divide by zper, by Py
+    unsigned zmul, ymul;     // divide by zper (if over 1), by Py
 };
 // Work-group shapes of these passes for one grid: lines (or columns) per work-group.
 // Zero where the pass has no such shape (the length's schedule, threads or LDS).

@@ -276,7 +276,8 @@ template <typename T>
 hipError_t launch_ryz(const RYzArgs& a, const LinePlan& y, const LinePlan& z, hipStream_t st)
 {
     const size_t lds = ryz_lds_bytes(y.P, z.P, sizeof(T));
-    if (a.nt > ryz_max_threads<T>() || y.TL > a.nt || z.TL > a.nt || lds > (size_t)kLdsBudget) return hipErrorInvalidValue;
+    if (a.nt > ryz_max_threads<T>() || y.TL > a.nt || a.zper < 1 || a.zper * z.TL > a.nt || lds > (size_t)kLdsBudget)
+        return hipErrorInvalidValue;
     if (a.hx <= 0) return hipSuccess;
     auto go = [&](auto kern) {
         if (lds > kRLdsBudget) {

@@ -591,7 +591,7 @@ __device__ inline void body_ryz(const RYzArgs& a, const LinePlan& ply, const Lin
     // z lines: line q = c Py + y, lanes line-fastest (neighbouring entries of a row)
     auto z_lines = [&]() __attribute__((always_inline)) {
         for (int q0 = 0; q0 < 3 * Py; q0 += zper) {
-            int u = sz.TL == 1 ? 0 : div_by(t, a.zmul);
+            int u = sz.TL == 1 ? 0 : (zper == 1 ? t : div_by(t, a.zmul));
             int q = q0 + t - u * zper;
             const bool real = u < sz.TL && q < 3 * Py;
             if (!real) u = 0, q = q0;
