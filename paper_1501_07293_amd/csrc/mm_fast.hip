@@ -29,6 +29,14 @@ __global__ __launch_bounds__((3 * kzl_cols<T, P>() * (P / Sched<P>::R0))) void k
     body_kspace_zl<T, P, CW>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
 }
 
+template <typename T, int P>
+__global__ __launch_bounds__((3 * kzl_cols<T, P>() * (P / Sched<P>::R0))) void k_kspace_zl_wide(KzArgs a)
+{
+    constexpr int CW = kzl_cols<T, P>();
+    __shared__ cpx<T> lds[3 * CW * padded_len<P>()];
+    body_kspace_zl<T, P, CW, true>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
+}
+
 template <typename T, int P, int L, bool FULL>
 __global__ __launch_bounds__(L * (P / Sched<P>::R0)) void k_xinv(XLineArgs a)
 {
@@ -190,17 +198,25 @@ bool launch_kspace_z(const KzArgs& a, int PZ, hipStream_t s)
         return true;
     };
     if (PZ >= 128 && 2 * a.nz <= PZ) {
-        // one descriptor each for the spectrum and the octant
-        if (3 * a.comp_stride * 2 * (int64_t)sizeof(T) >= kRLineBytes ||
-            6 * a.k_cs * (int64_t)sizeof(T) >= kRLineBytes)
-            return false;
+        // One descriptor each for the spectrum and the octant; past 2 GiB the wide form.  (An
+        // octant below it keeps P / 2 z steps, the largest scalar offset, below it too.)
+        const bool wide = 3 * a.comp_stride * 2 * (int64_t)sizeof(T) >= kRLineBytes ||
+                          6 * a.k_cs * (int64_t)sizeof(T) >= kRLineBytes;
         switch (PZ) {
-        case 128: return zl(k_kspace_zl<T, 128, kzl_tile<T, 128>()>, kzl_cols<T, 128>(), 128 / Sched<128>::R0);
-        case 256: return zl(k_kspace_zl<T, 256, kzl_tile<T, 256>()>, kzl_cols<T, 256>(), 256 / Sched<256>::R0);
-        case 512: return zl(k_kspace_zl<T, 512, kzl_tile<T, 512>()>, kzl_cols<T, 512>(), 512 / Sched<512>::R0);
+        case 128:
+            if (wide) return zl(k_kspace_zl_wide<T, 128>, kzl_cols<T, 128>(), 128 / Sched<128>::R0);
+            return zl(k_kspace_zl<T, 128, kzl_tile<T, 128>()>, kzl_cols<T, 128>(), 128 / Sched<128>::R0);
+        case 256:
+            if (wide) return zl(k_kspace_zl_wide<T, 256>, kzl_cols<T, 256>(), 256 / Sched<256>::R0);
+            return zl(k_kspace_zl<T, 256, kzl_tile<T, 256>()>, kzl_cols<T, 256>(), 256 / Sched<256>::R0);
+        case 512:
+            if (wide) return zl(k_kspace_zl_wide<T, 512>, kzl_cols<T, 512>(), 512 / Sched<512>::R0);
+            return zl(k_kspace_zl<T, 512, kzl_tile<T, 512>()>, kzl_cols<T, 512>(), 512 / Sched<512>::R0);
         case 1024:
-            if constexpr (sizeof(T) == 4)
+            if constexpr (sizeof(T) == 4) {
+                if (wide) return zl(k_kspace_zl_wide<T, 1024>, kzl_cols<T, 1024>(), 1024 / Sched<1024>::R0);
                 return zl(k_kspace_zl<T, 1024, kzl_tile<T, 1024>()>, kzl_cols<T, 1024>(), 1024 / Sched<1024>::R0);
+            }
             return false;
         default: return false;
         }

@@ -533,11 +533,17 @@ constexpr int kzl_cols()
     return c;
 }
 
-template <typename T, int P, int C>
+// WIDE: spectra or octants past the 2 GiB of a descriptor.  The places the work-group's waves
+// share (component, z step, octant component) are 64-bit scalar bases there, the rest a 32-bit
+// offset below 4 GiB; padding points load entry 0 of their base and drop it.  us a launch,
+// the LDS-staged pass -> this: 512x512x256 FP32 8072 -> 6586, 512x512x128 FP64 5151 -> 2907,
+// 1024x1024x64 FP32 4817 -> 2774, 320^3 FP32 padded to 1024 25846 -> 15454.
+template <typename T, int P, int C, bool WIDE = false>
 __device__ inline void body_kspace_zl(const KzArgs& a, int tile, cpx<T>* lds)
 {
     constexpr int R0 = Sched<P>::R0, TL = P / R0, NT = 3 * C * TL, LP = padded_len<P>();
     static_assert(Sched<P>::NS >= 2, "lines of 128 points or more");
+    static_assert(!WIDE || (C * TL) % 64 == 0, "a wave holds lines of one component");
     const int t = (int)threadIdx.x;
     const int l = t % C, u = (t / C) % TL, comp = t / (C * TL);
     const int col = tile * C + l;
@@ -547,7 +553,10 @@ __device__ inline void body_kspace_zl(const KzArgs& a, int tile, cpx<T>* lds)
     constexpr unsigned CS = sizeof(cpx<T>), TS = sizeof(T);
     const Buf g = buf_of(a.buf), K = buf_of(a.kern);
     const unsigned zs = (unsigned)a.ncols * CS;  // bytes from one z point to the next
-    const unsigned at = ((unsigned)comp * (unsigned)a.comp_stride + (unsigned)col) * CS + (unsigned)u * zs;
+    const unsigned at = WIDE ? (unsigned)l * CS + (unsigned)u * zs
+                             : ((unsigned)comp * (unsigned)a.comp_stride + (unsigned)col) * CS + (unsigned)u * zs;
+    char* const wide = (char*)a.buf +
+                       (__builtin_amdgcn_readfirstlane(comp) * a.comp_stride + (int64_t)tile * C) * (int64_t)CS;
     cpx<T>* ln = lds + (comp * C + l) * LP;
     LineTw<T, P> W;
     W.load(u, (const cpx<T>*)a.tw);
@@ -556,8 +565,16 @@ __device__ inline void body_kspace_zl(const KzArgs& a, int tile, cpx<T>* lds)
 #pragma unroll
     for (int r = 0; r < R0; ++r) {
         cpx<T> x = {(T)0, (T)0};
-        if (2 * r < R0)  // e >= P/2 is zero padding
+        if constexpr (WIDE) {
+            if (2 * r < R0) {
+                const bool in = u + TL * r < nz;
+                const char* from = wide + (TL * r < a.nz ? TL * r : 0) * (int64_t)zs;
+                const cpx<T> y = *reinterpret_cast<const cpx<T>*>(from + (in ? at : 0u));
+                x = cpx<T>{in ? y.re : (T)0, in ? y.im : (T)0};
+            }
+        } else if (2 * r < R0) {  // e >= P/2 is zero padding
             x = buf_ld<cpx<T>>(g, u + TL * r < nz ? at : kBufNone, (unsigned)(TL * r) * zs);
+        }
         v[r] = x;
     }
     // Eq. 14 spectra of the frequency pairs this thread takes (pair idx: column idx % C,
@@ -581,7 +598,12 @@ __device__ inline void body_kspace_zl(const KzArgs& a, int tile, cpx<T>* lds)
         }
         const unsigned ko = ((unsigned)kz * (unsigned)a.k_zs + (unsigned)kx * (unsigned)a.k_xs + (unsigned)ky) * TS;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) kv[it][c] = buf_ld<T>(K, in ? ko : kBufNone, (unsigned)c * kcs);
+        for (int c = 0; c < 6; ++c) {
+            if constexpr (WIDE)
+                kv[it][c] = *reinterpret_cast<const T*>((const char*)a.kern + c * a.k_cs * (int64_t)TS + (in ? ko : 0u));
+            else
+                kv[it][c] = buf_ld<T>(K, in ? ko : kBufNone, (unsigned)c * kcs);
+        }
         kv[it][1] *= sy;
         kv[it][4] *= sy;
     }
@@ -614,7 +636,11 @@ __device__ inline void body_kspace_zl(const KzArgs& a, int tile, cpx<T>* lds)
     __syncthreads();  // stage-1 reads of every line are done before LDS is rewritten
     finish_line<T, P, true>(ln, u, v, W, [&](int e, cpx<T> val) {
         // inverse by conjugation; e - u is a constant of the unrolled stage
-        buf_st(g, e < nz ? at : kBufNone, conj(val), (unsigned)(e - u) * zs);
+        if constexpr (WIDE) {
+            if (e < nz) *reinterpret_cast<cpx<T>*>(wide + (e - u) * (int64_t)zs + at) = conj(val);
+        } else {
+            buf_st(g, e < nz ? at : kBufNone, conj(val), (unsigned)(e - u) * zs);
+        }
     });
 }
 
