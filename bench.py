@@ -36,10 +36,14 @@ COPY_SCALE = {"FETCH_SIZE": 2.0, "WRITE_SIZE": 1.0}
 
 CSRC = os.path.join(ROOT, "paper_1501_07293_amd", "csrc")
 # translation unit that defines each kernel family
-KERNEL_TU = [("mm::kbf_", "mm_batch.hip"), ("mm::kb_", "mm_batch.hip"),
+KERNEL_TU = [("mm::kbr_", "mm_batch_rline.hip"), ("mm::kbf_", "mm_batch.hip"), ("mm::kb_", "mm_batch.hip"),
              ("mm::k_xfwd", "mm_fast.hip"), ("mm::k_xinv", "mm_fast.hip"),
-             ("mm::k_yline", "mm_fast.hip"), ("mm::k_kspace_z", "mm_fast.hip"),
+             ("mm::k_yline", "mm_fast.hip"), ("mm::k_kspace_z_mixed", "mm_zline.hip"),
+             ("mm::k_kspace_z", "mm_fast.hip"),
              ("mm::k_kspace_y", "mm_fast.hip"), ("mm::k_fused_", "mm_fused.hip"),
+             ("mm::k_rx", "mm_rline.hip"), ("mm::k_ry", "mm_rline.hip"), ("mm::k_rk", "mm_rline.hip"),
+             ("mm::k_rfused_", "mm_rfused.hip"), ("mm::k_plane", "mm_plane.hip"),
+             ("mm::k_tiny_steps", "mm_tiny.hip"),
              ("mm::k_llg_stage", "mm_llg.hip"),
              ("mm::k_row_", "mm_passes.hip"), ("mm::k_col_fft", "mm_passes.hip"),
              ("mm::k_kspace<", "mm_passes.hip"), ("mm::k_kspace_fixed", "mm_passes.hip")]
@@ -103,16 +107,18 @@ def recorded_traffic(kernel: str, workload: str) -> dict | None:
 
 def algorithmic_bytes(plan: dict, nx: int, ny: int, nz: int, esz: int) -> dict:
     """Bytes each kernel must move per launch (reads + writes of its inputs and
-    outputs once, nothing for the zero padding it never stores)."""
+    outputs once, nothing for the zero padding it never stores).  plan: mm_get_plan's, with
+    mm_get_routes' where it is of a handle (one launch may do the y and z passes)."""
     N = nx * ny * nz
     hx, Py = plan["hx"], plan["py"]
     cz = 2 * esz                           # one complex value
     real3 = 3 * N * esz                    # m or H, three components
     half_x = 3 * nz * ny * hx * cz         # after the x pass
-    if plan["passes"] == 1:                # one work-group: m in, field out, octant
+    passes = plan.get("launches", plan["passes"])
+    if passes == 1:                        # one work-group: m in, field out, octant
         b = {"x_fwd": 0, "y_fwd": 0, "kspace": 2 * real3 + plan["spectrum_elems"] * esz, "y_inv": 0,
              "x_inv": 0}
-    elif plan["passes"] == 5:
+    elif passes == 5:
         full_y = 3 * nz * Py * hx * cz     # after the y pass
         kern = plan["spectrum_elems"] * esz
         b = {"x_fwd": real3 + half_x, "y_fwd": half_x + full_y, "kspace": 2 * full_y + kern,
@@ -146,14 +152,14 @@ def run_gpu(args, cfg, precision: str, steps: int, warmup: int, profile: bool, r
     sim.set_hext(cfg.hext)
     m0 = random_unit_m(cfg.shape, seed=0)
     sim.set_m(m0)
-    plan = sim.plan()
+    plan = dict(sim.plan(), **sim.routes())
     sim.step(warmup, cfg.dt)
     torch.cuda.synchronize()
     per_kernel = {}
     if profile:
         # short untimed pass: average duration of every kernel class
         for k in KERNEL_IDS:
-            if plan["passes"] == 3 and k in ("y_fwd", "y_inv"):
+            if plan["launches"] == 3 and k in ("y_fwd", "y_inv"):
                 continue
             sim.profile_begin(k)
             sim.step(2, cfg.dt)
@@ -212,7 +218,7 @@ def batched_leg(steps: int, autotune: bool, warmup: int = 2, check: bool = False
     """512 uneven grids (nx, ny in [32, 128], nz in {1, 2}), FP32, one launch per pass
     over all grids, graph replay; value = total cells * steps / s.  autotune: the
     layout (padding and pass family) is timed at creation; otherwise `layout`:
-    "7smooth" (7-smooth padding, runtime-radix passes), "pow2" (power-of-two padding,
+    "7smooth" (7-smooth padding, runtime-length passes), "pow2" (power-of-two padding,
     size-class passes) or "fast" (powers of two and 96, 160, 192, 224, size-class
     passes)."""
     import torch
@@ -249,7 +255,7 @@ def batched_leg(steps: int, autotune: bool, warmup: int = 2, check: bool = False
            "padding": {"pow2": "power of two", "fast": "powers of two and 96, 160, 192, 224",
                        "7-smooth": "7-smooth"}[pad],
            "step_model_bytes_per_cell": step_bytes / b.cells,
-           "passes": "size classes" if info["size_classes"] else "runtime radix",
+           "passes": "size classes" if info["size_classes"] else "runtime length",
            "autotuned": bool(info["tuned"]), "layouts_timed": info["candidates"],
            "repeats": len(times)}
     if check:
@@ -271,7 +277,7 @@ def periodic_leg(steps: int, warmup: int = 3) -> dict:
                  precision="f32", periodic=(True, True, False), device="cuda:0")
     sim.set_hext(c.hext)
     sim.set_m(synthetic.random_unit_m(c.shape, seed=0))
-    plan = sim.plan()
+    plan = dict(sim.plan(), **sim.routes())
     sim.step(warmup, c.dt)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -500,7 +506,7 @@ def mid_leg(args, steps: int) -> dict:
                         f"padded FFT {plan['px']}x{plan['py']}x{plan['pz']}",
             "steps": steps, "repeats": len(times), "ms_per_step": 1e3 * med / steps,
             "value": c.N * steps / med, "unit": "cell-updates/s", "dtype": "f32", "graph": True,
-            "schedule": {k: plan[k] for k in ("passes", "generic_fft", "threads", "tuned", "candidates")},
+            "schedule": {k: plan[k] for k in ("passes", "launches", "mid", "stage", "generic_fft", "threads", "tuned", "candidates")},
             "err": {"demag_field_rel_max": err, "cells": nobs, "tolerance": 1e-5}}
 
 
@@ -589,7 +595,7 @@ def main():
         "config": {"workload": f"{cfg.name} cells={cfg.N} cell={cfg.cell:g} m, RK4 dt={cfg.dt:g} s, "
                                f"padded FFT {plan['px']}x{plan['py']}x{plan['pz']}",
                    "precision": args.precision, "graph": bool(args.graph),
-                   "fft_passes_per_field": plan["passes"], "threads_per_fft_wg": plan["threads"]},
+                   "fft_passes_per_field": plan["launches"], "threads_per_fft_wg": plan["threads"]},
         "timing": {"repeats": len(times), "statistic": "median",
                    "ms_per_step_each": [1e3 * t / args.steps for t in times]},
     }
@@ -621,7 +627,7 @@ def main():
         out["step_model_bytes_per_cell"] = step_bytes / cfg.N
         out["algorithmic_bytes"] = ab
         out["plan"] = {k: plan[k] for k in ("px", "py", "pz", "passes", "threads", "generic_fft", "x_lines",
-                                            "x_lines_inv")}
+                                            "x_lines_inv", "launches", "mid", "stage")}
         out["plan"]["n"] = [cfg.nx, cfg.ny, cfg.nz]
         out["effective_gbs"] = step_bytes / (secs / args.steps) / 1e9
     out["sources_sha256"] = {tu: tu_digest(tu) for tu in sorted({t for _, t in KERNEL_TU})}
@@ -691,7 +697,10 @@ def mm_kernel_symbol(k: str, precision: str, plan: dict, n: tuple | None = None)
     """Symbol of the kernel the library launches for pass k under this plan (the
     size-specialised one where it exists, as the library's dispatch decides).
     n = (nx, ny, nz): an axis whose cells fill more than half its FFT length (a
-    periodic axis) takes the whole-line instantiation; without n none is assumed."""
+    periodic axis) takes the whole-line instantiation; without n none is assumed.  With the
+    handle's routes (mm_get_routes) in plan the passes that do several at once and the
+    runtime-length ones are named too, the latter without their template arguments; without
+    them the passes are taken to run apart."""
     t = "float" if precision == "f32" else "double"
     fast = not plan.get("generic_fft", 0)
     px, py, pz = plan["px"], plan["py"], plan["pz"]
@@ -701,6 +710,8 @@ def mm_kernel_symbol(k: str, precision: str, plan: dict, n: tuple | None = None)
     x_ok = fast and pow2(px) and 16 <= px <= (2048 if t == "float" else 1024)
     y_ok = fast and pow2(py) and 16 <= py <= 2048
     if k == "llg":
+        if plan.get("stage") == 2:
+            return "mm::k_rfused_stage"
         if plan.get("fused_stage"):
             # the fused stage pass's row pairs per work-group, as the library picks them:
             # by the ny nz rows, one line from 512 points, at most 512 threads (3 lines of
@@ -716,8 +727,24 @@ def mm_kernel_symbol(k: str, precision: str, plan: dict, n: tuple | None = None)
         kz = 1 if nz == 1 else 2   # planes per thread
         ty = 2 if nx % 128 == 0 and ny % 2 == 0 else 1   # rows per work-group tile
         return f"mm::k_llg_stage<{t}, {kz}, {ty}>"
-    if plan["passes"] == 1:
+    passes = plan.get("launches", plan["passes"])
+    if passes == 1:
         return f"mm::k_demag_1wg<{t}, {plan['threads']}>"
+    if "mid" in plan:
+        if plan["mid"] in (3, 4) and k == "kspace":
+            return {3: "mm::k_plane", 4: "mm::k_ryz"}[plan["mid"]]
+        mixed = (96, 160, 192, 224)   # the size-specialised lengths that are no powers of two
+        if k in ("x_fwd", "x_inv") and not (fast and px in mixed) and not x_ok:
+            return {"x_fwd": "mm::k_rxfwd", "x_inv": "mm::k_rxinv"}[k]
+        if k in ("y_fwd", "y_inv") and not (fast and py in mixed) and not y_ok:
+            return "mm::k_ryline"
+        if k == "kspace" and plan["mid"] == 1 and not (fast and pow2(pz)):
+            reg = (3, 5, 6, 7, 9, 10, 12, 14, 15, 18, 20, 21, 24, 25, 28, 30)
+            return f"mm::k_kspace_z_mixed<{t}, {pz}>" if fast and pz in reg else "mm::k_rkz"
+        if k == "kspace" and plan.get("long_z") == 2:
+            return f"mm::k_kspace_zl_wide<{t}, {pz}>"
+        if k == "kspace" and plan["mid"] == 0 and not (fast and py in mixed) and not (y_ok and py <= 1024):
+            return "mm::k_rky"
     if k in ("x_fwd", "x_inv"):
         lines = plan.get("x_lines", 8) if k == "x_fwd" else plan.get("x_lines_inv", 4)
         return f"mm::k_{'xfwd' if k == 'x_fwd' else 'xinv'}<{t}, {px}, {lines}, {b(2 * nx > px)}>" \
@@ -726,7 +753,7 @@ def mm_kernel_symbol(k: str, precision: str, plan: dict, n: tuple | None = None)
     if k in ("y_fwd", "y_inv"):
         return f"mm::k_yline<{t}, {py}, {b(k == 'y_inv')}, {b(2 * ny > py)}>" if y_ok else \
             f"mm::k_col_fft<{t}, {plan['threads']}>"
-    if plan["passes"] == 5:
+    if passes == 5:
         z_ok = fast and pow2(pz) and 2 <= pz <= (64 if t == "float" else 32)
         if z_ok:
             # FP64 lines whose upper half is zero: two lanes per line

@@ -96,7 +96,7 @@ typedef enum {
  * per field evaluation instead of five).  Off by default: on the smaller planes the
  * library runs a fused pass by itself, with up to 12 points along z one that keeps the
  * z lines in registers (256x64x4 FP32: 76 against 88 us per RK4 step with this flag and
- * 87 with five passes; plan_info still counts five), and on the larger ones five passes
+ * 87 with five passes; mm_get_routes tells which runs), and on the larger ones five passes
  * are faster; MM_AUTOTUNE times both schedules where this one applies. */
 #define MM_FUSED_YZ 0x400u
 /* Grids whose padded volume of the three components fits one work-group's LDS
@@ -176,12 +176,12 @@ typedef struct {
     int32_t px, py, pz;  /* padded sizes */
     int32_t hx;          /* px/2 + 1 stored half-spectrum bins along x */
     int32_t ncomp;       /* 6 kernel spectra, or 4 (xx, xy, yy, zz) when nz == 1 */
-    int32_t threads;     /* FFT work-group size in use */
+    int32_t threads;     /* work-group size of the LDS-staged FFT passes */
     int64_t spectrum_elems; /* elements of the kernel spectrum: the octant, ncomp*(pz/2+1)*hx*(py/2+1),
                                or with two_plane the 10*hx*(py/2+1) coefficient planes */
     int32_t passes;      /* FFT passes per field evaluation (1 with MM_ONE_WG in use, 3 for
                             nz == 1, the two-plane schedule or MM_FUSED_YZ in use, else 5,
-                            also where a fused y-z pass runs by itself) */
+                            also where one launch does three of them by itself: mm_get_routes) */
     double kernel_imag_ratio; /* max |Im| / max |Re| of the FP64 kernel spectrum (should be ~1e-16) */
     int32_t generic_fft; /* 1 when the runtime-length passes are forced */
     int32_t tuned;       /* 1 when the schedule came from the autotuner */
@@ -199,7 +199,7 @@ typedef struct {
                             offset +1, the observer above the source; at offset +1 the xz and
                             yz spectra are i sxz and i syz) */
     int32_t fused_stage; /* 1: RK4 stages run the size-specialised fused stage pass (see
-                            MM_SPLIT_STAGE); 0 also where its runtime-length form runs */
+                            MM_SPLIT_STAGE); 0 also where its runtime-length form runs (mm_get_routes) */
 } mm_plan_info;
 
 typedef struct mm_sim mm_sim;
@@ -295,6 +295,37 @@ mm_status mm_get_mean_m(mm_sim* sim, double out[3]);
 mm_status mm_get_max_torque(mm_sim* sim, double* out);
 
 mm_status mm_get_plan(mm_sim* sim, mm_plan_info* out);
+
+/* What a handle's calls launch (mm_plan_info describes the transforms: its `passes` counts
+ * the transform passes of a field evaluation whether or not a launch does several of them, its
+ * `fused_stage` the size-specialised fused stage alone). */
+enum {
+    MM_MID_Y = 0,         /* the y k-space pass of a one-cell-thick grid */
+    MM_MID_SEPARATE = 1,  /* y forward, z k-space, y inverse: three launches */
+    MM_MID_TWO_PLANE = 2, /* the two-plane y k-space pass */
+    MM_MID_PLANE = 3,     /* the plane pass: y, z and back, z lines in registers */
+    MM_MID_FUSED_YZ = 4,  /* the fused y-z pass, z lines through LDS (by itself or MM_FUSED_YZ) */
+    MM_MID_ONE_WG = 5     /* MM_ONE_WG: the whole evaluation, x passes included */
+};
+enum {
+    MM_STAGE_SEPARATE = 0, /* x inverse, stage update and x forward: three launches */
+    MM_STAGE_FUSED = 1,    /* the fused stage pass, size-specialised */
+    MM_STAGE_FUSED_ANY = 2 /* the fused stage pass of runtime length */
+};
+enum {
+    MM_ZLINE_NONE = 0,     /* another z pass, or none */
+    MM_ZLINE_LONG = 1,     /* power-of-two lines of 128 points and more, registers and LDS */
+    MM_ZLINE_LONG_WIDE = 2 /* the same where the spectrum or the octant is past 2 GiB */
+};
+typedef struct {
+    int32_t launches;       /* launches of a field evaluation outside the steps (mm_get_field) */
+    int32_t mid;            /* MM_MID_*: what runs between the x passes */
+    int32_t stage;          /* MM_STAGE_*: what runs after it in a step */
+    int32_t one_launch_rk4; /* 1: mm_step runs all stages of its steps in one launch (of up to 4096
+                               steps); with a profile open it runs the passes above */
+    int32_t long_z;         /* MM_ZLINE_*: the z k-space pass of MM_MID_SEPARATE */
+} mm_route_info;
+mm_status mm_get_routes(mm_sim* sim, mm_route_info* out);
 
 /* Kernel-spectrum octant [ncomp][pz/2+1][hx][py/2+1] (ky fastest), working
  * precision, already scaled by 1/(px py pz) (the normalisation of the inverse

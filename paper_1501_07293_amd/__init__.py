@@ -31,12 +31,15 @@ MM_FAST_PAD = 0x1000
 MM_RK4, MM_EULER = 0, 1
 MM_NOALLOC_SCRATCH_BYTES = 96 << 20  # static adjoint scratch of mm_backward_noalloc
 TERMS = {"exch": 0, "anis": 1, "demag": 2, "ext": 3, "eff": 4}
+MID_Y, MID_SEPARATE, MID_TWO_PLANE, MID_PLANE, MID_FUSED_YZ, MID_ONE_WG = range(6)
+STAGE_SEPARATE, STAGE_FUSED, STAGE_FUSED_ANY = range(3)
+ZLINE_NONE, ZLINE_LONG, ZLINE_LONG_WIDE = range(3)
 KERNELS = {"x_fwd": 0, "y_fwd": 1, "kspace": 2, "y_inv": 3, "x_inv": 4, "llg": 5}
 
 EXPORTS = ["mm_workspace_query", "mm_create", "mm_destroy", "mm_set_stream", "mm_set_m", "mm_get_m",
            "mm_set_hext", "mm_set_alpha", "mm_set_ku_map", "mm_step", "mm_step_euler", "mm_run_schedule",
            "mm_get_field",
-           "mm_get_energy", "mm_get_mean_m", "mm_get_max_torque", "mm_get_plan", "mm_get_kernel_spectrum",
+           "mm_get_energy", "mm_get_mean_m", "mm_get_max_torque", "mm_get_plan", "mm_get_routes", "mm_get_kernel_spectrum",
            "mm_demag_tensor", "mm_demag_tensor_newell", "mm_batch_workspace_query", "mm_batch_create", "mm_batch_destroy",
            "mm_batch_set_stream", "mm_batch_set_m", "mm_batch_get_m", "mm_batch_step", "mm_batch_get_field",
            "mm_batch_cells", "mm_batch_get_info", "mm_batch_get_grid_plan", "mm_rollout", "mm_adjoint_workspace_query", "mm_backward", "mm_backward_noalloc", "mm_normalize_backward",
@@ -82,6 +85,11 @@ class PlanInfo(ctypes.Structure):
                 ("fused_stage", ctypes.c_int32)]
 
 
+class RouteInfo(ctypes.Structure):
+    _fields_ = [("launches", ctypes.c_int32), ("mid", ctypes.c_int32), ("stage", ctypes.c_int32),
+                ("one_launch_rk4", ctypes.c_int32), ("long_z", ctypes.c_int32)]
+
+
 class BatchInfo(ctypes.Structure):
     _fields_ = [("cells", ctypes.c_int64), ("n", ctypes.c_int32), ("pow2_pad", ctypes.c_int32),
                 ("size_classes", ctypes.c_int32), ("tuned", ctypes.c_int32),
@@ -120,6 +128,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "mm_get_mean_m": [vp, ctypes.POINTER(dbl)],
         "mm_get_max_torque": [vp, ctypes.POINTER(dbl)],
         "mm_get_plan": [vp, ctypes.POINTER(PlanInfo)],
+        "mm_get_routes": [vp, ctypes.POINTER(RouteInfo)],
         "mm_get_kernel_spectrum": [vp, vp, ctypes.c_int],
         "mm_demag_tensor": [i32, i32, i32, vp, vp],
         "mm_demag_tensor_newell": [i32, i32, i32, vp, vp],
@@ -332,6 +341,12 @@ class Sim:
         p = PlanInfo()
         _check(self._lib.mm_get_plan(self._h, ctypes.byref(p)), "mm_get_plan")
         return {k: getattr(p, k) for k, _ in PlanInfo._fields_}
+
+    def routes(self) -> dict:
+        """What the handle's calls launch (mm_route_info: MID_*, STAGE_*, ZLINE_*)."""
+        r = RouteInfo()
+        _check(self._lib.mm_get_routes(self._h, ctypes.byref(r)), "mm_get_routes")
+        return {k: getattr(r, k) for k, _ in RouteInfo._fields_}
 
     def kernel_spectrum(self):
         p = self.plan()

@@ -2915,6 +2915,25 @@ mm_status mm_get_plan(mm_sim* s, mm_plan_info* out)
     return MM_OK;
 }
 
+mm_status mm_get_routes(mm_sim* s, mm_route_info* out)
+{
+    if (!s || !out) return fail(MM_EINVAL, "sim or out is NULL");
+    const Plan& p = s->p;
+    *out = mm_route_info{};
+    out->mid = p.wg1          ? MM_MID_ONE_WG
+               : p.zd         ? MM_MID_TWO_PLANE
+               : !p.three_d   ? MM_MID_Y
+               : p.plane_nt   ? MM_MID_PLANE
+               : p.yz || p.yz_small ? MM_MID_FUSED_YZ
+                              : MM_MID_SEPARATE;
+    out->launches = p.wg1 ? 1 : (out->mid == MM_MID_SEPARATE ? 5 : 3);
+    out->stage = !p.fs ? MM_STAGE_SEPARATE : (p.fs_rt ? MM_STAGE_FUSED_ANY : MM_STAGE_FUSED);
+    out->one_launch_rk4 = p.tiny ? 1 : 0;
+    if (out->mid == MM_MID_SEPARATE && !(s->flags & MM_GENERIC_FFT))
+        out->long_z = kspace_zl_form(p.Pz, p.nz, (int64_t)p.nz * p.hx * p.Py, p.oct_elems, p.esz);
+    return MM_OK;
+}
+
 mm_status mm_get_kernel_spectrum(mm_sim* s, void* out, int on_device)
 {
     if (!s || !out) return fail(MM_EINVAL, "sim or out is NULL");

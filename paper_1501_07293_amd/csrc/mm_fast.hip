@@ -169,6 +169,15 @@ bool launch_xline(const XLineArgs& a, int P, int inverse, hipStream_t s)
     return 2 * a.nx > P ? xline_lines<T, true>(a, P, inverse, s) : xline_lines<T, false>(a, P, inverse, s);
 }
 
+int kspace_zl_form(int PZ, int nz, int64_t comp_stride, int64_t k_cs, size_t esz)
+{
+    if (3 * comp_stride > INT32_MAX || 6 * k_cs > INT32_MAX || 2 * nz > PZ) return 0;
+    if (PZ != 128 && PZ != 256 && PZ != 512 && !(PZ == 1024 && esz == 4)) return 0;
+    // One descriptor each for the spectrum and the octant; past 2 GiB the wide form.  (An octant
+    // below it keeps P / 2 z steps, the largest scalar offset, below it too.)
+    return 3 * comp_stride * 2 * (int64_t)esz >= kRLineBytes || 6 * k_cs * (int64_t)esz >= kRLineBytes ? 2 : 1;
+}
+
 template <typename T>
 bool launch_kspace_z(const KzArgs& a, int PZ, hipStream_t s)
 {
@@ -197,29 +206,22 @@ bool launch_kspace_z(const KzArgs& a, int PZ, hipStream_t s)
         hipLaunchKernelGGL(kern, dim3(zgrid), dim3(3 * C * tl), 0, s, a);
         return true;
     };
-    if (PZ >= 128 && 2 * a.nz <= PZ) {
-        // One descriptor each for the spectrum and the octant; past 2 GiB the wide form.  (An
-        // octant below it keeps P / 2 z steps, the largest scalar offset, below it too.)
-        const bool wide = 3 * a.comp_stride * 2 * (int64_t)sizeof(T) >= kRLineBytes ||
-                          6 * a.k_cs * (int64_t)sizeof(T) >= kRLineBytes;
+    if (const int form = kspace_zl_form(PZ, a.nz, a.comp_stride, a.k_cs, sizeof(T))) {
+        auto either = [&](auto kern, auto kern_wide, int C, int tl) { return form == 2 ? zl(kern_wide, C, tl) : zl(kern, C, tl); };
+#define MM_ZLCASE(PP)                                                                                            \
+    case PP:                                                                                                     \
+        return either(k_kspace_zl<T, PP, kzl_tile<T, PP>()>, k_kspace_zl_wide<T, PP>, kzl_cols<T, PP>(), PP / Sched<PP>::R0);
         switch (PZ) {
-        case 128:
-            if (wide) return zl(k_kspace_zl_wide<T, 128>, kzl_cols<T, 128>(), 128 / Sched<128>::R0);
-            return zl(k_kspace_zl<T, 128, kzl_tile<T, 128>()>, kzl_cols<T, 128>(), 128 / Sched<128>::R0);
-        case 256:
-            if (wide) return zl(k_kspace_zl_wide<T, 256>, kzl_cols<T, 256>(), 256 / Sched<256>::R0);
-            return zl(k_kspace_zl<T, 256, kzl_tile<T, 256>()>, kzl_cols<T, 256>(), 256 / Sched<256>::R0);
-        case 512:
-            if (wide) return zl(k_kspace_zl_wide<T, 512>, kzl_cols<T, 512>(), 512 / Sched<512>::R0);
-            return zl(k_kspace_zl<T, 512, kzl_tile<T, 512>()>, kzl_cols<T, 512>(), 512 / Sched<512>::R0);
-        case 1024:
+            MM_ZLCASE(128)
+            MM_ZLCASE(256)
+            MM_ZLCASE(512)
+        default:
             if constexpr (sizeof(T) == 4) {
-                if (wide) return zl(k_kspace_zl_wide<T, 1024>, kzl_cols<T, 1024>(), 1024 / Sched<1024>::R0);
-                return zl(k_kspace_zl<T, 1024, kzl_tile<T, 1024>()>, kzl_cols<T, 1024>(), 1024 / Sched<1024>::R0);
+                switch (PZ) { MM_ZLCASE(1024) }
             }
             return false;
-        default: return false;
         }
+#undef MM_ZLCASE
     }
     switch (PZ) {
     case 2: hipLaunchKernelGGL((k_kspace_z<T, 2>), dim3(grid), dim3(3 * ZC), 0, s, a); return true;

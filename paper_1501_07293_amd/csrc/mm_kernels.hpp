@@ -273,6 +273,9 @@ template <typename T>
 bool launch_xline(const XLineArgs& a, int P, int inverse, hipStream_t s);
 template <typename T>
 bool launch_kspace_z(const KzArgs& a, int PZ, hipStream_t s);
+// The long-line form it takes: 0 none, 1 one descriptor each for the spectrum and the octant, 2
+// the wide form past 2 GiB.
+int kspace_zl_form(int PZ, int nz, int64_t comp_stride, int64_t k_cs, size_t esz);
 
 // The same for lengths other than powers of two, up to 30 points (one line in a thread's
 // registers); false for the others.
