@@ -99,6 +99,10 @@ typedef enum {
  * 87 with five passes; mm_get_routes tells which runs), and on the larger ones five passes
  * are faster; MM_AUTOTUNE times both schedules where this one applies. */
 #define MM_FUSED_YZ 0x400u
+/* 3-D grids run y forward, z k-space and y inverse as three passes, also where one launch would
+ * do all three (MM_FUSED_YZ, which it takes precedence over, and the passes the library runs by
+ * itself on small planes).  The two-plane schedule and MM_ONE_WG are not affected. */
+#define MM_SPLIT_YZ 0x4000u
 /* Grids whose padded volume of the three components fits one work-group's LDS
  * (3 px py pz <= 16 x threads, e.g. 32x8x1 at 64x16 points): one work-group runs
  * the whole demag evaluation (every x, y and z transform of the padded volume,
@@ -162,7 +166,7 @@ typedef struct {
                             A periodic axis takes n (0 or n accepted). */
     uint32_t flags;      /* MM_NO_DEMAG | MM_USE_GRAPH | MM_GENERIC_FFT | MM_AUTOTUNE | MM_POW2_PAD | MM_FAST_PAD |
                             MM_NEWELL | MM_PER_GRID_MATERIAL (batches) | MM_PERIODIC_X/Y/Z |
-                            MM_FUSED_YZ | MM_ONE_WG | MM_SPLIT_STAGE (single-grid handles) */
+                            MM_FUSED_YZ | MM_SPLIT_YZ | MM_ONE_WG | MM_SPLIT_STAGE (single-grid handles) */
     int32_t threads;     /* threads per FFT work-group: 0 = automatic, 256 or 512 */
     int32_t x_lines;     /* row pairs per work-group of the size-specialised x passes:
                             0 = automatic (FP32 8 forward, 4 inverse; FP64 4 and 4 at

@@ -278,7 +278,8 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_pl
     (void)make_line_plan(p->Py, &p->ly);
     (void)make_line_plan(p->Pz, &p->lz);
     p->rs = rline_shapes(p->lx, p->ly, p->lz, p->nx, p->ny, p->nz, p->esz, 512, 256);
-    p->yz = p->three_d && (o->flags & MM_FUSED_YZ) && 3LL * p->Py * p->Pz <= (int64_t)kElemsPerThread * nt &&
+    const bool split_yz = (o->flags & MM_SPLIT_YZ) != 0;
+    p->yz = p->three_d && (o->flags & MM_FUSED_YZ) && !split_yz && 3LL * p->Py * p->Pz <= (int64_t)kElemsPerThread * nt &&
             p->rs.yz > 0;
     p->wg1 = (o->flags & MM_ONE_WG) && !(o->flags & MM_NO_DEMAG) &&
              3LL * p->Px * p->Py * p->Pz <= (int64_t)kElemsPerThread * nt;
@@ -313,9 +314,10 @@ mm_status build_plan(const mm_grid* g, const mm_options* o, Plan* p, bool two_pl
             ((!(o->flags & MM_GENERIC_FFT) && fast_ky2_lines(p->Py) > 0 && !(p->esz == 8 && p->Py > 1024)) ||
              (two_plane && batch_shapes(*p).ky2 > 0));
     p->plane_nt = 0;
-    if (p->three_d && !p->yz && !p->zd && !p->wg1 && !(o->flags & MM_GENERIC_FFT))
+    if (p->three_d && !p->yz && !p->zd && !p->wg1 && !split_yz && !(o->flags & MM_GENERIC_FFT))
         p->plane_nt = plane_threads(p->ly, p->Pz, p->hx, p->nz, p->esz, &p->plane_lines);
-    p->yz_small = p->three_d && p->plane_nt == 0 && !p->yz && !p->zd && !p->wg1 && p->rs.yz > 0 && yz_is_small(*p, (o->flags & MM_GENERIC_FFT) != 0);
+    p->yz_small = p->three_d && p->plane_nt == 0 && !p->yz && !p->zd && !p->wg1 && !split_yz && p->rs.yz > 0 &&
+                  yz_is_small(*p, (o->flags & MM_GENERIC_FFT) != 0);
     // open, small (latency-bound), with the specialised passes: the fused stage pass
     // (the y / z passes of one-cell-thick and thicker grids run between its launches)
     p->fs_lines = 0;
