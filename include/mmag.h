@@ -131,8 +131,10 @@ typedef enum {
 #define MM_AUTOTUNE 0x8u    /* mm_create times the candidate schedules of this grid (padded sizes
                                7-smooth vs power of two, specialised vs runtime-length passes,
                                256 vs 512 threads, x lines per work-group, fused y-z pass, one
-                               work-group) and keeps the fastest.  The candidates run in the
-                               caller's workspace when it holds every one of them (the size
+                               work-group) and keeps the fastest: by RK4 and Euler steps where
+                               a candidate fuses their stages (MM_SPLIT_STAGE), else by a field
+                               evaluation.  The candidates run in the caller's workspace when it
+                               holds every one of them (the size
                                mm_workspace_query returns with this flag), else in one temporary
                                workspace that mm_create allocates and frees; the kernel spectrum
                                is built once per candidate padded size.  Results are cached per
