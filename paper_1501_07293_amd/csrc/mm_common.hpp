@@ -92,4 +92,12 @@ __device__ inline int xcd_tile(int b, int nb)
     return xcd * per + (xcd < rem ? xcd : rem) + local;
 }
 
+// The same in whole groups of `group` tiles that share cache lines: an XCD's range holds no
+// part of a group, but for the last tiles (fewer than 8 groups), which stay in order.
+__device__ inline int xcd_tile(int b, int nb, int group)
+{
+    const int whole = nb / (8 * group) * (8 * group);
+    return b < whole ? (b & 7) * (whole >> 3) + (b >> 3) : b;
+}
+
 }  // namespace mm

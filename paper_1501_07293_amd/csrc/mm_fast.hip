@@ -19,14 +19,14 @@ __global__ __launch_bounds__(L * (P / Sched<P>::R0)) void k_xfwd(XLineArgs a)
     body_xfwd<T, P, L, FULL>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
 }
 
-// C: the columns kzl_tile<T, P>() that share an XCD
+// C: the columns, kzl_tile<T, P>(), whose work-groups share an XCD
 template <typename T, int P, int C>
 __global__ __launch_bounds__((3 * kzl_cols<T, P>() * (P / Sched<P>::R0))) void k_kspace_zl(KzArgs a)
 {
     constexpr int CW = kzl_cols<T, P>();
     static_assert(C % CW == 0, "whole work-groups a tile");
     __shared__ cpx<T> lds[3 * CW * padded_len<P>()];
-    body_kspace_zl<T, P, CW>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
+    body_kspace_zl<T, P, CW>(a, xcd_tile(blockIdx.x, gridDim.x, C / CW), lds);
 }
 
 template <typename T, int P>
@@ -34,7 +34,7 @@ __global__ __launch_bounds__((3 * kzl_cols<T, P>() * (P / Sched<P>::R0))) void k
 {
     constexpr int CW = kzl_cols<T, P>();
     __shared__ cpx<T> lds[3 * CW * padded_len<P>()];
-    body_kspace_zl<T, P, CW, true>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
+    body_kspace_zl<T, P, CW, true>(a, xcd_tile(blockIdx.x, gridDim.x, kzl_tile<T, P>() / CW), lds);
 }
 
 template <typename T, int P, int L, bool FULL>

@@ -512,9 +512,9 @@ __device__ inline void body_kspace_z(const KzArgs& a, int tile, cpx<T>* sh)
 // frequency 121); 64^3 FP32 32 columns 16.9 -> 11.9 with 8, FP64 16 columns 24.8 -> 18.9 with
 // 8; 256^3 FP32 4 columns 1428 -> 1203 with 2, FP64 2 columns 2628 but 2133 with 4; FP64
 // 128^3 235 with 4, 198 with 8.
-// Neighbouring work-groups run on one XCD (xcd_tile): kzl_tile columns, one 128-byte
-// segment per z point at FP32 and 256 points, are worked by kzl_tile / kzl_cols of them,
-// which find each other's half segments in its L2.
+// kzl_tile columns (one 128-byte segment per z point at FP32 and 256 points) are worked by
+// kzl_tile / kzl_cols neighbouring work-groups of one XCD (xcd_tile in groups of them), which
+// find each other's half segments in its L2.
 template <typename T, int P>
 constexpr int kzl_tile()
 {
