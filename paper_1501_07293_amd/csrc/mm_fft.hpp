@@ -325,15 +325,15 @@ template <typename T>
 __device__ inline cpx<T> w25(int j)
 {
     switch (j) {
-    case 1: return {(T)0.96858316112863108, (T)-0.24868988716485479};
-    case 2: return {(T)0.87630668004386358, (T)-0.48175367410171532};
-    case 3: return {(T)0.72896862742141155, (T)-0.68454710592868862};
-    case 4: return {(T)0.53582679497899655, (T)-0.84432792550201508};
-    case 6: return {(T)0.062790519529313527, (T)-0.99802672842827156};
-    case 8: return {(T)-0.42577929156507272, (T)-0.90482705246601947};
-    case 9: return {(T)-0.63742398974868975, (T)-0.77051324277578925};
-    case 12: return {(T)-0.99211470131447776, (T)-0.12533323356430454};
-    default: return {(T)-0.63742398974868952, (T)0.77051324277578936};  // 16
+    case 1: return {(T)0.96858316112863111949, (T)-0.24868988716485478824};
+    case 2: return {(T)0.87630668004386358731, (T)-0.48175367410171527499};
+    case 3: return {(T)0.72896862742141152315, (T)-0.68454710592868867373};
+    case 4: return {(T)0.53582679497899661827, (T)-0.84432792550201507855};
+    case 6: return {(T)0.06279051952931337608, (T)-0.99802672842827156195};
+    case 8: return {(T)-0.42577929156507264886, (T)-0.90482705246601952771};
+    case 9: return {(T)-0.63742398974868971018, (T)-0.77051324277578923080};
+    case 12: return {(T)-0.99211470131447783105, (T)-0.12533323356430424537};
+    default: return {(T)-0.63742398974868971018, (T)0.77051324277578923080};  // 16
     }
 }
 template <typename T>
