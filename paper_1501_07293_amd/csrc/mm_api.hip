@@ -1744,10 +1744,10 @@ mm_status batch_layout(int32_t n, const mm_grid* grids, const mm_options* opt, B
     mm_options o = opt ? *opt : mm_options{};
     o.threads = 256;
     // size classes (the specialised passes) are wanted with power-of-two or fast
-    // padding; otherwise every grid runs the runtime-length passes, whose plans
-    // must not take the two-plane schedule.  If some grid has no size class, the
-    // layout is built again that way, with the register passes where every grid has
-    // them, else with the LDS-staged ones.
+    // padding; otherwise every grid runs the runtime-length passes.  If some grid has no
+    // size class, the layout is built again that way: with the register passes (attempt 1,
+    // grids two cells thick under the two-plane schedule) where every grid has them, else
+    // with the LDS-staged ones (attempt 2), which have no two-plane form.
     const bool want_fast = (o.flags & (MM_POW2_PAD | MM_FAST_PAD)) && !(o.flags & MM_GENERIC_FFT);
     for (int attempt = want_fast ? 0 : 1; attempt < 3; ++attempt) {
         mm_options oa = o;

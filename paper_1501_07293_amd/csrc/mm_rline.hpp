@@ -3,8 +3,8 @@
 //
 // A line of P points is worked by TL = P / (its smallest radix) threads, one
 // butterfly per thread and stage: the radices of a LinePlan (2 .. 16, composites
-// such as 6, 10, 12, 14 and 15 included, so lengths up to 256 take two stages and up
-// to 4096 mostly three) are chosen on the host, and each stage switches on its radix
+// such as 6, 10, 12, 14 and 15 included, so lengths up to 256 take one or two stages, a dozen
+// of them three to five, and up to 4096 mostly three) are chosen on the host, and each stage switches on its radix
 // (the same for the whole work-group) to a body unrolled for it.  The first stage
 // takes its inputs straight from where they are (global memory, or LDS for an inverse
 // after the k-space product), the stages between exchange through LDS, and the last

@@ -21,7 +21,7 @@ constexpr int kTinyMaxThreads = 512;
 constexpr int kTinyRadix = 8;               // radices up to
 constexpr int kTinyPairs = 2;               // frequency pairs a thread takes
 constexpr size_t kTinyLds = 64 * 1024;
-constexpr int64_t kTinyStepsPerLaunch = 4096;  // some tens of milliseconds
+constexpr int64_t kTinyStepsPerLaunch = 4096;  // 63 to 124 ms at 15.5 to 30.2 us a step
 
 // LDS: the stage input and the demag field [3][2 np][nx + 1] (np = ceil(ny / 2) row pairs; the
 // last column and an odd grid's last row read as zero), the x lines [3][np], the spectrum

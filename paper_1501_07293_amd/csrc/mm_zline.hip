@@ -3,9 +3,12 @@
 //
 // One thread holds a whole z line of one component, as in the power-of-two pass; the
 // runtime-length pass (mm_rline.hpp) exchanges its stages through LDS and holds a radix's
-// worth of registers for every length it serves.  Memory and its own butterflies bound it alike;
-// per launch, that pass -> this one: 301x190x6 (12 points) FP32 15.7 -> 9.9 us, 360x300x10
-// periodic in x and y (20 points) 24.9 -> 12.3.
+// worth of registers for every length it serves.  Memory and its own butterflies bound it alike.
+// It is the faster at every length below, in both precisions, also where FP64 lines take 244
+// registers.  us a launch, that pass -> this one, FP32 and FP64: 200x150 cells a plane, 3 points
+// 7.1 -> 6.8 and 9.6 -> 7.8, 12 points 10.5 -> 9.4 and 16.3 -> 13.0, 15 points 11.8 -> 11.4 and
+// 19.9 -> 16.0, 30 points 31.3 -> 17.4 and 66.5 -> 28.2; 400x380: 7 points 19.5 -> 15.8 and 28.8 ->
+// 27.1, 20 points 64.2 -> 33.2 and 142.1 -> 77.8, 30 points 122 -> 50.1 and 341 -> 116.
 #include "mm_fast.hpp"
 
 namespace mm {
